@@ -356,6 +356,78 @@ __device__ __forceinline__ void merge_lead16(uint32_t& lab, float& wt, bool unit
   }
 }
 
+// Per-label sums of a row of up to 16 U entries held in registers by the 16
+// lanes of one DPP row, U entries per lane (kEmpty: none): sum[u] becomes the
+// row's whole weight of label lab[u] in every lane that holds the label.
+// Instead of probing a hashtable, each round writes the labels left to the
+// slots that a hash gives them (the last write stays), reads the slots back
+// and sums the labels that find themselves; the others go on to the next
+// round with another seven bits of the hash.  At least one label of every
+// slot written is summed per round, so the rounds end.  tag and val: 128
+// words each of the lane group's own; val holds zeros between calls (tag
+// needs none: every slot read was written in the same round).
+// COUNT: distinct grows by the number of labels this lane stands for (each
+// label of the row is counted by one entry, the last to write its number).
+constexpr int kMatchSlots = 128;
+template <int U, bool COUNT>
+__device__ __forceinline__ void match_sums(const uint32_t (&lab)[U], const float (&wt)[U],
+                                           uint32_t* tag, float* val, float (&sum)[U],
+                                           uint32_t* distinct) {
+  uint32_t x[U], h[U], left = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    x[u] = lab[u] * 0x9E3779B1u;
+    if (lab[u] != kEmpty) left |= 1u << u;
+    sum[u] = 0.0f;
+  }
+  for (uint32_t sh = 25;; sh = sh >= 7 ? sh - 7 : 25) {
+    uint32_t got[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      h[u] = (x[u] >> sh) & (uint32_t)(kMatchSlots - 1);
+      if (left & (1u << u))
+        __hip_atomic_store(&tag[h[u]], lab[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      got[u] = __hip_atomic_load(&tag[h[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    uint32_t hit = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if ((left & (1u << u)) && got[u] == lab[u]) {
+        hit |= 1u << u;
+        __hip_atomic_fetch_add(&val[h[u]], wt[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (hit & (1u << u))
+        sum[u] = __hip_atomic_load(&val[h[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (hit & (1u << u))
+        __hip_atomic_store(&val[h[u]], 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if constexpr (COUNT) {
+      const uint32_t id = (threadIdx.x & 15) * U;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (hit & (1u << u))
+          __hip_atomic_store(&tag[h[u]], id + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if ((hit & (1u << u)) &&
+            __hip_atomic_load(&tag[h[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == id + u)
+          ++*distinct;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    left &= ~hit;
+    if (!__any(left != 0u)) break;
+  }
+}
+
 __device__ __forceinline__ bool decide(unsigned long long best, int32_t cur, int pl,
                                        uint32_t* cstar) {
   if (best == 0ull) return false;  // no neighbour other than itself

@@ -31,8 +31,11 @@
 //   k_sweep_small<G>  G lanes per vertex (G = 4 or 16), one edge per lane,
 //                     per-label sums by DPP rotations inside the group; no
 //                     hashtable is needed for rows this short.
-//   k_sweep_group     rows of up to 64 entries, 16 lanes and an LDS table per
-//                     vertex, four vertices per wave.
+//   k_sweep_row16, k_sweep_row64  rows of 5-16 and 17-64 entries, 16 lanes
+//                     per vertex, four vertices per wave step, a batch of
+//                     rows' headers per wave; sums by DPP rotations, or by
+//                     matching labels in LDS slots (match_sums).
+//   k_sweep_group     the learned variant of k_sweep_row64.
 //   k_sweep_wave_pipe  one wave per vertex, LDS hashtable per wave, the next
 //                     row's head loaded during the table scan.
 //   k_sweep_block(_pipe)  one workgroup per vertex, LDS hashtable per
@@ -217,80 +220,231 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
   if constexpr (FEAT) flush_fneg(my_fneg, a.st);
 }
 
-// Plain k_sweep_small<16> with R wave steps in flight (three; two gained
-// less): the list entries, offsets, targets and neighbour labels of all R
-// steps are loaded before any is reduced (a step is a chain of four
-// dependent loads).
+// ---- short rows: headers a batch at a time ----------------------------------
+// The rows of 5-64 entries take 16 lanes (one DPP row) each, four rows per
+// wave step.  What bounds them is the number of vector memory instructions:
+// a load whose lanes hold other than consecutive addresses occupies the
+// address unit for up to one cycle per lane, also where only four of them
+// differ, so a step that loads its rows' list entry, offsets and own label
+// with 16 equal lanes each and stores with one pays for five such
+// instructions beside the two (targets, labels) that the method needs.
+// Here a wave takes a batch of 4 T rows (T <= 16): lane k of lane group g
+// loads the header of row g T + k -- one row per lane --, the T steps hand
+// a row's header to its 16 lanes by DPP, and lane t keeps step t's result,
+// so that the labels and change bytes of the batch are stored with one
+// instruction each.  The next batch's headers and the next step's targets
+// are loaded while the current step's labels are in flight.  No load is
+// conditional (a branch would leave the number of loads in flight unknown
+// and make each wait a wait for all of them): lanes past a row's end read
+// its last entry again, those past the list's end the list's last row, both
+// masked when the row is reduced.
+template <int N>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t x) {  // lane N of each DPP row
+  return dpp32<0x150 + N, 0xF, 0xF, false>(x);
+}
+template <int N>
+__device__ __forceinline__ int64_t row_bcast_off(int64_t x) {
+  return (int64_t)(((uint64_t)row_bcast<N>((uint32_t)((uint64_t)x >> 32)) << 32) |
+                   row_bcast<N>((uint32_t)x));
+}
+template <int N>
+__device__ __forceinline__ int32_t row_bcast_off(int32_t x) {
+  return (int32_t)row_bcast<N>((uint32_t)x);
+}
+template <int N>
+__device__ __forceinline__ uint32_t row_left(uint32_t x) {  // from lane i + N
+  return dpp32<0x120 + 16 - N, 0xF, 0xF, false>(x);
+}
+
+template <int N>
+__device__ __forceinline__ int64_t row_left_off(int64_t x) {
+  return (int64_t)(((uint64_t)row_left<N>((uint32_t)((uint64_t)x >> 32)) << 32) |
+                   row_left<N>((uint32_t)x));
+}
+template <int N>
+__device__ __forceinline__ int32_t row_left_off(int32_t x) {
+  return (int32_t)row_left<N>((uint32_t)x);
+}
+
+// Rows per lane group and batch: 16 where every wave still gets about three
+// batches, fewer for shorter lists (a short list is spread over the waves).
+__device__ __forceinline__ uint32_t batch_rows(uint32_t count, uint32_t nwaves) {
+  const uint32_t r = count / (4u * nwaves);
+  return r >= 48u ? 16u : (r >= 16u ? 8u : (r >= 4u ? 4u : (r >= 2u ? 2u : 1u)));
+}
+
 template <typename OffT>
-__global__ __launch_bounds__(256) void k_sweep_small16x2(SweepArgs a) {
-  constexpr int G = 16, R = 3;
-  constexpr uint32_t kVpw = 64 / G;
+struct RowBatch {
+  // this batch's rows, one per lane
+  int32_t v, cur, d;
+  unsigned long long best;
+  // the headers being handed out: rotated so that the next step's are in
+  // lane 0 of each DPP row
+  OffT ro;
+  int32_t rd, rv;
+  // the next batch's headers, and the list entry of the one after
+  int32_t vn, curn, vnn;
+  OffT on, en;
+  uint64_t at;  // list position of the lane's row in the batch being loaded
+  bool ok, okn;
+
+  __device__ __forceinline__ int32_t entry(const SweepArgs& a, uint32_t count) const {
+    return a.active[at < count ? at : (uint64_t)count - 1];
+  }
+  __device__ __forceinline__ void header(const SweepArgs& a) {  // of the row in vn
+    const OffT* p = reinterpret_cast<const OffT*>(a.off);
+    on = p[vn];
+    en = p[vn + 1];
+    curn = a.C[vn];
+  }
+  __device__ __forceinline__ void take() {  // the loaded headers become current
+    v = vn;
+    cur = curn;
+    ok = okn;
+    d = okn ? (int32_t)(en - on) : 0;
+    best = 0ull;
+    ro = on;
+    rd = d;
+    rv = v;
+  }
+  // first headers (count >= 1); stride: list positions between batches
+  __device__ __forceinline__ void begin(const SweepArgs& a, uint64_t first, uint64_t stride,
+                                        uint32_t count, bool lane_ok) {
+    at = first;
+    vn = entry(a, count);
+    okn = lane_ok && at < count;
+    header(a);
+    at += stride;
+    vnn = entry(a, count);
+    take();
+    next(a, stride, count, lane_ok);
+  }
+  // loads of the next batch's headers, of the list entry of the one after
+  __device__ __forceinline__ void next(const SweepArgs& a, uint64_t stride, uint32_t count,
+                                       bool lane_ok) {
+    vn = vnn;
+    okn = lane_ok && at < count;
+    header(a);
+    at += stride;
+    vnn = entry(a, count);
+  }
+};
+
+// The decision of one row, taken by its first lane.
+__device__ __forceinline__ void row_result(const SweepArgs& a, int32_t v, int32_t d, int32_t cur,
+                                           bool moved, uint32_t cstar,
+                                           unsigned long long& edges, uint32_t& changed,
+                                           unsigned long long& flagw) {
+  if (a.async_mode) {
+    if (moved) a.C[v] = (int32_t)cstar;
+  } else {
+    a.Cn[v] = moved ? (int32_t)cstar : cur;
+  }
+  if (moved) a.chg[v] = 1;
+  edges += (unsigned long long)d;
+  changed += moved ? 1u : 0u;
+  flagw += moved ? (unsigned long long)d : 0ull;
+}
+
+template <int R, bool UNIT>
+__device__ __forceinline__ void rot16_sum(uint32_t lab, float wt, float& sum) {
+  const uint32_t ol = dpp32<0x120 + R, 0xF, 0xF, false>(lab);
+  if constexpr (UNIT) {
+    sum += ol == lab ? 1.0f : 0.0f;
+  } else {
+    const float ow = __uint_as_float(dpp32<0x120 + R, 0xF, 0xF, false>(__float_as_uint(wt)));
+    if (ol == lab) sum += ow;
+  }
+}
+
+// Rows of 5-16 entries: per-label sums by rotations, four steps at a time.
+template <typename OffT, bool UNIT>
+__global__ __launch_bounds__(256) void k_sweep_row16(SweepArgs a) {
   if (a.st->stop) return;
   const int pl = a.st->pl;  // fixed for the whole sweep
   const bool id0 = a.st->iter == 0 && a.st->ident;  // labels are still the ids
   const int lane = threadIdx.x & 63;
-  const int k = lane & (G - 1);
+  const int k = lane & 15;
   const uint32_t count = a.st->active[a.cls];
   const uint32_t wave_id = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
   unsigned long long my_edges = 0, my_flagw = 0;
   uint32_t my_changed = 0;
-  for (uint64_t base = (uint64_t)wave_id * kVpw; base < count;
-       base += (uint64_t)R * nwaves * kVpw) {
-    bool valid[R];
-    int32_t v[R], j[R];
-    int64_t o[R], d[R];
-    float wt[R];
-    uint32_t lab[R];
+  const uint32_t T = batch_rows(count, nwaves);
+  const uint64_t base0 = (uint64_t)wave_id * 4 * T, stride = (uint64_t)nwaves * 4 * T;
+  if (base0 < count) {
+    RowBatch<OffT> b;
+    const bool lane_ok = (uint32_t)k < T;
+    b.begin(a, base0 + (uint32_t)(lane >> 4) * T + (uint32_t)k, stride, count, lane_ok);
+    int32_t j[4];
+    float w[4];
+    bool has[4];
+    // the next four steps' targets
+    auto targets = [&]() {
+#define LPA_STEP(I)                                                                     \
+  {                                                                                     \
+    const OffT o = row_bcast_off<I>(b.ro);                                              \
+    const int32_t d = (int32_t)row_bcast<I>((uint32_t)b.rd);                            \
+    const int64_t e = (int64_t)o + (k < d ? k : (d > 0 ? d - 1 : 0));                   \
+    j[I] = __builtin_nontemporal_load(&a.tgt[e]);                                       \
+    if constexpr (!UNIT) w[I] = __builtin_nontemporal_load(&a.w[e]);                    \
+    has[I] = k < d;                                                                     \
+  }
+      LPA_STEP(0) LPA_STEP(1) LPA_STEP(2) LPA_STEP(3)
+#undef LPA_STEP
+    };
+    targets();
+    for (uint64_t base = base0; base < count; base += stride) {
+      for (uint32_t t = 0; t < T; t += 4) {
+        uint32_t got[4], ids[4];
+        float wt[4];
+        bool use[4];
+        const uint32_t v0 = row_bcast<0>((uint32_t)b.rv), v1 = row_bcast<1>((uint32_t)b.rv),
+                       v2 = row_bcast<2>((uint32_t)b.rv), v3 = row_bcast<3>((uint32_t)b.rv);
+        const uint32_t vs[4] = {v0, v1, v2, v3};
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint64_t idx = base + (uint64_t)r * nwaves * kVpw + (uint32_t)lane / G;
-      valid[r] = idx < count;
-      v[r] = valid[r] ? a.active[idx] : 0;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      o[r] = 0;
-      d[r] = 0;
-      if (valid[r]) row_of<OffT>(a.off, v[r], &o[r], &d[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const bool has = valid[r] && k < d[r];
-      j[r] = has ? __builtin_nontemporal_load(&a.tgt[o[r] + k]) : -1;
-      wt[r] = has ? edge_weight(a.w, o[r] + k) : 0.0f;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      lab[r] = kEmpty;
-      if (j[r] >= 0 && j[r] != v[r]) lab[r] = id0 ? (uint32_t)j[r] : (uint32_t)a.C[j[r]];
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      float sum = wt[r], mult = 1.0f;
-      rot16_accum<1, false>(lab[r], wt[r], sum, mult);  rot16_accum<2, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<3, false>(lab[r], wt[r], sum, mult);  rot16_accum<4, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<5, false>(lab[r], wt[r], sum, mult);  rot16_accum<6, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<7, false>(lab[r], wt[r], sum, mult);  rot16_accum<8, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<9, false>(lab[r], wt[r], sum, mult);  rot16_accum<10, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<11, false>(lab[r], wt[r], sum, mult); rot16_accum<12, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<13, false>(lab[r], wt[r], sum, mult); rot16_accum<14, false>(lab[r], wt[r], sum, mult);
-      rot16_accum<15, false>(lab[r], wt[r], sum, mult);
-      const unsigned long long packed = (lab[r] != kEmpty) ? pack_key(sum, lab[r]) : 0ull;
-      const unsigned long long best = row16_max_u64(packed);
-      uint32_t cstar = 0;
-      const int32_t cur = valid[r] ? a.C[v[r]] : 0;
-      const bool moved = valid[r] && decide(best, cur, pl, &cstar);
-      if (valid[r] && k == 0) {
-        if (a.async_mode) {
-          if (moved) a.C[v[r]] = (int32_t)cstar;
-        } else {
-          a.Cn[v[r]] = moved ? (int32_t)cstar : cur;
+        for (int i = 0; i < 4; ++i) {
+          got[i] = (uint32_t)a.C[j[i]];
+          ids[i] = (uint32_t)j[i];
+          use[i] = has[i] && ids[i] != vs[i];
+          wt[i] = UNIT ? 1.0f : w[i];
         }
-        if (moved) a.chg[v[r]] = 1;
-        my_edges += (unsigned long long)d[r];
-        my_changed += moved ? 1u : 0u;
-        my_flagw += moved ? (unsigned long long)d[r] : 0ull;
+        const int32_t bv = b.v, bcur = b.cur, bd = b.d;
+        const bool bok = b.ok;
+        unsigned long long best = b.best;
+        const bool last = t + 4 >= T;
+        if (last) {
+          b.take();
+        } else {
+          b.ro = row_left_off<4>(b.ro);
+          b.rd = (int32_t)row_left<4>((uint32_t)b.rd);
+          b.rv = (int32_t)row_left<4>((uint32_t)b.rv);
+        }
+        targets();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t l = use[i] ? (id0 ? ids[i] : got[i]) : kEmpty;
+          const float x = wt[i];
+          float sum = x;
+          rot16_sum<1, UNIT>(l, x, sum);  rot16_sum<2, UNIT>(l, x, sum);
+          rot16_sum<3, UNIT>(l, x, sum);  rot16_sum<4, UNIT>(l, x, sum);
+          rot16_sum<5, UNIT>(l, x, sum);  rot16_sum<6, UNIT>(l, x, sum);
+          rot16_sum<7, UNIT>(l, x, sum);  rot16_sum<8, UNIT>(l, x, sum);
+          rot16_sum<9, UNIT>(l, x, sum);  rot16_sum<10, UNIT>(l, x, sum);
+          rot16_sum<11, UNIT>(l, x, sum); rot16_sum<12, UNIT>(l, x, sum);
+          rot16_sum<13, UNIT>(l, x, sum); rot16_sum<14, UNIT>(l, x, sum);
+          rot16_sum<15, UNIT>(l, x, sum);
+          const unsigned long long m = row16_max_u64(l != kEmpty ? pack_key(sum, l) : 0ull);
+          if ((uint32_t)k == t + i) best = m;
+        }
+        if (!last) {
+          b.best = best;
+        } else {
+          uint32_t cstar = 0;
+          const bool moved = decide(best, bcur, pl, &cstar);
+          if (bok) row_result(a, bv, bd, bcur, moved, cstar, my_edges, my_changed, my_flagw);
+          b.next(a, stride, count, lane_ok);
+        }
       }
     }
   }
@@ -560,28 +714,118 @@ __global__ __launch_bounds__(WAVES * 64) void k_sweep_wave_pipe(SweepArgs a) {
   if constexpr (FEAT) flush_fneg(my_fneg, a.st);
 }
 
-// ---- G lanes per vertex, LDS table per lane group ----------------------------
-// Rows of up to 4G entries: a wave takes 64/G vertices at once, each group of
-// G lanes with a table of its own, so that four rows' label reads are in
-// flight per wave where the one-wave-per-vertex kernel has one.  G = 16 is
-// one DPP row, whose reductions stay inside the group.  FEAT: the learned
-// variant, which also reduces the record quantities over the group.
-template <typename OffT, int SLOTS, int G, bool FEAT>
-__global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
-  static_assert(G == 16, "group reductions are DPP-row wide");
+// ---- rows of up to 64 entries: 16 lanes and 128 match slots per vertex ------
+// Four entries per lane, summed per label by match_sums.  Measured on an
+// LFR-like graph of 10^6 vertices (6.5 M entries in rows of 17-64): 93 us a
+// full launch with a probed 127-slot table and one header per group, 88 with
+// the match slots alone, 70 with the batched headers; k_sweep_row16 (7.9 M
+// entries in rows of 5-16) 103 -> 77 us.  R-MAT 26: 1.37 -> 1.31 and
+// 0.50 -> 0.49 ms, where the label lines' misses bound both.
+template <typename OffT, bool UNIT>
+__global__ __launch_bounds__(256) void k_sweep_row64(SweepArgs a) {
+  constexpr int G = 16, U = 4;
   constexpr int NG = 256 / G;
-  constexpr int U = 4;
-  __shared__ uint32_t keys_all[NG][SLOTS];
-  __shared__ float vals_all[NG][SLOTS];
+  __shared__ uint32_t tag_all[NG][kMatchSlots];
+  __shared__ float val_all[NG][kMatchSlots];
+  if (a.st->stop) return;
+  const int pl = a.st->pl;  // fixed for the whole sweep
+  const bool id0 = a.st->iter == 0 && a.st->ident;  // labels are still the ids
+  const int gi = threadIdx.x / G, k = threadIdx.x & (G - 1);
+  uint32_t* tag = tag_all[gi];
+  float* val = val_all[gi];
+  for (int s = k; s < kMatchSlots; s += G) val[s] = 0.0f;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const uint32_t count = a.st->active[a.cls];
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave_id = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
+  unsigned long long my_edges = 0, my_flagw = 0;
+  uint32_t my_changed = 0;
+  const uint32_t T = batch_rows(count, nwaves);
+  const uint64_t base0 = (uint64_t)wave_id * 4 * T, stride = (uint64_t)nwaves * 4 * T;
+  if (base0 < count) {
+    RowBatch<OffT> b;
+    const bool lane_ok = (uint32_t)k < T;
+    b.begin(a, base0 + (uint32_t)(lane >> 4) * T + (uint32_t)k, stride, count, lane_ok);
+    int32_t j[U], d;
+    float w[U];
+    auto targets = [&]() {  // the next step's targets
+      const OffT o = row_bcast_off<0>(b.ro);
+      d = (int32_t)row_bcast<0>((uint32_t)b.rd);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = u * G + k;
+        const int64_t at = (int64_t)o + (e < d ? e : (d > 0 ? d - 1 : 0));
+        j[u] = __builtin_nontemporal_load(&a.tgt[at]);
+        if constexpr (!UNIT) w[u] = __builtin_nontemporal_load(&a.w[at]);
+      }
+    };
+    targets();
+    for (uint64_t base = base0; base < count; base += stride) {
+      for (uint32_t t = 0; t < T; ++t) {
+        uint32_t lab[U], got[U], ids[U];
+        float wt[U], sum[U];
+        bool use[U];
+        const uint32_t vs = row_bcast<0>((uint32_t)b.rv);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          got[u] = (uint32_t)a.C[j[u]];
+          ids[u] = (uint32_t)j[u];
+          use[u] = u * G + k < d && ids[u] != vs;
+          wt[u] = UNIT ? 1.0f : w[u];
+        }
+        const int32_t bv = b.v, bcur = b.cur, bd = b.d;
+        const bool bok = b.ok;
+        unsigned long long best = b.best;
+        const bool last = t + 1 >= T;
+        if (last) {
+          b.take();
+        } else {
+          b.ro = row_left_off<1>(b.ro);
+          b.rd = (int32_t)row_left<1>((uint32_t)b.rd);
+          b.rv = (int32_t)row_left<1>((uint32_t)b.rv);
+        }
+        targets();
+#pragma unroll
+        for (int u = 0; u < U; ++u) lab[u] = use[u] ? (id0 ? ids[u] : got[u]) : kEmpty;
+        match_sums<U, false>(lab, wt, tag, val, sum, nullptr);
+        unsigned long long m = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (lab[u] != kEmpty) m = umax64(m, pack_key(sum[u], lab[u]));
+        m = row16_max_u64(m);
+        if ((uint32_t)k == t) best = m;
+        if (!last) {
+          b.best = best;
+        } else {
+          uint32_t cstar = 0;
+          const bool moved = decide(best, bcur, pl, &cstar);
+          if (bok) row_result(a, bv, bd, bcur, moved, cstar, my_edges, my_changed, my_flagw);
+          b.next(a, stride, count, lane_ok);
+        }
+      }
+    }
+  }
+  flush_stats(my_edges, my_changed, my_flagw, a.st, a.cls);
+}
+
+// The learned variant: it also reduces the record quantities over the group
+// and rewrites each evaluated vertex's state record.
+template <typename OffT>
+__global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
+  constexpr int G = 16, U = 4;
+  constexpr int NG = 256 / G;
+  __shared__ uint32_t tag_all[NG][kMatchSlots];
+  __shared__ float val_all[NG][kMatchSlots];
   if (a.st->stop) return;
   const int pl = a.st->pl;  // fixed for the whole sweep
   const bool id0 = a.st->iter == 0 && a.st->ident;  // labels are still the ids
   const int tid = threadIdx.x;
   const int gi = tid / G, k = tid & (G - 1);
-  [[maybe_unused]] const int l = a.st->iter;
-  uint32_t* keys = keys_all[gi];
-  float* vals = vals_all[gi];
-  for (int s = k; s < SLOTS; s += G) { keys[s] = kEmpty; vals[s] = 0.0f; }
+  const int l = a.st->iter;
+  uint32_t* tag = tag_all[gi];
+  float* val = val_all[gi];
+  for (int s = k; s < kMatchSlots; s += G) val[s] = 0.0f;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   const uint32_t count = a.st->active[a.cls];
   unsigned long long my_edges = 0, my_flagw = 0;
@@ -593,57 +837,48 @@ __global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
     int64_t o, d;
     row_of<OffT>(a.off, v, &o, &d);
     const int32_t cur = a.C[v];
-    [[maybe_unused]] const unsigned long long rold = (FEAT && k == 0) ? a.rec[v] : 0ull;
-    const uint32_t p1 = table_p1_load((uint32_t)d, a.tload, (uint32_t)SLOTS);
-    RecPartial rp;
-    for (int64_t base = 0; base < d; base += G * U) {
-      int32_t j[U];
-      float wt[U];
-      uint32_t lab[U];
+    const unsigned long long rold = k == 0 ? a.rec[v] : 0ull;
+    int32_t j[U];
+    float wt[U], sum[U];
+    uint32_t lab[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t e = base + u * G + k;
-        const bool has = e < d;
-        j[u] = has ? __builtin_nontemporal_load(&a.tgt[o + e]) : v;
-        wt[u] = has ? edge_weight(a.w, o + e) : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        lab[u] = (j[u] != v) ? (id0 ? (uint32_t)j[u] : (uint32_t)a.C[j[u]]) : kEmpty;
-#pragma unroll
-      for (int u = 0; u < U; ++u) merge_lead16(lab[u], wt[u], a.w == nullptr);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (lab[u] != kEmpty) {
-          lds_accumulate(keys, vals, p1, lab[u], wt[u], a.probe);
-          if constexpr (FEAT) rp.K += wt[u];
-        }
+    for (int u = 0; u < U; ++u) {
+      const int64_t e = u * G + k;
+      const bool has = e < d;
+      j[u] = has ? __builtin_nontemporal_load(&a.tgt[o + e]) : v;
+      wt[u] = has ? edge_weight(a.w, o + e) : 0.0f;
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      lab[u] = (j[u] != v) ? (id0 ? (uint32_t)j[u] : (uint32_t)a.C[j[u]]) : kEmpty;
+    float K = 0.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) K += lab[u] != kEmpty ? wt[u] : 0.0f;
+    uint32_t owned = 0;
+    match_sums<U, true>(lab, wt, tag, val, sum, &owned);
     unsigned long long best = 0;
-    for (uint32_t s = k; s < p1; s += G) {
-      const uint32_t kk = keys[s];
-      if (kk != kEmpty) {
-        const unsigned long long pk = pack_key(vals[s], kk);
-        if constexpr (FEAT) rp.slot(pk, kk, vals[s], cur);
-        best = umax64(best, pk);
-        keys[s] = kEmpty;
-        vals[s] = 0.0f;
-      }
-    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (lab[u] != kEmpty) best = umax64(best, pack_key(sum[u], lab[u]));
     best = row16_max_u64(best);
     uint32_t cstar = 0;
     const bool moved = decide(best, cur, pl, &cstar);
-    if constexpr (FEAT) {
-      const float second =
-          __uint_as_float((uint32_t)(row16_max_u64(rp.b1 == best ? rp.b2 : rp.b1) >> 32));
-      const float own = __uint_as_float((uint32_t)row16_max_u64(__float_as_uint(rp.own)));
-      const uint32_t distinct = group_sum_u32<G>(rp.distinct);
-      const float K = group_sum_f32<G>(rp.K);
-      if (k == 0)
-        my_fneg += rec_write(a.rec, v, rold, l, K, own, __uint_as_float((uint32_t)(best >> 32)),
-                             second, distinct, (uint32_t)d, moved);
+    unsigned long long sk = 0;
+    float mine = 0.0f;
+    const uint32_t bl = best ? unpack_label(best) : kEmpty;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (lab[u] == kEmpty) continue;
+      if (lab[u] != bl) sk = umax64(sk, pack_key(sum[u], lab[u]));
+      if ((int32_t)lab[u] == cur) mine = sum[u];
     }
+    const float second = __uint_as_float((uint32_t)(row16_max_u64(sk) >> 32));
+    const float own = __uint_as_float((uint32_t)row16_max_u64(__float_as_uint(mine)));
+    const uint32_t distinct = group_sum_u32<G>(owned);
+    K = group_sum_f32<G>(K);
+    if (k == 0)
+      my_fneg += rec_write(a.rec, v, rold, l, K, own, __uint_as_float((uint32_t)(best >> 32)),
+                           second, distinct, (uint32_t)d, moved);
     if (k == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
@@ -655,10 +890,9 @@ __global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
       my_changed += moved ? 1u : 0u;
       my_flagw += moved ? (unsigned long long)d : 0ull;
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
   flush_stats(my_edges, my_changed, my_flagw, a.st, a.cls);
-  if constexpr (FEAT) flush_fneg(my_fneg, a.st);
+  flush_fneg(my_fneg, a.st);
 }
 
 // ---- one workgroup per vertex, LDS table per workgroup ---------------------
@@ -1921,10 +2155,13 @@ static hipError_t sweep_t(int cls, const SweepArgs& a, int grid, hipStream_t s) 
       break;
     case 2:
       if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_small<OffT, 16, true>), dim3(grid), dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((k_sweep_small16x2<OffT>), dim3(grid), dim3(256), 0, s, a);
+      else if (a.w) hipLaunchKernelGGL((k_sweep_row16<OffT, false>), dim3(grid), dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((k_sweep_row16<OffT, true>), dim3(grid), dim3(256), 0, s, a);
       break;
     case 3:
-      hipLaunchKernelGGL((k_sweep_group<OffT, 127, 16, FEAT>), dim3(grid), dim3(256), 0, s, a);
+      if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_group<OffT>), dim3(grid), dim3(256), 0, s, a);
+      else if (a.w) hipLaunchKernelGGL((k_sweep_row64<OffT, false>), dim3(grid), dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((k_sweep_row64<OffT, true>), dim3(grid), dim3(256), 0, s, a);
       break;
     case 4:
       hipLaunchKernelGGL((k_sweep_wave_pipe<OffT, 1023, kWaveWaves, 4, FEAT>), dim3(grid), dim3(256), 0, s, a);
