@@ -292,12 +292,16 @@ struct lpa_graph_s {
   unsigned int* wq_qctr = nullptr;
   unsigned int* wq_qctr0 = nullptr;  // the initial queue's counters
   uint8_t* wq_cmark = nullptr;
+  uint32_t* wq_B0 = nullptr;
+  uint32_t* wq_B1 = nullptr;
   uint8_t* wq_F1 = nullptr;
+  int32_t wq_fb_words = 0;
   unsigned int* wq_gchanged = nullptr;
   QueueArgs queue_args(int async_mode) const {
     QueueArgs q;
     q.off = off; q.tgt = tgt; q.w = w;
     q.C0 = C; q.C1 = async_mode ? C : Cn;
+    q.B0 = wq_B0; q.B1 = wq_B1; q.fb_words = wq_fb_words;
     q.F0 = F; q.F1 = wq_F1;
     q.cmark = wq_cmark; q.cbase = wq_cbase; q.cgraph = wq_cgraph;
     q.items = wq_items; q.qbase = wq_qbase; q.qctr = wq_qctr; q.gchanged = wq_gchanged;
@@ -973,6 +977,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   a.rec = g->lrec;
   a.tload = g->tun.table_load;
   a.block_threads = g->tun.block_threads;
+  a.small_labels = g->n <= ((int64_t)1 << 25);
   for (int c = kClassHub - 1; c >= 1; --c) {
     if (g->cls_count[c] == 0) continue;
     a.cls = c;
@@ -1379,6 +1384,12 @@ static lpa_status build_queue(lpa_graph g, const int64_t* v_off, const lpa_tunin
   std::vector<int64_t> cbase(G + 1, 0);
   for (int32_t q = 0; q < G; ++q)
     cbase[q + 1] = cbase[q] + (((v_off[q + 1] - v_off[q]) + (1 << lg) - 1) >> lg);
+  // flag words of the largest graph, as many as LDS holds
+  int64_t most = 0;
+  for (int32_t q = 0; q < G; ++q)
+    if (v_off[q] < v_off[q + 1])
+      most = std::max(most, ((v_off[q + 1] - 1) >> 5) - (v_off[q] >> 5) + 1);
+  g->wq_fb_words = (int32_t)std::min<int64_t>(most, kQueueFlagWords);
   const int64_t nch = cbase[G];
   if (nch >= (int64_t)UINT32_MAX) return fail(LPA_ERR_INVALID, "too many queue items");
   std::vector<int32_t> cgraph((size_t)std::max<int64_t>(nch, 1));
@@ -1406,7 +1417,11 @@ static lpa_status build_queue(lpa_graph g, const int64_t* v_off, const lpa_tunin
   if (lpa_status e = g->dalloc(&g->wq_qctr, nctr)) return e;
   if (lpa_status e = g->dalloc(&g->wq_qctr0, nctr)) return e;
   if (lpa_status e = g->dalloc(&g->wq_cmark, nch)) return e;
-  if (lpa_status e = g->dalloc(&g->wq_F1, g->n)) return e;
+  if (lpa_status e = g->dalloc(&g->wq_B0, (g->n + 31) / 32)) return e;
+  if (lpa_status e = g->dalloc(&g->wq_B1, (g->n + 31) / 32)) return e;
+  if (most > kQueueFlagWords) {
+    if (lpa_status e = g->dalloc(&g->wq_F1, g->n)) return e;
+  }
   if (lpa_status e = g->dalloc(&g->wq_gchanged, G)) return e;
   LPA_HIP(hipMemcpyAsync(g->wq_cbase, cbase.data(), sizeof(int64_t) * (G + 1),
                          hipMemcpyHostToDevice, s));

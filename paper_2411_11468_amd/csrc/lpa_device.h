@@ -356,6 +356,69 @@ __device__ __forceinline__ void merge_lead16(uint32_t& lab, float& wt, bool unit
   }
 }
 
+// Lane N of each DPP row in all its 16 lanes; each lane's value taken from the
+// lane N to its right (cyclic in the row).
+template <int N>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t x) {  // lane N of each DPP row
+  return dpp32<0x150 + N, 0xF, 0xF, false>(x);
+}
+template <int N>
+__device__ __forceinline__ int64_t row_bcast_off(int64_t x) {
+  return (int64_t)(((uint64_t)row_bcast<N>((uint32_t)((uint64_t)x >> 32)) << 32) |
+                   row_bcast<N>((uint32_t)x));
+}
+template <int N>
+__device__ __forceinline__ int32_t row_bcast_off(int32_t x) {
+  return (int32_t)row_bcast<N>((uint32_t)x);
+}
+template <int N>
+__device__ __forceinline__ uint32_t row_left(uint32_t x) {  // from lane i + N
+  return dpp32<0x120 + 16 - N, 0xF, 0xF, false>(x);
+}
+
+template <int N>
+__device__ __forceinline__ int64_t row_left_off(int64_t x) {
+  return (int64_t)(((uint64_t)row_left<N>((uint32_t)((uint64_t)x >> 32)) << 32) |
+                   row_left<N>((uint32_t)x));
+}
+template <int N>
+__device__ __forceinline__ int32_t row_left_off(int32_t x) {
+  return (int32_t)row_left<N>((uint32_t)x);
+}
+
+// Weight sums of short rows: with unit weights they are counts.
+template <bool UNIT> struct RowSum { typedef float type; };
+template <> struct RowSum<true> { typedef uint32_t type; };
+
+// Sum of the weights that the 16 lanes of a DPP row hold for this lane's
+// label, by rotations (UNIT: every weight is 1).
+template <int R, bool UNIT>
+__device__ __forceinline__ void rot16_sum(uint32_t lab, float wt,
+                                          typename RowSum<UNIT>::type& sum) {
+  const uint32_t ol = dpp32<0x120 + R, 0xF, 0xF, false>(lab);
+  if constexpr (UNIT) {
+    sum += ol == lab ? 1u : 0u;
+  } else {
+    const float ow = __uint_as_float(dpp32<0x120 + R, 0xF, 0xF, false>(__float_as_uint(wt)));
+    if (ol == lab) sum += ow;
+  }
+}
+template <bool UNIT>
+__device__ __forceinline__ typename RowSum<UNIT>::type rotate_sum(uint32_t lab, float wt) {
+  typename RowSum<UNIT>::type sum;
+  if constexpr (UNIT) sum = 1u;
+  else sum = wt;
+  rot16_sum<1, UNIT>(lab, wt, sum);  rot16_sum<2, UNIT>(lab, wt, sum);
+  rot16_sum<3, UNIT>(lab, wt, sum);  rot16_sum<4, UNIT>(lab, wt, sum);
+  rot16_sum<5, UNIT>(lab, wt, sum);  rot16_sum<6, UNIT>(lab, wt, sum);
+  rot16_sum<7, UNIT>(lab, wt, sum);  rot16_sum<8, UNIT>(lab, wt, sum);
+  rot16_sum<9, UNIT>(lab, wt, sum);  rot16_sum<10, UNIT>(lab, wt, sum);
+  rot16_sum<11, UNIT>(lab, wt, sum); rot16_sum<12, UNIT>(lab, wt, sum);
+  rot16_sum<13, UNIT>(lab, wt, sum); rot16_sum<14, UNIT>(lab, wt, sum);
+  rot16_sum<15, UNIT>(lab, wt, sum);
+  return sum;
+}
+
 // Per-label sums of a row of up to 16 U entries held in registers by the 16
 // lanes of one DPP row, U entries per lane (kEmpty: none): sum[u] becomes the
 // row's whole weight of label lab[u] in every lane that holds the label.
@@ -369,16 +432,19 @@ __device__ __forceinline__ void merge_lead16(uint32_t& lab, float& wt, bool unit
 // COUNT: distinct grows by the number of labels this lane stands for (each
 // label of the row is counted by one entry, the last to write its number).
 constexpr int kMatchSlots = 128;
-template <int U, bool COUNT>
+template <int U, bool UNIT, bool COUNT>
 __device__ __forceinline__ void match_sums(const uint32_t (&lab)[U], const float (&wt)[U],
-                                           uint32_t* tag, float* val, float (&sum)[U],
+                                           uint32_t* tag, void* vals,
+                                           typename RowSum<UNIT>::type (&sum)[U],
                                            uint32_t* distinct) {
+  typedef typename RowSum<UNIT>::type Sum;
+  Sum* val = static_cast<Sum*>(vals);
   uint32_t x[U], h[U], left = 0;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     x[u] = lab[u] * 0x9E3779B1u;
     if (lab[u] != kEmpty) left |= 1u << u;
-    sum[u] = 0.0f;
+    sum[u] = 0;
   }
   for (uint32_t sh = 25;; sh = sh >= 7 ? sh - 7 : 25) {
     uint32_t got[U];
@@ -397,7 +463,10 @@ __device__ __forceinline__ void match_sums(const uint32_t (&lab)[U], const float
     for (int u = 0; u < U; ++u)
       if ((left & (1u << u)) && got[u] == lab[u]) {
         hit |= 1u << u;
-        __hip_atomic_fetch_add(&val[h[u]], wt[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        Sum add;
+        if constexpr (UNIT) add = 1u;
+        else add = wt[u];
+        __hip_atomic_fetch_add(&val[h[u]], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 #pragma unroll
@@ -408,7 +477,7 @@ __device__ __forceinline__ void match_sums(const uint32_t (&lab)[U], const float
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (hit & (1u << u))
-        __hip_atomic_store(&val[h[u]], 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&val[h[u]], (Sum)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if constexpr (COUNT) {
       const uint32_t id = (threadIdx.x & 15) * U;
 #pragma unroll
@@ -426,6 +495,50 @@ __device__ __forceinline__ void match_sums(const uint32_t (&lab)[U], const float
     left &= ~hit;
     if (!__any(left != 0u)) break;
   }
+}
+
+// Max within each 16-lane row of 32-bit keys, result in every lane of the row.
+__device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint32_t row16_max_u32(uint32_t x) {
+  x = umax32(x, dpp32<0x128>(x));  // row_ror:8
+  x = umax32(x, dpp32<0x124>(x));
+  x = umax32(x, dpp32<0x122>(x));
+  x = umax32(x, dpp32<0x121>(x));
+  return x;
+}
+
+// Eq. 3's label of a row of up to 16 U entries from its sums, in all 16 lanes
+// of the row's group: the largest sum, the smallest label among equal ones;
+// own where the row has no entry.  With unit weights (a row then sums to at
+// most 64) and labels below base + 2^25 the key of an entry fits 32 bits
+// (small), whose maximum takes one instruction a step instead of five.
+constexpr int64_t kSmallLabels = (int64_t)1 << 25;
+template <int U, bool UNIT>
+__device__ __forceinline__ uint32_t row16_label(const uint32_t (&lab)[U],
+                                                const typename RowSum<UNIT>::type (&sum)[U],
+                                                bool small, uint32_t base, uint32_t own) {
+  if constexpr (UNIT) {
+    if (small) {
+      const uint32_t top = base + (uint32_t)kSmallLabels - 1u;
+      uint32_t key = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        key = umax32(key, lab[u] != kEmpty ? (sum[u] << 25) | (top - lab[u]) : 0u);
+      key = row16_max_u32(key);
+      return key ? top - (key & (uint32_t)(kSmallLabels - 1)) : own;
+    }
+  }
+  unsigned long long best = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (lab[u] != kEmpty) best = umax64(best, pack_key((float)sum[u], lab[u]));
+  best = row16_max_u64(best);
+  return best ? unpack_label(best) : own;
+}
+
+// Whether a vertex with label cur moves to label c (its own: none found).
+__device__ __forceinline__ bool moves(uint32_t c, int32_t cur, int pl) {
+  return (int32_t)c != cur && (!pl || (int32_t)c < cur);
 }
 
 __device__ __forceinline__ bool decide(unsigned long long best, int32_t cur, int pl,

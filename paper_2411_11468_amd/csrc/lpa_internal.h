@@ -148,6 +148,7 @@ struct SweepArgs {
   const int32_t* ctgt = nullptr;
   const float* uw;
   const int32_t* inv;
+  int small_labels = 0;   // every label is below 2^25 (row16_label)
 };
 
 // Hubs (rows longer than the largest LDS table).  Each slice of chunk CSR
@@ -239,6 +240,7 @@ struct BatchArgs {
 // the chunks marked for the next iteration.
 constexpr int kQueueMaxChunkLog2 = 10;   // chunks of at most 1024 vertices
 constexpr int kQueueMaxDegree = 512;     // longest row the queue kernel takes
+constexpr int kQueueFlagWords = 2048;    // LDS flag words: graphs of about 65,536 vertices
 constexpr int kQueueCtrStride = 16;      // words between two queue counters
 struct QueueArgs {
   const void* off;
@@ -247,9 +249,13 @@ struct QueueArgs {
   int32_t* C0;                     // labels read in even iterations ...
   int32_t* C1;                     // ... and odd ones (the same array in
                                    // asynchronous mode)
-  uint8_t* F0;                     // flags of even / odd iterations
-  uint8_t* F1;
-  uint8_t* cmark;                  // per chunk: visit in the next iteration
+  uint32_t* B0;                    // flags of even / odd iterations, one bit
+  uint32_t* B1;                    // per vertex, of the graphs whose flags
+  int32_t fb_words;                // span at most fb_words words;
+  uint8_t* F0;                     // one byte per vertex of the larger graphs
+  uint8_t* F1;                     // (F1 NULL: there are none)
+  uint8_t* cmark;                  // per chunk: visit in the next iteration (of
+                                   // the graphs with bits: besides its flags)
   const int64_t* cbase;            // G + 1: each graph's first chunk
   const int32_t* cgraph;           // per chunk: its graph
   uint32_t* items;                 // two queues of nchunks items each
@@ -388,8 +394,8 @@ hipError_t launch_modularity(bool off64, const void* off, const int32_t* tgt,
 // non-empty graph for iteration 0 (counters, marks and the odd flags
 // cleared, the odd labels copied in deterministic mode); per iteration the
 // counters reset, the sweep, the per-graph stop test and next queue; at the
-// end the flags (and deterministic labels) of graphs that stopped after an
-// odd number of iterations moved to F0 (C0).
+// end the flags as bytes in F0, and the deterministic labels of graphs that
+// stopped after an odd number of iterations in C0.
 hipError_t launch_queue_begin(const QueueArgs& q, int64_t n, hipStream_t s);
 hipError_t launch_queue_iter_begin(const QueueArgs& q, hipStream_t s);
 hipError_t launch_queue_sweep(bool off64, const QueueArgs& q, int grid, hipStream_t s);

@@ -8,21 +8,22 @@
 //                       once) pops items from the queue until it is drained.
 //                       For each item the workgroup reads and clears the
 //                       chunk's flags, sorts the flagged vertices by row
-//                       length into two LDS lists and processes them: rows of
-//                       up to group_max entries with 16 lanes and a 127-slot
-//                       LDS table each (16 rows at a time), longer ones (up
-//                       to 512 entries) with the whole workgroup and a
-//                       1023-slot table in the same LDS.  The first sweep
+//                       length into LDS lists and processes them: rows of
+//                       up to group_max entries with 16 lanes each (16 rows
+//                       at a time), longer ones (up to 512 entries) with the
+//                       whole workgroup and a 1023-slot table in LDS.  The
+//                       first sweep
 //                       from the ids over strictly increasing rows needs no
 //                       table (each label occurs once per row).
 //                       Each vertex takes the label of maximum summed weight
 //                       (Eq. 3; smallest label on ties), moves under the
 //                       Pick-Less rule (Sec. 4.1) and, when it moves, flags
 //                       every neighbour for the next iteration (Sec. 4 item
-//                       4) and marks their chunks to be queued;
+//                       4);
 //   k_queue_step        one workgroup per graph applies Algorithm 1's stop
 //                       test with the graph's own vertex count and queues
-//                       the graph's marked chunks for the next iteration;
+//                       the graph's chunks that hold flags or changes for the
+//                       next iteration;
 //   k_iter_end          (graph.hip) records the iteration and ends the run
 //                       when every graph has stopped.
 // The iteration boundary is the only barrier: a graph's next iteration reads
@@ -42,6 +43,8 @@
 // labels in both arrays.  A graph's final labels (and its flags for a next
 // iteration) are in the arrays of its iteration-count parity;
 // k_queue_finish moves the odd ones.
+#include <type_traits>
+
 #include "lpa_device.h"
 
 namespace lpa {
@@ -50,9 +53,8 @@ namespace {
 
 constexpr int kQBT = 256;                 // threads per sweep workgroup
 constexpr int kQGroups = kQBT / 16;       // 16-lane groups per workgroup
-constexpr int kQGroupSlots = 127;         // group tables: rows of up to 64 entries
 constexpr int kQWaves = kQBT / 64;
-constexpr int kQPool = kQGroups * kQGroupSlots;  // LDS table slots per workgroup
+constexpr int kQPool = kQGroups * kMatchSlots;  // LDS table slots per workgroup
 constexpr uint32_t kNoItem = 0xFFFFFFFFu;
 static_assert(2 * kQueueMaxDegree - 1 <= kQPool, "the pool holds a 512-entry row's table");
 
@@ -82,49 +84,92 @@ __device__ uint32_t queue_pop(const QueueArgs& q, int par, uint32_t& from) {
   return kNoItem;
 }
 
+// Words of the bit flags that hold the vertices gv0 .. gv1 - 1.
+__device__ __forceinline__ int64_t graph_bits(int64_t gv0, int64_t gv1) {
+  return ((gv1 - 1) >> 5) - (gv0 >> 5) + 1;
+}
+
+// Bits of flag word x that stand for the vertices v0 .. v1 - 1.
+__device__ __forceinline__ uint32_t word_mask(int64_t x, int64_t v0, int64_t v1) {
+  const int64_t b0 = x << 5;
+  const uint32_t lo = v0 > b0 ? ~0u << (v0 - b0) : ~0u;
+  const uint32_t hi = v1 < b0 + 32 ? ~(~0u << (v1 - b0)) : ~0u;
+  return lo & hi;
+}
+
 }  // namespace
 
-template <typename OffT>
-__global__ __launch_bounds__(kQBT) void k_queue_sweep(QueueArgs q) {
-  // one LDS pool: 16 group tables of 127 slots, or one 1023-slot table for
-  // the workgroup path
-  __shared__ uint32_t keys[kQPool];
+// Dynamic LDS of k_queue_sweep, per vertex of a chunk: its row's header
+// (offset from the chunk's first entry << 10 | length), its label, two list
+// words.
+constexpr size_t kQChunkBytes = 4 + 4 + 2 + 2;
+constexpr uint32_t kQMaxRel = 1u << 22;   // header offsets are below this
+static_assert((int64_t)kQueueMaxDegree << kQueueMaxChunkLog2 <= (int64_t)kQMaxRel, "header");
+static_assert(kQueueMaxDegree < 1024, "header");
+
+// What bounds it: the labels of a graph lie in its XCD's L2, so the sweep is
+// bound by instruction issue and by the address unit, which spends up to a
+// cycle per lane on a load or store of scattered addresses.  The rows'
+// offsets and own labels are therefore read once per chunk, coalesced, into
+// LDS, with the flags; a wave takes the headers of up to 64 listed rows from
+// there, one per lane, and hands them to the 16 lanes of each row by DPP, so
+// that a step loads only targets and labels (the next step's targets while
+// the current step's labels are in flight).  The lists are by row length, so
+// that the four rows of a wave step take the same number of 16-entry
+// slices: up to 16 entries (sums by rotations), up to 32 and up to 64 (sums
+// by match_sums).  New flags are gathered as bits in LDS and added to the
+// graph's words once per chunk, where a byte store per entry took as many
+// address cycles as reading the entry's label; a graph whose bits LDS does
+// not hold keeps flag bytes (atomic bits per entry were twice as slow there).
+// Measured on 2,048 planted partitions (24 M vertices, 490 M entries): a
+// full table sweep 5.9 -> 1.8 ms, the first sweep 1.99 -> 1.14 ms, a
+// deterministic run 35.8 -> 13.7 ms, an asynchronous one 21.4 -> 12.1 ms; of
+// the gain 16 ms came with the chunk headers and match_sums, 6 ms with the
+// 32-bit keys (row16_label) and one kernel per mode.
+template <typename OffT, bool UNIT, bool DET>
+__global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
+  // match slots of the 16 lane groups, or one 1023-slot table for the
+  // workgroup path
+  __shared__ uint32_t tags[kQPool];
   __shared__ float vals[kQPool];
-  __shared__ uint16_t lsmall[1 << kQueueMaxChunkLog2];
-  __shared__ uint16_t llarge[1 << kQueueMaxChunkLog2];
+  extern __shared__ uint32_t chunk_lds[];
   __shared__ unsigned long long wbest[kQWaves];
-  __shared__ uint32_t nsmall, nlarge, ichg, item_sh;
+  __shared__ uint32_t nlist[4], ichg, item_sh;
   __shared__ int moved_sh;
   DevStats* st = q.st;
   if (st->stop) return;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, k = tid & 15;
   const int l = st->iter;
   const int par = l & 1;
   const int pl = st->pl;                       // fixed for the whole sweep
   const bool id0 = l == 0 && st->ident;        // labels are still the ids
   // first sweep from the ids over rows with strictly increasing targets:
   // every neighbour label occurs once, so a row's Eq. 3 maximum is its
-  // largest (weight, smallest id) entry and no table is needed
+  // largest (weight, smallest id) entry and no sums are needed
   const bool direct = id0 && q.strict_rows;
   int32_t* Cc = par ? q.C1 : q.C0;             // labels at the iteration start
   int32_t* Cw = par ? q.C0 : q.C1;             // deterministic: labels after it
-  uint8_t* Fc = par ? q.F1 : q.F0;
-  uint8_t* Fn = par ? q.F0 : q.F1;
+  uint32_t* Bc = par ? q.B1 : q.B0;            // flags of this iteration: bits
+  uint32_t* Bn = par ? q.B0 : q.B1;            // (and of the next one), or
+  uint8_t* Fc = par ? q.F1 : q.F0;             // bytes for the graphs whose
+  uint8_t* Fn = par ? q.F0 : q.F1;             // bits LDS does not hold
   const OffT* off = reinterpret_cast<const OffT*>(q.off);
   const int64_t CH = (int64_t)1 << q.chunk_log2;
+  uint32_t* hdr = chunk_lds;
+  int32_t* lab_sh = reinterpret_cast<int32_t*>(chunk_lds + CH);
+  uint16_t* lst_a = reinterpret_cast<uint16_t*>(chunk_lds + 2 * CH);
+  uint16_t* lst_b = lst_a + CH;
+  uint32_t* fb = chunk_lds + 3 * CH;           // the graph's new flags, bits
   const int64_t gm = q.group_max;
-  const bool unit = q.w == nullptr;
-  const bool det = !q.async_mode;
-  for (int s = tid; s < kQPool; s += kQBT) {
-    keys[s] = kEmpty;
-    vals[s] = 0.0f;
-  }
+  for (int s = tid; s < kQPool; s += kQBT) vals[s] = 0.0f;
+  for (int s = tid; s < q.fb_words; s += kQBT) fb[s] = 0u;
+  uint32_t* tag = tags + (tid >> 4) * kMatchSlots;
+  float* val = vals + (tid >> 4) * kMatchSlots;
   uint32_t from = xcc_id();
   unsigned long long my_edges = 0, my_proc = 0;
   uint32_t my_changed = 0;
+  if (tid < 4) nlist[tid] = 0;
   if (tid == 0) {
-    nsmall = 0;
-    nlarge = 0;
     ichg = 0;
     item_sh = queue_pop(q, par, from);
   }
@@ -137,141 +182,222 @@ __global__ __launch_bounds__(kQBT) void k_queue_sweep(QueueArgs q) {
     const int64_t c0 = q.cbase[g], c1 = q.cbase[g + 1];
     const int64_t v0 = gv0 + (((int64_t)it - c0) << q.chunk_log2);
     const int64_t v1 = (v0 + CH < gv1) ? v0 + CH : gv1;
-    // 1. the chunk's flags: flagged vertices into the two lists by row
-    //    length; in deterministic mode the others carry their label over
+    // the graph's words of the bit flags
+    const int64_t w0 = gv0 >> 5;
+    const bool bits = graph_bits(gv0, gv1) <= q.fb_words;
+    const uint32_t fbw = bits ? (uint32_t)graph_bits(gv0, gv1) : 0u;
+    auto flag = [&](int32_t j) {
+      if (bits) {
+        const uint32_t r = (uint32_t)j - (uint32_t)(w0 << 5);
+        if ((r >> 5) < fbw)
+          __hip_atomic_fetch_or(&fb[r >> 5], 1u << (j & 31), __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_WORKGROUP);
+      } else {
+        Fn[j] = 1;
+        const int64_t cj = c0 + (((int64_t)j - gv0) >> q.chunk_log2);
+        if (cj >= c0 && cj < c1) q.cmark[cj] = 1;
+      }
+    };
+    const int64_t e0 = (int64_t)off[v0];
+    const int32_t* tgt = q.tgt + e0;
+    const float* w = UNIT ? nullptr : q.w + e0;
+    // 1. the chunk's labels, row headers and flags; flagged vertices into the
+    //    lists by row length, each array filled from both ends
     for (int64_t base = v0; base < v1; base += kQBT) {
       const int64_t v = base + tid;
-      bool fs = false, fl = false;
+      int kind = -1;
       if (v < v1) {
-        if (Fc[v]) {
-          Fc[v] = 0;
-          const int64_t d = (int64_t)off[v + 1] - (int64_t)off[v];
+        const int64_t o = (int64_t)off[v], d = (int64_t)off[v + 1] - o;
+        const bool f = bits ? (Bc[v >> 5] >> (v & 31)) & 1u : Fc[v] != 0;
+        if (f && !bits) Fc[v] = 0;
+        lab_sh[v - v0] = Cc[v];
+        if (f) {
           ++my_proc;
-          fs = d >= 1 && d <= gm;
-          fl = d > gm && d <= kQueueMaxDegree;
           // a row longer than the tables (the CSR changed after create):
           // left alone, reported through the error bits
-          if (d > kQueueMaxDegree) atomicOr(&st->error, 32u);
-          if ((d == 0 || d > kQueueMaxDegree) && det) Cw[v] = Cc[v];
-        } else if (det) {
-          Cw[v] = Cc[v];
+          const bool fits = d <= kQueueMaxDegree && o - e0 < (int64_t)kQMaxRel;
+          if (!fits) atomicOr(&st->error, 32u);
+          if (d >= 1 && fits) {
+            hdr[v - v0] = (uint32_t)(o - e0) << 10 | (uint32_t)d;
+            // by slices in deterministic mode; one list in asynchronous mode,
+            // whose result would change with the order (taken shortest rows
+            // first, batches of 256-4,000 vertices ended 0.01-0.02 of
+            // modularity lower)
+            kind = d > gm ? 3 : (!DET || d > 32 ? 2 : (d > 16 ? 1 : 0));
+          }
         }
       }
-      const unsigned long long ms = __ballot(fs), ml = __ballot(fl);
-      uint32_t bs = 0, bl = 0;
-      if (lane == 0) {
-        if (ms) bs = atomicAdd(&nsmall, (uint32_t)__popcll(ms));
-        if (ml) bl = atomicAdd(&nlarge, (uint32_t)__popcll(ml));
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const unsigned long long m = __ballot(kind == b);
+        if (m == 0ull) continue;
+        uint32_t pos = 0;
+        if (lane == 0) pos = atomicAdd(&nlist[b], (uint32_t)__popcll(m));
+        pos = (uint32_t)__shfl((int)pos, 0) + lane_rank(m);
+        if (kind == b) {
+          uint16_t* lst = b < 2 ? lst_a : lst_b;
+          lst[(b & 1) ? (uint32_t)CH - 1u - pos : pos] = (uint16_t)(v - v0);
+        }
       }
-      bs = (uint32_t)__shfl((int)bs, 0);
-      bl = (uint32_t)__shfl((int)bl, 0);
-      if (fs) lsmall[bs + lane_rank(ms)] = (uint16_t)(v - v0);
-      if (fl) llarge[bl + lane_rank(ml)] = (uint16_t)(v - v0);
     }
     __syncthreads();
+    // the chunk's flags are taken (its first and last word it may share)
+    if (bits)
+      for (int64_t x = (v0 >> 5) + tid; x <= (v1 - 1) >> 5; x += kQBT)
+        atomicAnd(&Bc[x], ~word_mask(x, v0, v1));
     uint32_t item_changed = 0;
-    // 2. rows of up to group_max (<= 64) entries: 16 lanes each
-    {
-      const int gi = tid >> 4, k = tid & 15;
-      uint32_t* tk = keys + gi * kQGroupSlots;
-      float* tv = vals + gi * kQGroupSlots;
-      const uint32_t ns = nsmall;
-      // the 16 lanes of a group are active or inactive together
-      for (uint32_t idx = (uint32_t)gi; idx < ns; idx += kQGroups) {
-        const int32_t v = (int32_t)(v0 + lsmall[idx]);
-        const int64_t o = (int64_t)off[v];
-        const int64_t d = (int64_t)off[v + 1] - o;
-        const int32_t cur = Cc[v];
-        int32_t j[4];
-        float wt[4];
+    // 2. rows of up to group_max (<= 64) entries: 16 lanes each, U entries a
+    //    lane, R rows of a lane group in flight; FIRST: the first sweep from
+    //    the ids over strictly increasing rows
+    const bool small = st->ident ? gv1 - gv0 <= kSmallLabels : q.b.v_off[q.b.G] <= kSmallLabels;
+    const uint32_t lbase = st->ident ? (uint32_t)gv0 : 0u;  // no label lies below
+    auto rows = [&](auto uc, auto rc, auto fc, uint32_t cnt, const uint16_t* lst, int dir) {
+      constexpr int U = decltype(uc)::value, R = decltype(rc)::value;
+      constexpr bool FIRST = decltype(fc)::value;
+      // rows per lane group and batch, so that every group has some
+      const uint32_t per = (cnt + kQGroups - 1) / kQGroups;
+      const uint32_t T = per < 16u ? per : 16u;
+      for (uint32_t b0 = 0; b0 < cnt; b0 += kQGroups * T) {
+        // step t takes listed rows 16 t .. 16 t + 15 of the batch
+        const uint32_t idx = b0 + (uint32_t)k * kQGroups + (uint32_t)(tid >> 4);
+        const bool ok = (uint32_t)k < T && idx < cnt;
+        const uint32_t li = ok ? lst[dir * (int)idx] : 0u;
+        // headers being handed out: the next row's is in lane 0 of its DPP row
+        uint32_t rh = ok ? hdr[li] : 0u, rl = li, rcur = ok ? (uint32_t)lab_sh[li] : 0u;
+        const uint32_t dl = rh & 1023u;
+        const int32_t old = (int32_t)rcur;
+        uint32_t res = rcur;
+        int32_t j[R][U];
+        uint32_t vs[R], cur[R], d[R];
+        float wt[R][U];
+        auto targets = [&]() {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t e = u * 16 + k;
-          const bool has = e < d;
-          j[u] = has ? __builtin_nontemporal_load(&q.tgt[o + e]) : v;
-          wt[u] = has ? edge_weight(q.w, o + e) : 0.0f;
-        }
-        unsigned long long best = 0;
-        if (direct) {
+          for (int r = 0; r < R; ++r) {
+            const uint32_t h = row_bcast<0>(rh);
+            d[r] = h & 1023u;
+            vs[r] = (uint32_t)v0 + row_bcast<0>(rl);
+            cur[r] = row_bcast<0>(rcur);
+            rh = row_left<1>(rh);
+            rl = row_left<1>(rl);
+            rcur = row_left<1>(rcur);
+            const uint32_t last = d[r] ? d[r] - 1u : 0u;
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (j[u] != v) best = umax64(best, pack_key(wt[u], (uint32_t)j[u]));
-        } else {
-          const uint32_t p1 = table_p1((uint32_t)d);
-          uint32_t lab[4];
+            for (int u = 0; u < U; ++u) {
+              const uint32_t e = (uint32_t)(u * 16 + k);
+              const uint32_t at = (h >> 10) + (e < last ? e : last);
+              j[r][u] = __builtin_nontemporal_load(&tgt[at]);
+              if constexpr (!UNIT) wt[r][u] = __builtin_nontemporal_load(&w[at]);
+            }
+          }
+        };
+        targets();
+        for (uint32_t t = 0; t < T; t += R) {
+          uint32_t got[R][U], ids[R][U], dc[R], vc[R], cc[R];
+          float wc[R][U];
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            lab[u] = (j[u] != v) ? (id0 ? (uint32_t)j[u] : (uint32_t)Cc[j[u]]) : kEmpty;
+          for (int r = 0; r < R; ++r) {
+            dc[r] = d[r];
+            vc[r] = vs[r];
+            cc[r] = cur[r];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) merge_lead16(lab[u], wt[u], unit);
+            for (int u = 0; u < U; ++u) {
+              ids[r][u] = (uint32_t)j[r][u];
+              wc[r][u] = UNIT ? 1.0f : wt[r][u];
+              // asynchronous mode reads past the CU's cache: a graph whose
+              // labels fit there would otherwise not see the other CUs'
+              // updates until the sweep ends
+              if constexpr (FIRST) got[r][u] = ids[r][u];
+              else if constexpr (DET) got[r][u] = (uint32_t)Cc[ids[r][u]];
+              else got[r][u] = (uint32_t)__hip_atomic_load(&Cc[ids[r][u]], __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT);
+            }
+          }
+          targets();
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (lab[u] != kEmpty) lds_accumulate(tk, tv, p1, lab[u], wt[u], q.probe);
-          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-          for (uint32_t s = (uint32_t)k; s < p1; s += 16) {
-            const uint32_t kk = tk[s];
-            if (kk != kEmpty) {
-              best = umax64(best, pack_key(tv[s], kk));
-              tk[s] = kEmpty;
-              tv[s] = 0.0f;
+          for (int r = 0; r < R; ++r) {
+            uint32_t lab[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              if constexpr (!DET && !FIRST)
+                if (id0) got[r][u] = ids[r][u];
+              lab[u] = (uint32_t)(u * 16 + k) < dc[r] && ids[r][u] != vc[r] ? got[r][u] : kEmpty;
+            }
+            typename RowSum<UNIT>::type sum[U];
+            if constexpr (FIRST) {
+#pragma unroll
+              for (int u = 0; u < U; ++u) sum[u] = wc[r][u];
+            } else if constexpr (U == 1) {
+              sum[0] = rotate_sum<UNIT>(lab[0], wc[r][0]);
+            } else {
+              match_sums<U, UNIT, false>(lab, wc[r], tag, val, sum, nullptr);
+            }
+            const uint32_t c = row16_label<U, UNIT>(lab, sum, small, lbase, cc[r]);
+            if ((uint32_t)k == t + r) res = c;
+            if (moves(c, (int32_t)cc[r], pl)) {
+              // in place at once, so that the steps that follow read it
+              if (!DET && k == 0) Cc[vc[r]] = (int32_t)c;
+#pragma unroll
+              for (int u = 0; u < U; ++u)
+                if ((uint32_t)(u * 16 + k) < dc[r]) flag((int32_t)ids[r][u]);
             }
           }
         }
-        best = row16_max_u64(best);
-        uint32_t cstar = 0;
-        const bool moved = decide(best, cur, pl, &cstar);
-        if (k == 0) {
-          if (det) Cw[v] = moved ? (int32_t)cstar : cur;
-          else if (moved) Cc[v] = (int32_t)cstar;
-          my_edges += (unsigned long long)d;
-          if (moved) {
+        if (ok) {
+          my_edges += dl;
+          if (moves(res, old, pl)) {
             ++my_changed;
             ++item_changed;
+            if (DET) lab_sh[li] = (int32_t)res;
           }
         }
-        if (moved) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (u * 16 + k < d) {
-              Fn[j[u]] = 1;
-              const int64_t cj = c0 + (((int64_t)j[u] - gv0) >> q.chunk_log2);
-              if (cj >= c0 && cj < c1) q.cmark[cj] = 1;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       }
-    }
+    };
+    auto lists = [&](auto fc) {
+      using std::integral_constant;
+      rows(integral_constant<int, 1>{}, integral_constant<int, 2>{}, fc, nlist[0], lst_a, 1);
+      rows(integral_constant<int, 2>{}, integral_constant<int, 1>{}, fc, nlist[1],
+           lst_a + CH - 1, -1);
+      rows(integral_constant<int, 4>{}, integral_constant<int, 1>{}, fc, nlist[2], lst_b, 1);
+    };
+    if (direct) lists(std::true_type{});
+    else lists(std::false_type{});
     // 3. rows of group_max + 1 .. 512 entries: the whole workgroup, one row
-    //    at a time, in a 1023-slot table over the group tables' LDS
-    const uint32_t nl = nlarge;
+    //    at a time, in a 1023-slot table over the match slots' LDS
+    const uint32_t nl = nlist[3];
+    if (nl) {
+      __syncthreads();  // the groups' slots are free
+      for (int s = tid; s < 2 * kQueueMaxDegree - 1; s += kQBT) tags[s] = kEmpty;
+    }
     for (uint32_t idx = 0; idx < nl; ++idx) {
-      __syncthreads();  // the previous row's (or the groups') table is clear
-      const int32_t v = (int32_t)(v0 + llarge[idx]);
-      const int64_t o = (int64_t)off[v];
-      const int64_t d = (int64_t)off[v + 1] - o;
-      const int32_t cur = Cc[v];
-      const uint32_t p1 = table_p1((uint32_t)d);
+      __syncthreads();  // the previous row's table is clear
+      const uint32_t li = lst_b[CH - 1 - idx];
+      const int32_t v = (int32_t)v0 + (int32_t)li;
+      const uint32_t o = hdr[li] >> 10, d = hdr[li] & 1023u;
+      const int32_t cur = lab_sh[li];
+      const uint32_t p1 = table_p1(d);
       unsigned long long best = 0;
-      for (int64_t e0 = 0; e0 < d; e0 += kQBT) {
-        const int64_t e = e0 + tid;
+      for (uint32_t b = 0; b < d; b += kQBT) {
+        const uint32_t e = b + tid;
         const bool has = e < d;
-        const int32_t j = has ? __builtin_nontemporal_load(&q.tgt[o + e]) : v;
-        float wt = has ? edge_weight(q.w, o + e) : 0.0f;
+        const int32_t j = has ? __builtin_nontemporal_load(&tgt[o + e]) : v;
+        float wt = 0.0f;
+        if constexpr (UNIT) wt = has ? 1.0f : 0.0f;
+        else wt = has ? __builtin_nontemporal_load(&w[o + e]) : 0.0f;
         if (direct) {
           if (j != v) best = umax64(best, pack_key(wt, (uint32_t)j));
         } else {
           uint32_t lab = (j != v) ? (id0 ? (uint32_t)j : (uint32_t)Cc[j]) : kEmpty;
-          merge_lead(lab, wt, unit);
-          if (lab != kEmpty) lds_accumulate(keys, vals, p1, lab, wt, q.probe);
+          merge_lead(lab, wt, UNIT);
+          if (lab != kEmpty) lds_accumulate(tags, vals, p1, lab, wt, q.probe);
         }
       }
       if (!direct) {
         __syncthreads();
         for (uint32_t s = (uint32_t)tid; s < p1; s += kQBT) {
-          const uint32_t kk = keys[s];
+          const uint32_t kk = tags[s];
           if (kk != kEmpty) {
             best = umax64(best, pack_key(vals[s], kk));
-            keys[s] = kEmpty;
+            tags[s] = kEmpty;
             vals[s] = 0.0f;
           }
         }
@@ -281,13 +407,13 @@ __global__ __launch_bounds__(kQBT) void k_queue_sweep(QueueArgs q) {
       __syncthreads();
       if (tid == 0) {
         unsigned long long b = 0;
-        for (int w = 0; w < kQWaves; ++w) b = umax64(b, wbest[w]);
+        for (int x = 0; x < kQWaves; ++x) b = umax64(b, wbest[x]);
         uint32_t cstar = 0;
         const bool moved = decide(b, cur, pl, &cstar);
-        if (det) Cw[v] = moved ? (int32_t)cstar : cur;
-        else if (moved) Cc[v] = (int32_t)cstar;
-        my_edges += (unsigned long long)d;
+        my_edges += d;
         if (moved) {
+          if (DET) lab_sh[li] = (int32_t)cstar;
+          else Cc[v] = (int32_t)cstar;
           ++my_changed;
           ++item_changed;
         }
@@ -295,12 +421,7 @@ __global__ __launch_bounds__(kQBT) void k_queue_sweep(QueueArgs q) {
       }
       __syncthreads();
       if (moved_sh) {
-        for (int64_t e = tid; e < d; e += kQBT) {
-          const int32_t jj = q.tgt[o + e];
-          Fn[jj] = 1;
-          const int64_t cj = c0 + (((int64_t)jj - gv0) >> q.chunk_log2);
-          if (cj >= c0 && cj < c1) q.cmark[cj] = 1;
-        }
+        for (uint32_t e = tid; e < d; e += kQBT) flag(tgt[o + e]);
       }
     }
     // 4. the item's changes go to the graph's count; a chunk with a change
@@ -308,14 +429,22 @@ __global__ __launch_bounds__(kQBT) void k_queue_sweep(QueueArgs q) {
     const uint32_t c = wave_sum_u32(item_changed);
     if (lane == 0 && c) atomicAdd(&ichg, c);
     __syncthreads();
+    if (DET)
+      for (int64_t v = v0 + tid; v < v1; v += kQBT) Cw[v] = lab_sh[v - v0];
+    if (ichg)
+      for (uint32_t x = tid; x < fbw; x += kQBT)
+        if (const uint32_t b = fb[x]) {
+          atomicOr(&Bn[w0 + x], b);
+          fb[x] = 0u;
+        }
+    __syncthreads();
+    if (tid < 4) nlist[tid] = 0;
     if (tid == 0) {
       if (ichg) {
         atomicAdd(&q.gchanged[g], ichg);
         q.cmark[it] = 1;
       }
       ichg = 0;
-      nsmall = 0;
-      nlarge = 0;
       item_sh = queue_pop(q, par, from);
     }
     __syncthreads();
@@ -328,7 +457,7 @@ __global__ __launch_bounds__(kQBT) void k_queue_sweep(QueueArgs q) {
   __syncthreads();
   if (tid == 0) {
     unsigned long long t = 0;
-    for (int w = 0; w < kQWaves; ++w) t += wp[w];
+    for (int x = 0; x < kQWaves; ++x) t += wp[x];
     if (t) atomicAdd(&st->processed, t);
   }
 }
@@ -393,14 +522,25 @@ __global__ __launch_bounds__(kQBT) void k_queue_step(QueueArgs q) {
     __syncthreads();
     if (state_sh == 2) {
       const int64_t c0 = q.cbase[g], c1 = q.cbase[g + 1];
+      const int64_t gv0 = q.b.v_off[g], gv1 = q.b.v_off[g + 1];
+      const uint32_t* Bn = np ? q.B1 : q.B0;
       const uint32_t x = (uint32_t)g & (uint32_t)(kXcds - 1);
+      const int64_t CH = (int64_t)1 << q.chunk_log2;
       uint32_t* out = q.items + (size_t)np * (size_t)q.nchunks + (size_t)q.qbase[x];
       for (int64_t cb = c0; cb < c1; cb += kQBT) {
         const int64_t c = cb + tid;
         bool vis = false;
-        if (c < c1 && q.cmark[c]) {
-          q.cmark[c] = 0;
-          vis = true;
+        if (c < c1) {
+          if (q.cmark[c]) {
+            q.cmark[c] = 0;
+            vis = true;
+          } else if (graph_bits(gv0, gv1) <= q.fb_words) {
+            const int64_t v0 = gv0 + ((c - c0) << q.chunk_log2);
+            const int64_t v1 = v0 + CH < gv1 ? v0 + CH : gv1;
+            uint32_t any = 0;
+            for (int64_t x = v0 >> 5; x <= (v1 - 1) >> 5 && !any; ++x) any = Bn[x] & word_mask(x, v0, v1);
+            vis = any != 0u;
+          }
         }
         const unsigned long long m = __ballot(vis);
         if (lane == 0) wcnt[wv] = (uint32_t)__popcll(m);
@@ -421,16 +561,25 @@ __global__ __launch_bounds__(kQBT) void k_queue_step(QueueArgs q) {
   }
 }
 
-// Graphs that stopped after an odd number of iterations hold their flags for
-// a next iteration in F1 and, in deterministic mode, their labels in C1:
-// both move to the even arrays, which are the handle's.
+// After the run, by chunk: each vertex's flag for a next iteration, held in
+// the array of its graph's iteration-count parity, to the handle's flag bytes
+// F0; in deterministic mode the labels of the graphs with an odd count move
+// from C1 to C0, the handle's.
 __global__ __launch_bounds__(kQBT) void k_queue_finish(QueueArgs q) {
   const bool det = q.C1 != q.C0;
-  for (int32_t g = blockIdx.x; g < q.b.G; g += gridDim.x) {
-    if ((q.b.iters[g] & 1) == 0) continue;
-    for (int64_t v = q.b.v_off[g] + threadIdx.x; v < q.b.v_off[g + 1]; v += kQBT) {
-      q.F0[v] = q.F1[v];
-      if (det) q.C0[v] = q.C1[v];
+  const int64_t CH = (int64_t)1 << q.chunk_log2;
+  for (int64_t c = blockIdx.x; c < q.nchunks; c += gridDim.x) {
+    const int32_t g = q.cgraph[c];
+    const bool odd = q.b.iters[g] & 1;
+    const int64_t gv0 = q.b.v_off[g], gv1 = q.b.v_off[g + 1];
+    const bool bits = graph_bits(gv0, gv1) <= q.fb_words;
+    if (!bits && !odd) continue;
+    const uint32_t* B = odd ? q.B1 : q.B0;
+    const int64_t v0 = gv0 + ((c - q.cbase[g]) << q.chunk_log2);
+    const int64_t v1 = v0 + CH < gv1 ? v0 + CH : gv1;
+    for (int64_t v = v0 + threadIdx.x; v < v1; v += kQBT) {
+      q.F0[v] = bits ? (uint8_t)((B[v >> 5] >> (v & 31)) & 1u) : q.F1[v];
+      if (det && odd) q.C0[v] = q.C1[v];
     }
   }
 }
@@ -451,11 +600,13 @@ __global__ void k_max_degree(const OffT* off, int64_t n, unsigned long long* dma
 }
 
 // The initial queue (every chunk of every non-empty graph, in XCD parts)
-// and its counters are built once by the host and copied in; the odd flags,
-// the chunk marks and the graphs' counts start at zero; deterministic mode
-// starts both label arrays equal.
+// and its counters are built once by the host and copied in; every vertex is
+// flagged for iteration 0, the odd flags, the chunk marks and the graphs'
+// counts start at zero; deterministic mode starts both label arrays equal.
 hipError_t launch_queue_begin(const QueueArgs& q, int64_t n, hipStream_t s) {
-  hipError_t e = launch_fill_u8(q.F1, 0, n, s);
+  hipError_t e = launch_fill_u32(q.B0, ~0u, (n + 31) / 32, s);
+  if (e == hipSuccess) e = launch_fill_u32(q.B1, 0u, (n + 31) / 32, s);
+  if (e == hipSuccess && q.F1) e = launch_fill_u8(q.F1, 0, n, s);
   if (e == hipSuccess) e = launch_fill_u8(q.cmark, 0, q.nchunks, s);
   if (e == hipSuccess) e = launch_fill_u32(q.gchanged, 0u, q.b.G, s);
   if (e == hipSuccess && q.C1 != q.C0)
@@ -470,12 +621,23 @@ hipError_t launch_queue_iter_begin(const QueueArgs& q, hipStream_t s) {
 
 hipError_t launch_queue_sweep(bool off64, const QueueArgs& q, int grid, hipStream_t s) {
   if (q.chunk_log2 < 0 || q.chunk_log2 > kQueueMaxChunkLog2 || q.group_max < 1 ||
-      q.group_max > 64)
+      q.group_max > 64 || q.fb_words < 0 || q.fb_words > kQueueFlagWords)
     return hipErrorInvalidValue;
-  if (off64)
-    hipLaunchKernelGGL(k_queue_sweep<int64_t>, dim3(grid), dim3(kQBT), 0, s, q);
-  else
-    hipLaunchKernelGGL(k_queue_sweep<int32_t>, dim3(grid), dim3(kQBT), 0, s, q);
+  const size_t lds = (kQChunkBytes << q.chunk_log2) + sizeof(uint32_t) * (size_t)q.fb_words;
+  auto launch = [&](auto oc, auto uc, auto dc) {
+    hipLaunchKernelGGL((k_queue_sweep<decltype(oc), decltype(uc)::value, decltype(dc)::value>),
+                       dim3(grid), dim3(kQBT), lds, s, q);
+  };
+  auto by_mode = [&](auto oc, auto uc) {
+    if (q.async_mode) launch(oc, uc, std::false_type{});
+    else launch(oc, uc, std::true_type{});
+  };
+  auto by_weight = [&](auto oc) {
+    if (q.w) by_mode(oc, std::false_type{});
+    else by_mode(oc, std::true_type{});
+  };
+  if (off64) by_weight(int64_t{});
+  else by_weight(int32_t{});
   return hipGetLastError();
 }
 
@@ -486,13 +648,15 @@ hipError_t launch_queue_step(const QueueArgs& q, hipStream_t s) {
 }
 
 hipError_t launch_queue_finish(const QueueArgs& q, hipStream_t s) {
-  const int g = q.b.G < 8192 ? (q.b.G > 0 ? q.b.G : 1) : 8192;
-  hipLaunchKernelGGL(k_queue_finish, dim3(g), dim3(kQBT), 0, s, q);
+  const int64_t want = q.nchunks < 1 ? 1 : q.nchunks;
+  hipLaunchKernelGGL(k_queue_finish, dim3((unsigned)(want < 8192 ? want : 8192)), dim3(kQBT), 0,
+                     s, q);
   return hipGetLastError();
 }
 
-// Seven workgroups per CU: 16 KB of tables and 4 KB of lists each.
-int queue_sweep_resident() { return 256 * 7; }
+// Five workgroups per CU: 96 VGPRs; 22 KB of LDS at the default chunk and up to
+// 8 KB of flag bits each.  (Those that start later find the queue drained.)
+int queue_sweep_resident() { return 256 * 6; }
 
 hipError_t launch_max_degree(bool off64, const void* off, int64_t n, unsigned long long* dmax,
                              hipStream_t s) {
