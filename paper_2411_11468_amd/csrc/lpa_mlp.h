@@ -38,8 +38,26 @@ struct MlpTiles {
   float b3;
 };
 
+// One Adam step's constants: omb = 1 - beta, c = 1 - beta^t.
+struct AdamStep {
+  float lr, beta1, omb1, beta2, omb2, eps, c1, c2;
+};
+
+// Gradients of a minibatch by workgroup: at most kMlpMaxParts of
+// kMlpPartStride floats.
+constexpr int kMlpPartStride = 5120;
+constexpr int kMlpMaxParts = 512;
+static_assert(kMlpParams <= kMlpPartStride, "part stride");
+
 typedef short bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Four floats rounded to bfloat16 (nearest, ties to even) by v_cvt_pk_bf16_f32:
+// the rounding of bf16_bits in two instructions instead of about 28.
+__device__ inline bf16x4_t bf16_pack4(f32x4_t x) {
+  typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(bf16x4_t, __builtin_convertvector(x, b4));
+}
 
 // The operands one lane needs, held in registers across many calls: the
 // layer-1 and layer-2 A tiles, and the biases / output weights of the hidden
@@ -107,15 +125,17 @@ struct MlpFromTiles {
 // active.  The same operations in the same order whatever the source.
 template <typename Src>
 __device__ inline float mlp_logit16_src(const Src& r, const float f[4]) {
-  bf16x4_t xb;
-  for (int j = 0; j < 4; ++j) xb[j] = (short)bf16_bits(f[j]);
+  const f32x4_t fx = {f[0], f[1], f[2], f[3]};
+  const bf16x4_t xb = bf16_pack4(fx);
   bf16x4_t h1[4];
   const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     const f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(r.w1(m), xb, zero, 0, 0, 0);
+    f32x4_t h;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h1[m][i] = (short)bf16_bits(fmaxf(acc[i] + r.b1(m, i), 0.0f));
+    for (int i = 0; i < 4; ++i) h[i] = fmaxf(acc[i] + r.b1(m, i), 0.0f);
+    h1[m] = bf16_pack4(h);
   }
   float part = 0.0f;
 #pragma unroll
@@ -136,13 +156,23 @@ __device__ inline float mlp_logit16(const MlpLane& r, const float f[4]) {
   return mlp_logit16_src(MlpFromRegs{r}, f);
 }
 
-hipError_t launch_mlp_grad(const float* p, const float* X, const float* y, int64_t B,
-                           float pos_weight, float* grad, double* loss, hipStream_t s);
+// Gradient of the mean loss of B >= 1 samples (idx: samples idx[0 .. B-1] of X
+// and y; NULL: the first B) in mlp_grad_parts(B) parts, and the samples'
+// losses (B floats; *loss cleared unless add); then the parts summed into g
+// and the losses added to *loss; the same with one Adam step.
+int mlp_grad_parts(int64_t B);
+hipError_t launch_mlp_grad(const float* p, const float* X, const float* y, const int32_t* idx,
+                           int64_t B, float pos_weight, float* part, float* ploss, double* loss,
+                           bool add, hipStream_t s);
+hipError_t launch_mlp_reduce(const float* part, const float* ploss, int64_t B, float* g,
+                             double* loss, hipStream_t s);
+hipError_t launch_mlp_reduce_step(const float* part, const float* ploss, int64_t B, float* g,
+                                  double* loss, float* p, float* m, float* v, int t, float lr,
+                                  hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int t, float lr,
-                       double beta1, double beta2, float eps, hipStream_t s);
+                       hipStream_t s);
+hipError_t launch_fill_zero(float* x, int n, hipStream_t s);
 hipError_t launch_mlp_pack(const float* p, MlpTiles* t, hipStream_t s);
-hipError_t launch_mlp_gather(const float* X, const float* y, const int32_t* idx, int64_t n,
-                             float* sX, float* sy, hipStream_t s);
 hipError_t launch_mlp_infer(const MlpTiles* t, const float* X, int64_t B, float* out,
                             hipStream_t s);
 

@@ -12,37 +12,51 @@
 
 using namespace lpa;
 
+namespace {
+// The gradient, then the loss, in one allocation read back with one copy.
+constexpr size_t kLossAt = ((size_t)kMlpParams * sizeof(float) + 7) / 8 * 8;
+constexpr size_t kGradBytes = kLossAt + sizeof(double);
+}  // namespace
+
 struct lpa_predictor_s {
   hipStream_t stream = nullptr;
   float* p = nullptr;      // fp32 master parameters
-  float* g = nullptr;      // gradient
+  float* g = nullptr;      // gradient (with loss behind it)
   float* m = nullptr;      // Adam first moment
   float* v = nullptr;      // Adam second moment
   double* loss = nullptr;  // summed loss of the last gradient
+  float* part = nullptr;   // gradients by workgroup
+  float* ploss = nullptr;  // the samples' losses (loss_cap of them)
+  int64_t loss_cap = 0;
+  uint8_t host[kGradBytes];  // a gradient and its loss read back
   MlpTiles* tiles = nullptr;
   bool tiles_ok = false;
   int32_t steps = 0;       // Adam steps taken
-  std::vector<void*> allocs;
+  uint8_t* slab = nullptr;  // one allocation for all of the above
+  float* more_loss = nullptr;  // ploss once it outgrows its part of the slab
 
-  template <typename T>
-  lpa_status alloc(T** out, size_t count) {
-    void* q = nullptr;
-    const hipError_t e = hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T));
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(LPA_ERR_OOM, std::string("hipMalloc failed for the predictor: ") +
-                                   hipGetErrorString(e));
-    }
-    allocs.push_back(q);
-    *out = static_cast<T*>(q);
-    return LPA_OK;
-  }
   ~lpa_predictor_s() {
-    for (void* q : allocs) (void)hipFree(q);
+    if (slab) (void)hipFree(slab);
+    if (more_loss) (void)hipFree(more_loss);
   }
 };
 
 namespace {
+
+// Room for the losses of n samples at a time.
+constexpr int64_t kLossCap = 8192;
+lpa_status loss_space(lpa_predictor p, int64_t n) {
+  if (n <= p->loss_cap) return LPA_OK;
+  float* q = nullptr;
+  if (hipMalloc(&q, sizeof(float) * (size_t)n) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(LPA_ERR_OOM, "hipMalloc failed for the samples' losses");
+  }
+  if (p->more_loss) (void)hipFree(p->more_loss);  // idle: every call waits for its work
+  p->more_loss = p->ploss = q;
+  p->loss_cap = n;
+  return LPA_OK;
+}
 
 // Copy n elements from host or device memory to a device buffer (staging).
 template <typename T>
@@ -97,13 +111,33 @@ lpa_status lpa_predictor_create(uint64_t seed, void* stream, lpa_predictor* out)
   lpa_predictor p = new (std::nothrow) lpa_predictor_s();
   if (!p) return fail(LPA_ERR_OOM, "host allocation failed");
   p->stream = (hipStream_t)stream;
-  lpa_status e = LPA_OK;
-  if ((e = p->alloc(&p->p, kMlpParams)) || (e = p->alloc(&p->g, kMlpParams)) ||
-      (e = p->alloc(&p->m, kMlpParams)) || (e = p->alloc(&p->v, kMlpParams)) ||
-      (e = p->alloc(&p->loss, 1)) || (e = p->alloc(&p->tiles, 1))) {
+  // parameters, gradient and loss, moments, operand tiles, losses and the
+  // gradient's parts (10 MB) in one allocation
+  size_t bytes = 0;
+  auto take = [&](size_t size) {
+    const size_t at = bytes;
+    bytes += (size + 255) / 256 * 256;
+    return at;
+  };
+  const size_t params = sizeof(float) * kMlpParams;
+  const size_t at_p = take(params), at_g = take(kGradBytes), at_m = take(params),
+               at_v = take(params), at_t = take(sizeof(MlpTiles)),
+               at_l = take(sizeof(float) * kLossCap),
+               at_part = take(sizeof(float) * (size_t)kMlpMaxParts * kMlpPartStride);
+  if (hipMalloc(&p->slab, bytes) != hipSuccess) {
+    (void)hipGetLastError();
     delete p;
-    return e;
+    return fail(LPA_ERR_OOM, "allocation failed for the predictor");
   }
+  p->p = reinterpret_cast<float*>(p->slab + at_p);
+  p->g = reinterpret_cast<float*>(p->slab + at_g);
+  p->loss = reinterpret_cast<double*>(p->slab + at_g + kLossAt);
+  p->m = reinterpret_cast<float*>(p->slab + at_m);
+  p->v = reinterpret_cast<float*>(p->slab + at_v);
+  p->tiles = reinterpret_cast<MlpTiles*>(p->slab + at_t);
+  p->ploss = reinterpret_cast<float*>(p->slab + at_l);
+  p->loss_cap = kLossCap;
+  p->part = reinterpret_cast<float*>(p->slab + at_part);
   // He-uniform weights (limit sqrt(6 / fan_in)), zero biases
   std::vector<float> h(kMlpParams, 0.0f);
   std::mt19937_64 rng(seed);
@@ -233,18 +267,19 @@ lpa_status lpa_predictor_gradient(lpa_predictor p, const float* X, const float* 
   float *dX = nullptr, *dy = nullptr;
   if (lpa_status e = to_device(X, (size_t)n * kMlpIn, &dX, &st.bufs, p->stream)) return e;
   if (lpa_status e = to_device(y, (size_t)n, &dy, &st.bufs, p->stream)) return e;
-  std::vector<float> z(kMlpParams, 0.0f);
-  LPA_HIP(hipMemcpyAsync(p->g, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice,
-                         p->stream));
-  const double zero = 0.0;
-  LPA_HIP(hipMemcpyAsync(p->loss, &zero, sizeof(double), hipMemcpyHostToDevice, p->stream));
-  LPA_HIP(launch_mlp_grad(p->p, dX, dy, n, pos_weight, p->g, p->loss, p->stream));
-  if (grad)
-    LPA_HIP(hipMemcpyAsync(grad, p->g, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost,
-                           p->stream));
-  double l = 0.0;
-  LPA_HIP(hipMemcpyAsync(&l, p->loss, sizeof(double), hipMemcpyDeviceToHost, p->stream));
+  if (lpa_status e = loss_space(p, n)) return e;
+  if (n > 0) {
+    LPA_HIP(launch_mlp_grad(p->p, dX, dy, nullptr, n, pos_weight, p->part, p->ploss, p->loss,
+                            false, p->stream));
+    LPA_HIP(launch_mlp_reduce(p->part, p->ploss, n, p->g, p->loss, p->stream));
+  } else {
+    LPA_HIP(launch_fill_zero(p->g, kMlpParams, p->stream));
+  }
+  LPA_HIP(hipMemcpyAsync(p->host, p->g, kGradBytes, hipMemcpyDeviceToHost, p->stream));
   LPA_HIP(hipStreamSynchronize(p->stream));
+  double l = 0.0;
+  std::memcpy(&l, p->host + kLossAt, sizeof(l));
+  if (grad) std::memcpy(grad, p->host, sizeof(float) * kMlpParams);
   if (loss) *loss = n > 0 ? l / (double)n : 0.0;
   return LPA_OK;
 }
@@ -255,7 +290,7 @@ lpa_status lpa_predictor_adam(lpa_predictor p, const float* grad, float lr) {
     LPA_HIP(hipMemcpyAsync(p->g, grad, sizeof(float) * kMlpParams, hipMemcpyHostToDevice,
                            p->stream));
   p->steps += 1;
-  LPA_HIP(launch_adam(p->p, p->g, p->m, p->v, p->steps, lr, 0.9, 0.999, 1e-8f, p->stream));
+  LPA_HIP(launch_adam(p->p, p->g, p->m, p->v, p->steps, lr, p->stream));
   LPA_HIP(hipStreamSynchronize(p->stream));
   p->tiles_ok = false;
   return LPA_OK;
@@ -270,52 +305,44 @@ lpa_status lpa_predictor_train(lpa_predictor p, const float* X, const float* y, 
   float *dX = nullptr, *dy = nullptr;
   if (lpa_status e = to_device(X, (size_t)n * kMlpIn, &dX, &st.bufs, p->stream)) return e;
   if (lpa_status e = to_device(y, (size_t)n, &dy, &st.bufs, p->stream)) return e;
-  // shuffled copies of the samples, one permutation per epoch (host RNG)
-  float *sX = nullptr, *sy = nullptr;
+  if (lpa_status e = loss_space(p, std::min<int64_t>(n, opt->batch))) return e;
+  // one permutation of the samples per epoch (host RNG); the minibatches take
+  // the samples through it, and the host draws the next epoch's while the GPU
+  // runs this one
   int32_t* didx = nullptr;
   {
     void* q;
-    if (hipMalloc(&q, sizeof(float) * (size_t)n * kMlpIn) != hipSuccess)
+    if (hipMalloc(&q, sizeof(int32_t) * (size_t)n) != hipSuccess) {
+      (void)hipGetLastError();
       return fail(LPA_ERR_OOM, "hipMalloc failed");
-    st.bufs.push_back(q);
-    sX = static_cast<float*>(q);
-    if (hipMalloc(&q, sizeof(float) * (size_t)n) != hipSuccess)
-      return fail(LPA_ERR_OOM, "hipMalloc failed");
-    st.bufs.push_back(q);
-    sy = static_cast<float*>(q);
-    if (hipMalloc(&q, sizeof(int32_t) * (size_t)n) != hipSuccess)
-      return fail(LPA_ERR_OOM, "hipMalloc failed");
+    }
     st.bufs.push_back(q);
     didx = static_cast<int32_t*>(q);
   }
   std::vector<int32_t> perm((size_t)n);
   std::iota(perm.begin(), perm.end(), 0);
   std::mt19937_64 rng(opt->seed);
-  std::vector<float> z(kMlpParams, 0.0f);
   double last = 0.0;
+  if (opt->epochs > 0) std::shuffle(perm.begin(), perm.end(), rng);
   for (int32_t ep = 0; ep < opt->epochs; ++ep) {
-    std::shuffle(perm.begin(), perm.end(), rng);
     LPA_HIP(hipMemcpyAsync(didx, perm.data(), sizeof(int32_t) * (size_t)n,
                            hipMemcpyHostToDevice, p->stream));
-    LPA_HIP(launch_mlp_gather(dX, dy, didx, n, sX, sy, p->stream));
-    double ep_loss = 0.0;
+    LPA_HIP(hipStreamSynchronize(p->stream));  // perm is free again
     for (int64_t b0 = 0; b0 < n; b0 += opt->batch) {
       const int64_t nb = std::min<int64_t>(opt->batch, n - b0);
-      LPA_HIP(hipMemcpyAsync(p->g, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice,
-                             p->stream));
-      const double zero = 0.0;
-      LPA_HIP(hipMemcpyAsync(p->loss, &zero, sizeof(double), hipMemcpyHostToDevice, p->stream));
-      LPA_HIP(launch_mlp_grad(p->p, sX + b0 * kMlpIn, sy + b0, nb, opt->pos_weight, p->g,
-                              p->loss, p->stream));
+      LPA_HIP(launch_mlp_grad(p->p, dX, dy, didx + b0, nb, opt->pos_weight, p->part, p->ploss,
+                              p->loss, b0 > 0, p->stream));
       p->steps += 1;
-      LPA_HIP(launch_adam(p->p, p->g, p->m, p->v, p->steps, opt->lr, 0.9, 0.999, 1e-8f,
-                          p->stream));
-      double l = 0.0;
-      LPA_HIP(hipMemcpyAsync(&l, p->loss, sizeof(double), hipMemcpyDeviceToHost, p->stream));
-      LPA_HIP(hipStreamSynchronize(p->stream));
-      ep_loss += l;
+      LPA_HIP(launch_mlp_reduce_step(p->part, p->ploss, nb, p->g, p->loss, p->p, p->m, p->v,
+                                     p->steps, opt->lr, p->stream));
     }
-    last = ep_loss / (double)n;
+    if (ep + 1 < opt->epochs) std::shuffle(perm.begin(), perm.end(), rng);
+  }
+  if (opt->epochs > 0) {
+    double l = 0.0;
+    LPA_HIP(hipMemcpyAsync(&l, p->loss, sizeof(double), hipMemcpyDeviceToHost, p->stream));
+    LPA_HIP(hipStreamSynchronize(p->stream));
+    last = l / (double)n;
   }
   p->tiles_ok = false;
   if (final_loss) *final_loss = (float)last;
