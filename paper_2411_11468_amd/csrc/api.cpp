@@ -98,10 +98,9 @@ struct lpa_graph_s {
   void* tv_gvals = nullptr;           // hubs' table values of that width
   unsigned long long* tv_vmax = nullptr;
   uint32_t* tv_nl = nullptr;
-  int frontier_grid = 1, apply_grid = 1, hub_acc_grid = 1, hub_fin_grid = 1, pull_grid = 1,
+  int frontier_grid = 1, hub_acc_grid = 1, hub_fin_grid = 1, pull_grid = 1,
       push_grid = 1, hub_direct_grid = 1;
-  int32_t* pend_v = nullptr;
-  int32_t* pend_c = nullptr;
+  int32_t* lab_in = nullptr;  // labels given by the caller, staged
   int32_t* Cn = nullptr;
   uint8_t* chg = nullptr;
   DevStats* st = nullptr;
@@ -232,10 +231,11 @@ struct lpa_graph_s {
     } else if (kid == kKidBatch) {
       bytes = 2.0 * n;  // change byte read, flag cleared at most once
     } else if (kid == kKidApply) {
-      unsigned long long listed = 0;
-      for (int c = 1; c < kClassHub; ++c) listed += h.active[c];
-      verts = (int64_t)(h.pending + listed);
-      bytes = 12.0 * (double)h.pending + 12.0 * (double)listed;
+      // change byte per vertex; per changed vertex its label read and written
+      unsigned long long changed = 0;
+      for (int c = 0; c < kNumClasses; ++c) changed += h.changed[c];
+      verts = (int64_t)changed;
+      bytes = (double)n + 8.0 * (double)changed;
     }
     p.launches += 1;
     p.total_ms += ms;
@@ -348,7 +348,7 @@ struct lpa_graph_s {
     HubArgs a;
     a.off = off; a.tgt = tgt; a.w = w; a.C = C; a.F = F; a.chg = chg;
     a.uoff = uoff; a.utgt = utgt; a.uw = uw; a.inv = inv; a.ctgt = ctgt;
-    a.pend_v = pend_v; a.pend_c = pend_c; a.st = st;
+    a.Cn = Cn; a.st = st;
     a.hub_vid = hub_vid; a.hub_tab = hub_tab; a.hub_best = hub_best; a.hub_old = hub_old;
     a.hub_nch = hub_nch; a.hub_ovf = hub_ovf; a.hub_lgb = hub_lgb;
     a.hub_slice0 = hub_slice0; a.hub_boff0 = hub_boff0;
@@ -696,8 +696,7 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
   // labels, flags, deterministic-mode queue
   if (lpa_status e = G->dalloc(&G->C, n)) return e;
   if (lpa_status e = G->dalloc(&G->F, n)) return e;
-  if (lpa_status e = G->dalloc(&G->pend_v, n)) return e;
-  if (lpa_status e = G->dalloc(&G->pend_c, n)) return e;
+  if (lpa_status e = G->dalloc(&G->lab_in, n)) return e;
   if (lpa_status e = G->dalloc(&G->Cn, n)) return e;
   if (lpa_status e = G->dalloc(&G->chg, n)) return e;
   if (lpa_status e = G->dalloc(&G->chg_bits, (n + 31) / 32)) return e;
@@ -749,7 +748,6 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
   }
   G->frontier_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 8191) / 8192, 256 * 8));
   G->learn_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 2048));
-  G->apply_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 256 * 8));
   G->pull_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 31) / 32, 256 * 8));
   G->push_grid = 256 * 8;
 
@@ -996,11 +994,9 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     if (lpa_status e = mark(kKidHubFin)) return e;
     LPA_HIP(launch_hub_fin(g->off64, ha, g->hub_fin_grid, s));
   }
-  if (!async_mode) {
-    if (lpa_status e = mark(kKidApply)) return e;
-    LPA_HIP(launch_apply(g->st, g->lists, g->Cn, g->pend_v, g->pend_c, g->C, g->apply_grid, s));
-  }
   if (cc) {
+    if (!async_mode)
+      LPA_HIP(launch_publish(g->st, g->chg, g->n_active, g->Cn, g->C, g->chg_bits, true, false, s));
     // Cross-Check: rounds until no revert decision changes (the decisions
     // depend only on smaller ids, so at most one round per chain step)
     if (lpa_status e = mark(-1)) return e;
@@ -1019,6 +1015,10 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   // push or pull from this iteration's counters, the other kernels return
   if (lpa_status e = mark(kKidDecide)) return e;
   LPA_HIP(launch_flag_decide(g->st, g->m, g->n, o.flag_mode, g->tun.pull_divisor, s));
+  // labels (Cross-Check has published its own) and change bits
+  if (lpa_status e = mark(kKidApply)) return e;
+  LPA_HIP(launch_publish(g->st, g->chg, g->n_active, g->Cn, g->C, g->chg_bits,
+                         !async_mode && !cc, true, s));
   if (lpa_status e = mark(kKidPush)) return e;
   LPA_HIP(launch_push_lists(g->off64, g->off, g->tgt, g->lists, g->chg, g->F, g->st,
                             g->push_grid, s));
@@ -1027,8 +1027,8 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     LPA_HIP(launch_push_hubs(g->off64, ha, g->hub_fin_grid, s));
   }
   if (lpa_status e = mark(kKidPull)) return e;
-  LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg, g->chg_bits, g->F, g->st,
-                            g->pull_grid, s));
+  LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
+                            g->st, g->pull_grid, s));
   if (g->H > 0) {
     if (lpa_status e = mark(kKidPullHubs)) return e;
     LPA_HIP(launch_pull_hubs(g->off64, g->off, g->tgt, g->hub_vid, g->H, g->chg_bits, g->F,
@@ -1192,8 +1192,8 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
   if (g->G > 0) LPA_HIP(launch_batch_reset(g->batch_args(), s));
   const int32_t* init = nullptr;
   if (o.initial_labels) {
-    if (lpa_status e = stage_labels(g, o.initial_labels, g->pend_v)) return e;
-    init = g->pend_v;
+    if (lpa_status e = stage_labels(g, o.initial_labels, g->lab_in)) return e;
+    init = g->lab_in;
   }
   LPA_HIP(launch_init(n, init, g->inv, g->C, g->F, g->st, s));
   if (init) {
@@ -1649,8 +1649,10 @@ lpa_status lpa_get_flags(lpa_graph g, uint8_t* flags) {
     // from the change bytes it left (the frontier of a next run clears them)
     hipStream_t s = g->stream;
     LPA_HIP(launch_flags_resume(g->st, s));
-    LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg, g->chg_bits, g->F, g->st,
-                              g->pull_grid, s));
+    LPA_HIP(launch_publish(g->st, g->chg, g->n_active, nullptr, nullptr, g->chg_bits, false, true,
+                           s));
+    LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
+                              g->st, g->pull_grid, s));
     if (g->H > 0)
       LPA_HIP(launch_pull_hubs(g->off64, g->off, g->tgt, g->hub_vid, g->H, g->chg_bits, g->F,
                                g->st, s));
@@ -1735,8 +1737,8 @@ lpa_status lpa_modularity(lpa_graph g, const int32_t* labels, double* q) {
   }
   const int32_t* lab = labels;
   if (!is_device_ptr(labels)) {
-    if (lpa_status e = stage_labels(g, labels, g->pend_v)) return e;
-    lab = g->pend_v;
+    if (lpa_status e = stage_labels(g, labels, g->lab_in)) return e;
+    lab = g->lab_in;
   }
   LPA_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(g->st), 0u,
                           sizeof(DevStats) / sizeof(uint32_t), s));
@@ -1775,8 +1777,8 @@ lpa_status lpa_modularity_noalloc(lpa_graph g, const int32_t* labels, double* q)
   LPA_HIP(modularity_scratch(&sig, &acc));
   const int32_t* lab = labels;
   if (!is_device_ptr(labels)) {
-    if (lpa_status e = stage_labels(g, labels, g->pend_v)) return e;
-    lab = g->pend_v;
+    if (lpa_status e = stage_labels(g, labels, g->lab_in)) return e;
+    lab = g->lab_in;
   }
   LPA_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(g->st), 0u,
                           sizeof(DevStats) / sizeof(uint32_t), s));

@@ -22,7 +22,6 @@ constexpr int kXcds = 8;                  // accelerator complex dies of an MI35
 // the hub-plan kernel, read back by the host after the iteration.
 struct DevStats {
   unsigned long long processed;                 // vertices taken this iteration
-  unsigned long long pending;                   // deterministic mode: queued hub label writes
   unsigned long long edges[kNumClasses];        // CSR entries scanned, per class
   unsigned long long changed[kNumClasses];      // label changes, per class
   unsigned long long flagw[kNumClasses];        // sum of degrees of changed vertices
@@ -128,7 +127,7 @@ struct SweepArgs {
   const float* w;         // NULL: unit weights
   int32_t* C;             // labels (read; written in place in async mode)
   int32_t* Cn;            // deterministic mode: label after this iteration,
-                          // written for every processed vertex
+                          // written for the vertices that move
   uint8_t* F;             // flags for the next iteration (set on change)
   uint8_t* chg;           // changed-in-this-iteration byte per vertex
   const int32_t* active;  // active vertex list of this class
@@ -170,8 +169,8 @@ struct HubArgs {
   int32_t* C;
   uint8_t* F;
   uint8_t* chg;
-  int32_t* pend_v;                 // deterministic mode: queued (hub, label)
-  int32_t* pend_c;
+  int32_t* Cn;                     // deterministic mode: labels after this
+                                   // iteration of the vertices that move
   DevStats* st;
   const int32_t* hub_vid;          // H hub vertex ids
   const int64_t* hub_tab;          // H offsets into the overflow table
@@ -339,10 +338,15 @@ hipError_t launch_cc_apply(int32_t* C, const int32_t* Cp, uint8_t* chg, uint8_t*
 // pass (resume), close it again (done).
 hipError_t launch_flags_resume(DevStats* st, hipStream_t s);
 hipError_t launch_flags_done(DevStats* st, hipStream_t s);
-// packs chg into chg_bits ((n + 31) / 32 words), then pulls the flags
+// After the sweep: the changed vertices' labels copied from Cn to C (apply),
+// and chg packed into chg_bits ((n + 31) / 32 words) if this iteration's
+// flags are pulled (pack).
+hipError_t launch_publish(const DevStats* st, const uint8_t* chg, int64_t n, const int32_t* Cn,
+                          int32_t* C, uint32_t* chg_bits, bool apply, bool pack, hipStream_t s);
+// Pulls the flags, from the bits that launch_publish packed.
 hipError_t launch_pull_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
-                             const uint8_t* cls, const uint8_t* chg, uint32_t* chg_bits,
-                             uint8_t* F, DevStats* st, int grid, hipStream_t s);
+                             const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F,
+                             DevStats* st, int grid, hipStream_t s);
 hipError_t launch_push_lists(bool off64, const void* off, const int32_t* tgt,
                              int32_t* const* lists, const uint8_t* chg, uint8_t* F,
                              DevStats* st, int grid, hipStream_t s);
@@ -350,9 +354,6 @@ hipError_t launch_push_hubs(bool off64, const HubArgs& a, int grid, hipStream_t 
 hipError_t launch_pull_hubs(bool off64, const void* off, const int32_t* tgt,
                             const int32_t* hub_vid, int32_t H, const uint32_t* chg_bits,
                             uint8_t* F, DevStats* st, hipStream_t s);
-hipError_t launch_apply(const DevStats* st, int32_t* const* lists, const int32_t* Cn,
-                        const int32_t* pv, const int32_t* pc, int32_t* C, int grid,
-                        hipStream_t s);
 hipError_t launch_sweep(bool off64, int cls, const SweepArgs& a, int grid, bool feat,
                         hipStream_t s);
 // The first sweep from identity labels over rows with strictly increasing

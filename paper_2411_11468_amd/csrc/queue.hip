@@ -470,7 +470,6 @@ __global__ void k_queue_iter_begin(QueueArgs q) {
   const int tid = threadIdx.x;
   if (tid == 0) {
     st->processed = 0;
-    st->pending = 0;
     st->pull_scanned = 0;
     st->pull_mode = 0;
     st->graphs_left = 0;

@@ -12,8 +12,8 @@
 //      the neighbours of changed vertices are flagged for the next iteration
 //      (Sec. 4 item 4) after the sweep, by the flag kernels of graph.hip.
 // In asynchronous mode the new label is stored in place; in deterministic
-// mode it is queued and applied after the sweep, so every vertex reads the
-// iteration-start labels.  In the first iteration of a run that starts from
+// mode it goes to Cn and is copied after the sweep (k_publish), so every
+// vertex reads the iteration-start labels.  In the first iteration of a run that starts from
 // labels = vertex ids (Algorithm 1's initialisation) a neighbour's label is
 // its id and is not gathered: the deterministic result is unchanged, and in
 // asynchronous mode this is the read of the iteration-start value, which an
@@ -205,8 +205,8 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
     if (leader) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
     }
     if (moved && leader) a.chg[v] = 1;
@@ -314,7 +314,7 @@ __device__ __forceinline__ void row_result(const SweepArgs& a, int32_t v, int32_
                                            unsigned long long& edges, uint32_t& changed,
                                            unsigned long long& flagw) {
   const bool moved = moves(res, cur, pl);
-  if (!a.async_mode) a.Cn[v] = moved ? (int32_t)res : cur;
+  if (!a.async_mode && moved) a.Cn[v] = (int32_t)res;
   if (moved) a.chg[v] = 1;
   edges += (unsigned long long)d;
   changed += moved ? 1u : 0u;
@@ -476,8 +476,8 @@ __global__ __launch_bounds__(256) void k_sweep_lane4(SweepArgs a) {
       const bool moved = decide(best, cur[r], pl, &cstar);
       if (a.async_mode) {
         if (moved) a.C[v[r]] = (int32_t)cstar;
-      } else {
-        a.Cn[v[r]] = moved ? (int32_t)cstar : cur[r];
+      } else if (moved) {
+        a.Cn[v[r]] = (int32_t)cstar;
       }
       if (moved) a.chg[v[r]] = 1;
       my_edges += (unsigned long long)d[r];
@@ -657,8 +657,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_sweep_wave_pipe(SweepArgs a) {
     if (lane == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
       if (moved) a.chg[v] = 1;
       my_edges += (unsigned long long)d;
@@ -846,8 +846,8 @@ __global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
     if (k == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
       if (moved) a.chg[v] = 1;
       my_edges += (unsigned long long)d;
@@ -965,8 +965,8 @@ __global__ __launch_bounds__(BT) void k_sweep_block(SweepArgs a) {
     if (tid == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
     }
     if (moved && tid == 0) a.chg[v] = 1;
@@ -1125,8 +1125,8 @@ __global__ __launch_bounds__(BT) void k_sweep_block_pipe(SweepArgs a) {
     if (tid == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
       if (moved) a.chg[v] = 1;
       my_edges += (unsigned long long)d;
@@ -1708,9 +1708,7 @@ __global__ __launch_bounds__(BT) void k_hub_fin(HubArgs a) {
       if (a.async_mode) {
         a.C[v] = (int32_t)cstar;
       } else {
-        const unsigned long long pos = atomicAdd(&a.st->pending, 1ull);
-        a.pend_v[pos] = v;
-        a.pend_c[pos] = (int32_t)cstar;
+        a.Cn[v] = (int32_t)cstar;
       }
       atomicAdd(&a.st->changed[kClassHub], 1ull);
       a.chg[v] = 1;
@@ -1874,8 +1872,8 @@ __global__ __launch_bounds__(BT) void k_sweep_direct(SweepArgs a) {
     if (leader) {
       if (a.async_mode) {
         if (moved) a.C[vi] = (int32_t)cstar;
-      } else {
-        a.Cn[vi] = moved ? (int32_t)cstar : v;
+      } else if (moved) {
+        a.Cn[vi] = (int32_t)cstar;
       }
       if (moved) a.chg[vi] = 1;
       my_edges += (unsigned long long)d;
@@ -1977,8 +1975,8 @@ __global__ __launch_bounds__(BT) void k_sweep_direct2(SweepArgs a) {
       if (valid[r] && k == 0) {
         if (a.async_mode) {
           if (moved) a.C[vi[r]] = (int32_t)cstar;
-        } else {
-          a.Cn[vi[r]] = moved ? (int32_t)cstar : v[r];
+        } else if (moved) {
+          a.Cn[vi[r]] = (int32_t)cstar;
         }
         if (moved) a.chg[vi[r]] = 1;
         my_edges += (unsigned long long)d[r];

@@ -200,8 +200,8 @@ __global__ __launch_bounds__(kTvWaves * 64) void k_tv_wave(SweepArgs a) {
     if (lane == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
       if (moved) a.chg[v] = 1;
       my_edges += (unsigned long long)d;
@@ -270,8 +270,8 @@ __global__ __launch_bounds__(BT) void k_tv_block(SweepArgs a) {
     if (tid == 0) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
-      } else {
-        a.Cn[v] = moved ? (int32_t)cstar : cur;
+      } else if (moved) {
+        a.Cn[v] = (int32_t)cstar;
       }
       if (moved) a.chg[v] = 1;
       my_edges += (unsigned long long)d;
