@@ -98,7 +98,7 @@ struct lpa_graph_s {
   void* tv_gvals = nullptr;           // hubs' table values of that width
   unsigned long long* tv_vmax = nullptr;
   uint32_t* tv_nl = nullptr;
-  int frontier_grid = 1, hub_acc_grid = 1, hub_fin_grid = 1, pull_grid = 1,
+  int hub_acc_grid = 1, hub_fin_grid = 1, pull_grid = 1,
       push_grid = 1, hub_direct_grid = 1;
   int32_t* lab_in = nullptr;  // labels given by the caller, staged
   int32_t* Cn = nullptr;
@@ -746,7 +746,6 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
                                tv_max_resident(c, t.table_values)));
     }
   }
-  G->frontier_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 8191) / 8192, 256 * 8));
   G->learn_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 2048));
   G->pull_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 31) / 32, 256 * 8));
   G->push_grid = 256 * 8;
@@ -948,7 +947,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     LPA_HIP(launch_frontier_learned(n, n_later, g->F, g->cls, g->lists, g->chg, g->st, g->lrec, rc.tiles,
                                     rc.tr, g->learn_grid, s));
   else
-    LPA_HIP(launch_frontier(n, n_later, g->F, g->cls, g->lists, g->chg, g->st, g->frontier_grid, s));
+    LPA_HIP(launch_frontier(n, n_later, g->F, g->cls, g->lists, g->chg, g->st, s));
   if (g->H > 0 && direct) {
     if (lpa_status e = mark(kKidHubDirect)) return e;
     LPA_HIP(launch_hub_direct(g->off64, ha, g->hub_direct_grid, s));

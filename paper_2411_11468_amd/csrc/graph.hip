@@ -628,15 +628,25 @@ hipError_t launch_hub_plan(bool off64, const HubArgs& a, int32_t* C, uint8_t* F,
 // ---- frontier: append flagged vertices to their class list, clear flags ------
 struct ListPtrs { int32_t* p[kNumClasses]; };
 
+// Words per thread and step by vertex count: few words spread a small graph's
+// steps over the chip, many keep the count of global atomics down (1 M
+// vertices: 22 us with one word, 13 with four, 20 with eight; 10 000: 5.7 us
+// with one, 16 with eight).
+constexpr int64_t kFrontierOneWord = (int64_t)1 << 18, kFrontierFourWords = (int64_t)1 << 22;
+
+// kWords words of four vertices per thread and block step: the block's
+// appends cost one global atomic per class and step.  A wave whose 256
+// vertices are all listed in one class skips the placing, and four vertices
+// of one class are stored at once.  67 M vertices (8192 x 8192 lattice), per
+// launch: 212 -> 174 us; the flags, classes and list entries alone take 106.
+template <int kWords>
 __global__ __launch_bounds__(kBT) void k_frontier(int64_t n_all, int64_t n_later, uint8_t* F,
                                                   const uint8_t* cls, ListPtrs lists,
                                                   uint8_t* chg_clear, DevStats* st) {
-  // kWords words of four vertices per thread and block step: the block's
-  // appends cost one global atomic per class and step
-  constexpr int kWords = 8;
   constexpr int64_t kStep = (int64_t)kBT * kWords * 4;
+  static_assert(kStep <= 65536, "places within a step are kept in 16 bits");
   __shared__ uint32_t cnt[kNumClasses];
-  __shared__ uint32_t base[kNumClasses];
+  __shared__ int32_t* out[kNumClasses];  // where this step's vertices of a class go
   if (st->stop) return;
   // vertices scanned: all in the first iteration, then n_later (the
   // vertices of degree 0, last in the internal order, are flagged only by
@@ -670,68 +680,86 @@ __global__ __launch_bounds__(kBT) void k_frontier(int64_t n_all, int64_t n_later
         }
       }
     }
-    // class of each vertex to be listed (-1: none) and its place among those
-    // of its class, in vertex order within the wave's 256 vertices of word k:
-    // the sweeps' loads and stores by listed vertex then fall on consecutive
-    // addresses where consecutive vertices are listed.  (Placed byte by byte
-    // of the words instead, 64 lanes spanned 256 vertices: 0.88 against 0.48
-    // ms per sweep of the 67 M short rows of an 8192 x 8192 lattice, 0.29
-    // against 0.18 ms per label copy; R-MAT 26 56.0 against 54.5 ms per run.)
-    int8_t cq[kWords][4];
-    uint32_t pos[kWords][4];
+    // class of each vertex to be listed (byte q of c4; 0: none) and its place
+    // among those of its class (half q & 1 of pos[q >> 1]), in vertex order
+    // within the wave's 256 vertices of word k: the sweeps' loads and stores
+    // by listed vertex then fall on consecutive addresses where consecutive
+    // vertices are listed.  (Placed byte by byte of the words instead, 64
+    // lanes spanned 256 vertices: 0.88 against 0.48 ms per sweep of the 67 M
+    // short rows of an 8192 x 8192 lattice, 0.29 against 0.18 ms per label
+    // copy; R-MAT 26 56.0 against 54.5 ms per run.)
+    uint32_t pos[kWords][2];
 #pragma unroll
     for (int k = 0; k < kWords; ++k) {
-      unsigned long long left = 0ull;
+      const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)c4[k]);
+      const bool all4 = ((f4[k] - 0x01010101u) & ~f4[k] & 0x80808080u) == 0u;
+      pos[k][0] = pos[k][1] = 0u;
+      if (__all(all4 && c4[k] == first) && first == (first & 0xFFu) * 0x01010101u &&
+          first != 0u && (first & 0xFFu) != (uint32_t)kClassHub) {
+        // all 256 vertices listed, in one class
+        uint32_t b = 0;
+        if (lane == 0) b = atomicAdd(&cnt[first & 0xFFu], 256u);
+        b = (uint32_t)__builtin_amdgcn_readfirstlane((int)b) + 4u * (uint32_t)lane;
+        pos[k][0] = b | (b + 1u) << 16;
+        pos[k][1] = (b + 2u) | (b + 3u) << 16;
+        proc += 4u;
+        continue;
+      }
+      uint32_t todo = 0u;  // q with a vertex still to be placed
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const bool f = ((f4[k] >> (8 * q)) & 0xFFu) != 0u;
-        const int c = (int)((c4[k] >> (8 * q)) & 0xFFu);
+        const uint32_t c = (c4[k] >> (8 * q)) & 0xFFu;
         proc += f ? 1u : 0u;
-        cq[k][q] = (f && c != 0 && c != kClassHub) ? (int8_t)c : (int8_t)-1;
-        pos[k][q] = 0u;
-        left |= __ballot(cq[k][q] >= 0);
+        if (f && c != 0u && c != (uint32_t)kClassHub) todo |= 1u << q;
+        else c4[k] &= ~(0xFFu << (8 * q));
       }
+      unsigned long long left = __ballot(todo != 0u);
       // one LDS atomic per class present in the wave
-      uint32_t todo = 0u;  // q with a vertex still to be placed
-#pragma unroll
-      for (int q = 0; q < 4; ++q) todo |= cq[k][q] >= 0 ? 1u << q : 0u;
       while (left) {
         const int src = __ffsll((long long)left) - 1;
-        int mine = -1;
-#pragma unroll
-        for (int q = 3; q >= 0; --q)
-          if (todo & (1u << q)) mine = cq[k][q];
-        const int cc = __builtin_amdgcn_readlane(mine, src);
-        uint32_t total = 0, before = 0, own = 0;
+        const uint32_t mine = todo ? (c4[k] >> (8 * (__ffs((int)todo) - 1))) & 0xFFu : 0u;
+        const uint32_t cc = (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
+        uint32_t total = 0, before = 0;
+        uint32_t in4 = 0u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const bool in = cq[k][q] == cc;
+          const bool in = ((c4[k] >> (8 * q)) & 0xFFu) == cc;
           const unsigned long long m = __ballot(in);
           total += (uint32_t)__popcll(m);
           before += lane_rank(m);
-          if (in) {
-            pos[k][q] = own++;
-            todo &= ~(1u << q);
-          }
+          in4 |= in ? 1u << q : 0u;
         }
+        todo &= ~in4;
         uint32_t b = 0;
         if (lane == 0) b = atomicAdd(&cnt[cc], total);
         b = (uint32_t)__builtin_amdgcn_readfirstlane((int)b) + before;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (cq[k][q] == cc) pos[k][q] += b;
+          if (in4 & (1u << q)) pos[k][q >> 1] |= b++ << (16 * (q & 1));
         left = __ballot(todo != 0u);
       }
     }
     __syncthreads();
-    if (tid < kNumClasses) base[tid] = cnt[tid] ? atomicAdd(&st->active[tid], cnt[tid]) : 0u;
+    if (tid < kNumClasses && cnt[tid])
+      out[tid] = lists.p[tid] + atomicAdd(&st->active[tid], cnt[tid]);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kWords; ++k)
+    for (int k = 0; k < kWords; ++k) {
+      const uint32_t c0 = c4[k] & 0xFFu;
+      if (c0 != 0u && c4[k] == c0 * 0x01010101u) {
+        // four of one class: their places follow one another
+        const int32_t v = (int32_t)v0[k];
+        const int4 four = make_int4(v, v + 1, v + 2, v + 3);
+        __builtin_memcpy(out[c0] + (pos[k][0] & 0xFFFFu), &four, sizeof(four));
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (cq[k][q] >= 0)
-          lists.p[cq[k][q]][base[cq[k][q]] + pos[k][q]] = (int32_t)(v0[k] + q);
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t c = (c4[k] >> (8 * q)) & 0xFFu;
+          if (c) out[c][pos[k][q >> 1] >> (16 * (q & 1)) & 0xFFFFu] = (int32_t)(v0[k] + q);
+        }
+      }
+    }
     __syncthreads();
   }
   // one atomic per workgroup for the processed count (cnt is free after the
@@ -748,12 +776,18 @@ __global__ __launch_bounds__(kBT) void k_frontier(int64_t n_all, int64_t n_later
 }
 
 hipError_t launch_frontier(int64_t n, int64_t n_later, uint8_t* F, const uint8_t* cls,
-                           int32_t* const* lists, uint8_t* chg_clear, DevStats* st, int grid,
-                           hipStream_t s) {
+                           int32_t* const* lists, uint8_t* chg_clear, DevStats* st, hipStream_t s) {
   ListPtrs lp;
   for (int q = 0; q < kNumClasses; ++q) lp.p[q] = lists[q];
-  hipLaunchKernelGGL(k_frontier, dim3(grid), dim3(kBT), 0, s, n, n_later, F, cls, lp, chg_clear,
-                     st);
+  if (n <= kFrontierOneWord)
+    hipLaunchKernelGGL(k_frontier<1>, dim3(grid_for(n, kBT * 4, 2048)), dim3(kBT), 0, s, n,
+                       n_later, F, cls, lp, chg_clear, st);
+  else if (n <= kFrontierFourWords)
+    hipLaunchKernelGGL(k_frontier<4>, dim3(grid_for(n, kBT * 16, 2048)), dim3(kBT), 0, s, n,
+                       n_later, F, cls, lp, chg_clear, st);
+  else
+    hipLaunchKernelGGL(k_frontier<8>, dim3(grid_for(n, kBT * 32, 2048)), dim3(kBT), 0, s, n,
+                       n_later, F, cls, lp, chg_clear, st);
   return hipGetLastError();
 }
 
