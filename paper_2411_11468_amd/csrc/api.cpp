@@ -98,8 +98,7 @@ struct lpa_graph_s {
   void* tv_gvals = nullptr;           // hubs' table values of that width
   unsigned long long* tv_vmax = nullptr;
   uint32_t* tv_nl = nullptr;
-  int hub_acc_grid = 1, hub_fin_grid = 1, pull_grid = 1,
-      push_grid = 1, hub_direct_grid = 1;
+  int hub_acc_grid = 1, hub_fin_grid = 1, push_grid = 1, hub_direct_grid = 1;
   int32_t* lab_in = nullptr;  // labels given by the caller, staged
   int32_t* Cn = nullptr;
   uint8_t* chg = nullptr;
@@ -747,7 +746,6 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
     }
   }
   G->learn_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 2048));
-  G->pull_grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 31) / 32, 256 * 8));
   G->push_grid = 256 * 8;
 
   // hubs: sorted ids, global table offsets (p1 = nextPow2(D) - 1 slots each),
@@ -1027,7 +1025,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   }
   if (lpa_status e = mark(kKidPull)) return e;
   LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
-                            g->st, g->pull_grid, s));
+                            g->st, s));
   if (g->H > 0) {
     if (lpa_status e = mark(kKidPullHubs)) return e;
     LPA_HIP(launch_pull_hubs(g->off64, g->off, g->tgt, g->hub_vid, g->H, g->chg_bits, g->F,
@@ -1651,7 +1649,7 @@ lpa_status lpa_get_flags(lpa_graph g, uint8_t* flags) {
     LPA_HIP(launch_publish(g->st, g->chg, g->n_active, nullptr, nullptr, g->chg_bits, false, true,
                            s));
     LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
-                              g->st, g->pull_grid, s));
+                              g->st, s));
     if (g->H > 0)
       LPA_HIP(launch_pull_hubs(g->off64, g->off, g->tgt, g->hub_vid, g->H, g->chg_bits, g->F,
                                g->st, s));

@@ -1222,14 +1222,12 @@ hipError_t launch_push_hubs(bool off64, const HubArgs& a, int grid, hipStream_t 
   return hipGetLastError();
 }
 
-// pull: non-hub rows with 8 lanes per vertex, 8 entries per step; hub rows
-// with one workgroup per hub.
+// pull: non-hub rows with one lane, then 16 lanes per vertex; hub rows with one
+// workgroup per hub.
 namespace {
-__device__ __forceinline__ uint32_t or8(uint32_t x) {
-  x |= dpp32<0xB1, 0xF, 0xF, false>(x);   // quad_perm [1,0,3,2]
-  x |= dpp32<0x4E, 0xF, 0xF, false>(x);   // quad_perm [2,3,0,1]
-  x |= dpp32<0x141, 0xF, 0xF, false>(x);  // row_half_mirror
-  return x;
+// whether x holds on any lane of the 16-lane group g = lane / 16
+__device__ __forceinline__ bool group_any16(bool x, int g) {
+  return ((uint32_t)(__ballot(x) >> (16 * g)) & 0xFFFFu) != 0u;
 }
 }  // namespace
 
@@ -1301,83 +1299,155 @@ __device__ __forceinline__ bool chg_bit(const uint32_t* bits, int32_t j) {
   return (bits[j >> 5] >> (j & 31)) & 1u;
 }
 
-template <typename OffT>
-__global__ __launch_bounds__(kBT) void k_pull_flags(const OffT* off, const int32_t* tgt,
-                                                    int64_t n, const uint8_t* cls,
-                                                    const uint32_t* chg, uint8_t* F,
-                                                    DevStats* st) {
+// tgt[p .. p + 3]: one 16-byte load, or entry by entry where the row is one of
+// the array's first few and p is negative (entries before `lo`, the row's
+// start, are read as -1).  In a row of fewer entries the load takes in the end
+// of the row before; those entries are not looked at.
+__device__ __forceinline__ int4 load_four(const int32_t* tgt, int64_t p, int64_t lo) {
+  int4 j;
+  if (p >= 0) {
+    __builtin_memcpy(&j, tgt + p, sizeof(j));
+  } else {
+    j.x = -1;
+    j.y = p + 1 >= lo ? tgt[p + 1] : -1;
+    j.z = p + 2 >= lo ? tgt[p + 2] : -1;
+    j.w = p + 3 >= lo ? tgt[p + 3] : -1;
+  }
+  return j;
+}
+
+// WORDS > 0: the bits are copied to LDS first (n <= 32 WORDS), where a lookup
+// costs a few cycles a wave instead of the address unit's 64 (LFR, 1 M
+// vertices, 20 M entries: 87 -> 61 us in the longest pull of a run).  From
+// memory it is bound by the latency of offset, entries and bits one after the
+// other, so by the waves in flight: eight per SIMD, the whole grid resident at
+// once (8192 x 8192 lattice: 0.41 ms per launch; with the last four entries
+// read one by one 0.43, with two vertices per lane and six waves 0.48).
+template <typename OffT, int BT, int WORDS>
+__global__ __launch_bounds__(BT, WORDS ? 1 : 8) void k_pull_flags(const OffT* off, const int32_t* tgt,
+                                                   int64_t n, const uint8_t* cls,
+                                                   const uint32_t* bits, uint8_t* F,
+                                                   DevStats* st) {
   if (st->stop || st->pull_mode != 1u) return;
+  __shared__ uint32_t copy[WORDS ? WORDS : 1];
+  const int64_t words = (n + 31) / 32;
+  if constexpr (WORDS > 0) {
+    for (int w = threadIdx.x; w < (int)words; w += BT) copy[w] = bits[w];
+    __syncthreads();
+  }
+  auto changed = [&](int32_t j) {
+    if constexpr (WORDS > 0) return chg_bit(copy, j);
+    else return chg_bit(bits, j);
+  };
   const int lane = threadIdx.x & 63;
-  const int k = lane & 7;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int g = lane >> 4, k = lane & 15;
+  const int64_t wave = (blockIdx.x * (int64_t)BT + threadIdx.x) >> 6;
+  const int64_t nwaves = ((int64_t)gridDim.x * BT) >> 6;
   unsigned long long scanned = 0;
   constexpr int kFirst = 4;  // entries a lane checks for its own vertex
+  constexpr int kRows = WORDS > 0 ? 4 : 2;  // unresolved rows per lane group and round
   // one vertex per lane for its last kFirst entries (most rows find a
-  // changed neighbour there); the rows left unresolved are then scanned
-  // eight lanes per row, up to eight rows at a time.  Rows are read from
-  // their end: with the internal order's rows sorted by target, the last
-  // entries are the lowest-degree neighbours, which are the ones that still
-  // change late in a run (from the start: 0.58 -> 0.89 ms per launch on
-  // R-MAT 26)
+  // changed neighbour there); the rows left unresolved are then scanned by 16
+  // lanes each, kRows x 4 rows at a time with their loads in flight together:
+  // 16 entries, then 64 a step.  Rows are read from their end: with the
+  // internal order's rows sorted by target, the last entries are the
+  // lowest-degree neighbours, which are the ones that still change late in a
+  // run (from the start: 0.58 -> 0.89 ms per launch on R-MAT 26)
   for (int64_t base = wave * 64; base < n; base += nwaves * 64) {
     const int64_t v = base + lane;
-    const bool valid = v < n && cls[v] != kClassHub;
-    int64_t o = 0, d = 0;
-    if (valid) {
-      o = (int64_t)off[v];
-      d = (int64_t)off[v + 1] - o;
+    OffT o = 0;
+    int32_t d = 0;  // a hub's row is scanned by k_pull_hubs
+    if (v < n && cls[v] != kClassHub) {
+      o = off[v];
+      d = (int32_t)(off[v + 1] - o);
     }
-    int32_t j[kFirst];
-#pragma unroll
-    for (int u = 0; u < kFirst; ++u) j[u] = (u < d) ? tgt[o + d - 1 - u] : -1;
+    int4 j = make_int4(0, 0, 0, 0);
+    if (d > 0) j = load_four(tgt, (int64_t)o + d - kFirst, (int64_t)o);
+    const int32_t e[kFirst] = {j.w, j.z, j.y, j.x};
     bool found = false;
 #pragma unroll
     for (int u = 0; u < kFirst; ++u) {
-      if (j[u] >= 0 && !found) {
+      if (u < d && !found) {
         ++scanned;
-        found = chg_bit(chg, j[u]);
+        found = changed(e[u]);
       }
     }
     if (found) F[v] = 1;
     unsigned long long pend = __ballot(!found && d > kFirst);
     while (pend) {
-      // the g-th pending row of this round goes to lane group g
-      const int g = lane >> 3;
-      unsigned long long m = pend;
-      for (int q = 0; q < g && m; ++q) m &= m - 1;
-      const int src = m ? __ffsll((long long)m) - 1 : -1;
-      const int sl = src < 0 ? 0 : src;
-      const int64_t pv = base + sl;
-      const int64_t po = __shfl(o, sl), pd = __shfl(d, sl);
-      bool done = src < 0;  // the same for the 8 lanes of a group
-      bool hitany = false;
-      for (int64_t t = kFirst; __any(!done); t += 8) {
-        uint32_t hit = 0;
-        const int64_t e = t + k;
-        if (!done && e < pd) {
-          hit = chg_bit(chg, tgt[po + pd - 1 - e]) ? 1u : 0u;
+      // the next kRows x 4 pending rows, dealt out over the lane groups
+      int src[kRows];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) src[r] = -1;
+#pragma unroll
+      for (int q = 0; q < kRows * 4; ++q) {
+        const int sq = pend ? __ffsll((long long)pend) - 1 : -1;
+        pend &= pend - 1;
+        if (g == (q & 3)) src[q >> 2] = sq;
+      }
+      OffT po[kRows];
+      int32_t left[kRows];  // entries of the row not scanned; 0: row done
+      bool hit[kRows];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        const int sl = src[r] < 0 ? 0 : src[r];
+        po[r] = __shfl(o, sl);
+        const int32_t pd = __shfl(d, sl);  // by all lanes, as it reads any
+        left[r] = src[r] < 0 ? 0 : pd - kFirst;
+      }
+      int32_t j[kRows];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        j[r] = k < left[r] ? tgt[(int64_t)po[r] + left[r] - 1 - k] : -1;
+      bool more = false;
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        bool h = false;
+        if (j[r] >= 0) {
+          h = changed(j[r]);
           ++scanned;
         }
-        hit = or8(hit);
-        if (!done) {
-          if (hit) { hitany = true; done = true; }
-          else if (t + 8 >= pd) done = true;
+        hit[r] = group_any16(h, g);
+        left[r] = hit[r] || left[r] <= 16 ? 0 : left[r] - 16;
+        more |= left[r] != 0;
+      }
+      while (__any(more)) {
+        int4 f[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+          if (4 * k < left[r])
+            f[r] = load_four(tgt, (int64_t)po[r] + left[r] - 4 * k - 4, (int64_t)po[r]);
+        more = false;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+          bool h = false;
+          const int32_t in = left[r] - 4 * k;  // entries of the row in f[r]
+          if (in > 0) {
+            h = changed(f[r].w);
+            if (in > 1) h |= changed(f[r].z);
+            if (in > 2) h |= changed(f[r].y);
+            if (in > 3) h |= changed(f[r].x);
+            scanned += in < 4 ? in : 4;
+          }
+          h = group_any16(h, g);
+          hit[r] |= h;
+          left[r] = h || left[r] <= 64 ? 0 : left[r] - 64;
+          more |= left[r] != 0;
         }
       }
-      if (hitany && k == 0) F[pv] = 1;
-      // drop the (up to eight) rows taken this round
-      for (int q = 0; q < 8 && pend; ++q) pend &= pend - 1;
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+        if (hit[r] && k == 0) F[base + src[r]] = 1;
     }
   }
   // one atomic per workgroup
-  __shared__ unsigned long long ws[kBT / 64];
+  __shared__ unsigned long long ws[BT / 64];
   for (int ofs = 32; ofs > 0; ofs >>= 1) scanned += __shfl_xor(scanned, ofs);
   if (lane == 0) ws[threadIdx.x >> 6] = scanned;
   __syncthreads();
   if (threadIdx.x == 0) {
     unsigned long long t = 0;
-    for (int q = 0; q < kBT / 64; ++q) t += ws[q];
+    for (int q = 0; q < BT / 64; ++q) t += ws[q];
     if (t) atomicAdd(&st->pull_scanned, t);
   }
 }
@@ -1425,15 +1495,32 @@ __global__ __launch_bounds__(kBT) void k_pull_hubs(const OffT* off, const int32_
   }
 }
 
+// Where the bits go: graphs of up to 2^18 vertices keep them in 32 KB of LDS,
+// four workgroups and more to a CU; of up to 1.2 M in 152 KB, one workgroup
+// of 16 waves to a CU; larger graphs read them from memory.
+constexpr int kPullSmallWords = 8192, kPullBigWords = 38912;
+
+template <typename OffT>
+static void pull_flags(const void* off, const int32_t* tgt, int64_t n, const uint8_t* cls,
+                       const uint32_t* bits, uint8_t* F, DevStats* st, hipStream_t s) {
+  const OffT* o = (const OffT*)off;
+  const int64_t words = (n + 31) / 32;
+  if (words <= kPullSmallWords)
+    hipLaunchKernelGGL((k_pull_flags<OffT, 256, kPullSmallWords>), dim3(grid_for(n, 256, 1024)),
+                       dim3(256), 0, s, o, tgt, n, cls, bits, F, st);
+  else if (words <= kPullBigWords)
+    hipLaunchKernelGGL((k_pull_flags<OffT, 1024, kPullBigWords>), dim3(grid_for(n, 1024, 256)),
+                       dim3(1024), 0, s, o, tgt, n, cls, bits, F, st);
+  else
+    hipLaunchKernelGGL((k_pull_flags<OffT, 256, 0>), dim3(grid_for(n, 256, 2048)), dim3(256), 0, s,
+                       o, tgt, n, cls, bits, F, st);
+}
+
 hipError_t launch_pull_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
                              const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F,
-                             DevStats* st, int grid, hipStream_t s) {
-  if (off64)
-    hipLaunchKernelGGL(k_pull_flags<int64_t>, dim3(grid), dim3(kBT), 0, s,
-                       (const int64_t*)off, tgt, n, cls, chg_bits, F, st);
-  else
-    hipLaunchKernelGGL(k_pull_flags<int32_t>, dim3(grid), dim3(kBT), 0, s,
-                       (const int32_t*)off, tgt, n, cls, chg_bits, F, st);
+                             DevStats* st, hipStream_t s) {
+  if (off64) pull_flags<int64_t>(off, tgt, n, cls, chg_bits, F, st, s);
+  else pull_flags<int32_t>(off, tgt, n, cls, chg_bits, F, st, s);
   return hipGetLastError();
 }
 

@@ -346,7 +346,7 @@ hipError_t launch_publish(const DevStats* st, const uint8_t* chg, int64_t n, con
 // Pulls the flags, from the bits that launch_publish packed.
 hipError_t launch_pull_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
                              const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F,
-                             DevStats* st, int grid, hipStream_t s);
+                             DevStats* st, hipStream_t s);
 hipError_t launch_push_lists(bool off64, const void* off, const int32_t* tgt,
                              int32_t* const* lists, const uint8_t* chg, uint8_t* F,
                              DevStats* st, int grid, hipStream_t s);
