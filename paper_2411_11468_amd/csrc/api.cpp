@@ -964,7 +964,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     LPA_HIP(launch_hub_spill(g->off64, ha, g->hub_fin_grid, s));
   }
   SweepArgs a;
-  a.off = g->off; a.tgt = g->tgt; a.w = g->w; a.C = g->C; a.Cn = g->Cn; a.F = g->F;
+  a.off = g->off; a.tgt = g->tgt; a.m = g->m; a.w = g->w; a.C = g->C; a.Cn = g->Cn; a.F = g->F;
   a.chg = g->chg; a.st = g->st;
   a.uoff = g->uoff; a.utgt = g->utgt; a.uw = g->uw; a.inv = g->inv; a.ctgt = g->ctgt;
   a.async_mode = async_mode;

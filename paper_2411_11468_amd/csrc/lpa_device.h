@@ -599,4 +599,36 @@ __device__ __forceinline__ float edge_weight(const float* w, int64_t e) {
   return w ? __builtin_nontemporal_load(&w[e]) : 1.0f;
 }
 
+// The at most four entries of a row at o, in arrays of m entries; `none` and
+// weight 0 past the row's end.  One 16-byte load per array (of 4-byte
+// alignment): read entry by entry, 64 lanes on neighbouring rows cost the
+// address unit four times 64 lanes 16 bytes apart.  The array's last rows,
+// where the load would reach past its end, are read entry by entry.
+typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void row_of_four(const int32_t* tgt, const float* w, int64_t m,
+                                            int64_t o, int64_t d, int32_t none, int32_t (&j)[4],
+                                            float (&wt)[4]) {
+  i32x4 t = {none, none, none, none};
+  f32x4u f = {1.0f, 1.0f, 1.0f, 1.0f};
+  if (d > 0) {
+    if (o + 4 <= m) {
+      t = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(tgt + o));
+      if (w) f = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(w + o));
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u < d) {
+          t[u] = tgt[o + u];
+          if (w) f[u] = w[o + u];
+        }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    j[u] = u < d ? t[u] : none;
+    wt[u] = u < d ? f[u] : 0.0f;
+  }
+}
+
 }  // namespace lpa

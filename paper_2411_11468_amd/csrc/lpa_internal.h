@@ -124,6 +124,7 @@ struct ProbeCfg {
 struct SweepArgs {
   const void* off;        // int32_t* or int64_t* (kernel template picks)
   const int32_t* tgt;
+  int64_t m;              // entries of tgt (and of w)
   const float* w;         // NULL: unit weights
   int32_t* C;             // labels (read; written in place in async mode)
   int32_t* Cn;            // deterministic mode: label after this iteration,

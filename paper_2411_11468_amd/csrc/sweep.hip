@@ -447,12 +447,7 @@ __global__ __launch_bounds__(256) void k_sweep_lane4(SweepArgs a) {
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool has = u < d[r];
-        j[r][u] = has ? __builtin_nontemporal_load(&a.tgt[o[r] + u]) : v[r];
-        wt[r][u] = has ? edge_weight(a.w, o[r] + u) : 0.0f;
-      }
+      row_of_four(a.tgt, a.w, a.m, o[r], d[r], v[r], j[r], wt[r]);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
@@ -1788,15 +1783,11 @@ __global__ __launch_bounds__(BT) void k_sweep_direct(SweepArgs a) {
     constexpr int UD = 4;
     int64_t e = k;
     if constexpr (G == 1) {
-      // rows of at most 4 entries (the smallest class): one predicated load
-      // per slot, all in flight at once
+      // rows of at most 4 entries (the smallest class)
       int32_t jr[4];
       float wj[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        jr[u] = (u < d) ? __builtin_nontemporal_load(&rt[o + u]) : self;
-        wj[u] = (u < d) ? edge_weight(rw, o + u) : 0.0f;
-      }
+      static_assert(INT, "rt has a.m entries");
+      row_of_four(rt, rw, a.m, o, d, self, jr, wj);
 #pragma unroll
       for (int u = 0; u < 4; ++u) take(jr[u], wj[u]);
       e = d;
