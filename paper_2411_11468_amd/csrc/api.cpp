@@ -565,14 +565,18 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
   G->uw = G->w;
 
   // counters
-  if (lpa_status e = G->dalloc(&G->st, 1)) return e;
+  {
+    DevState* state = nullptr;
+    if (lpa_status e = G->dalloc(&state, 1)) return e;
+    G->st = &state->st;
+  }
   {
     void* h = nullptr;
     LPA_HIP(hipHostMalloc(&h, sizeof(DevStats), hipHostMallocDefault));
     G->st_host = static_cast<DevStats*>(h);
   }
   LPA_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(G->st), 0u,
-                          sizeof(DevStats) / sizeof(uint32_t), s));
+                          sizeof(DevState) / sizeof(uint32_t), s));
   if (g->validate) {
     LPA_HIP(launch_validate(G->off64, G->off, G->tgt, G->w, n, m, G->st, s));
     LPA_HIP(hipMemcpyAsync(G->st_host, G->st, sizeof(DevStats), hipMemcpyDeviceToHost, s));
@@ -927,7 +931,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     if (lpa_status e = mark(kKidQueueStep)) return e;
     LPA_HIP(launch_queue_step(q, s));
     if (lpa_status e = mark(-1)) return e;
-    LPA_HIP(launch_iter_end(g->st, g->hist, n, s));
+    LPA_HIP(launch_iter_end(g->st, g->hist, n, true, s));
     return LPA_OK;
   }
   const int tv = g->tun.table_values;  // 0, or the ablation kernels' value bits
@@ -1040,7 +1044,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     LPA_HIP(launch_trace_label(g->st, g->chg, rc.tr, s));
   }
   if (lpa_status e = mark(-1)) return e;
-  LPA_HIP(launch_iter_end(g->st, g->hist, n, s));
+  LPA_HIP(launch_iter_end(g->st, g->hist, n, false, s));
   return LPA_OK;
 }
 

@@ -65,8 +65,8 @@ hipError_t launch_init(int64_t n, const int32_t* init, const int32_t* inv, int32
 __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
                             int graphs, LearnParams lp) {
   uint32_t* w = reinterpret_cast<uint32_t*>(st);
-  for (uint32_t i = threadIdx.x; i < sizeof(DevStats) / sizeof(uint32_t); i += blockDim.x)
-    w[i] = 0u;
+  for (uint32_t i = threadIdx.x; i < sizeof(DevState) / sizeof(uint32_t); i += blockDim.x)
+    w[i] = 0u;  // the counters and their copies
   __syncthreads();
   if (threadIdx.x == 0) {
     st->tol = tol;
@@ -93,7 +93,7 @@ __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batc
 
 hipError_t launch_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
                             int graphs, const LearnParams& lp, hipStream_t s) {
-  hipLaunchKernelGGL(k_run_begin, dim3(1), dim3(256), 0, s, st, tol, cap, rho, batched, graphs,
+  hipLaunchKernelGGL(k_run_begin, dim3(1), dim3(1024), 0, s, st, tol, cap, rho, batched, graphs,
                      lp);
   return hipGetLastError();
 }
@@ -110,8 +110,22 @@ hipError_t launch_arm_flags(uint8_t* F, int64_t n, const DevStats* st, hipStream
   return hipGetLastError();
 }
 
-__global__ void k_iter_end(DevStats* st, DevIterStats* hist, int64_t n) {
-  if (threadIdx.x != 0 || blockIdx.x != 0 || st->stop) return;
+// FOLD: no k_flag_decide has added up the counters' copies (a work-queue run);
+// otherwise only the pull kernels have added to them since.
+template <bool FOLD>
+__global__ __launch_bounds__(1024) void k_iter_end(DevStats* st, DevIterStats* hist, int64_t n) {
+  if (st->stop) return;
+  if constexpr (FOLD) {
+    fold_stats(st);
+  } else if (threadIdx.x < kStatSlots) {
+    unsigned long long* p =
+        &reinterpret_cast<DevState*>(st)->slot[threadIdx.x][kStatPullScanned];
+    unsigned long long t = *p;
+    *p = 0ull;
+    for (int ofs = kStatSlots / 2; ofs > 0; ofs >>= 1) t += __shfl_xor(t, ofs, kStatSlots);
+    if (threadIdx.x == 0) st->pull_scanned = t;
+  }
+  if (threadIdx.x != 0) return;
   unsigned long long changed = 0, edges = 0;
   for (int c = 0; c < kNumClasses; ++c) {
     changed += st->changed[c];
@@ -146,8 +160,10 @@ __global__ void k_iter_end(DevStats* st, DevIterStats* hist, int64_t n) {
   st->stop = (stop || l + 1 >= st->cap) ? 1 : 0;
 }
 
-hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_iter_end, dim3(1), dim3(64), 0, s, st, hist, n);
+hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, bool fold,
+                           hipStream_t s) {
+  if (fold) hipLaunchKernelGGL(k_iter_end<true>, dim3(1), dim3(1024), 0, s, st, hist, n);
+  else hipLaunchKernelGGL(k_iter_end<false>, dim3(1), dim3(64), 0, s, st, hist, n);
   return hipGetLastError();
 }
 
@@ -504,7 +520,7 @@ __global__ __launch_bounds__(1024) void k_hub_plan(HubArgs a, int32_t* C, uint8_
     run_s = 0; run_b = 0; nproc = 0;
   }
   if (tid < kNumClasses) {
-    st->active[tid] = 0;
+    st->active[tid].n = 0;
     st->edges[tid] = 0;
     st->changed[tid] = 0;
     st->flagw[tid] = 0;
@@ -742,7 +758,7 @@ __global__ __launch_bounds__(kBT) void k_frontier(int64_t n_all, int64_t n_later
     }
     __syncthreads();
     if (tid < kNumClasses && cnt[tid])
-      out[tid] = lists.p[tid] + atomicAdd(&st->active[tid], cnt[tid]);
+      out[tid] = lists.p[tid] + atomicAdd(&st->active[tid].n, cnt[tid]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kWords; ++k) {
@@ -771,7 +787,7 @@ __global__ __launch_bounds__(kBT) void k_frontier(int64_t n_all, int64_t n_later
   if (tid == 0) {
     uint32_t t = 0;
     for (int q = 0; q < kBT / 64; ++q) t += cnt[q];
-    if (t) atomicAdd(&st->processed, (unsigned long long)t);
+    if (t) atomicAdd(&stat_slot(st)[kStatProcessed], (unsigned long long)t);
   }
 }
 
@@ -952,7 +968,7 @@ __global__ __launch_bounds__(kLearnWaves * 64) void k_frontier_learned(
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
     __syncthreads();
-    if (tid < kNumClasses) cbase[tid] = cnt[tid] ? atomicAdd(&st->active[tid], cnt[tid]) : 0u;
+    if (tid < kNumClasses) cbase[tid] = cnt[tid] ? atomicAdd(&st->active[tid].n, cnt[tid]) : 0u;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kLearnChunks; ++q)
@@ -977,9 +993,10 @@ __global__ __launch_bounds__(kLearnWaves * 64) void k_frontier_learned(
       ss += cnt[kLearnWaves + q];
       sn += cbase[q];
     }
-    if (sp) atomicAdd(&st->processed, (unsigned long long)sp);
-    if (ss) atomicAdd(&st->skipped, (unsigned long long)ss);
-    if (sn) atomicAdd(&st->npred, (unsigned long long)sn);
+    unsigned long long* slot = stat_slot(st);
+    if (sp) atomicAdd(&slot[kStatProcessed], (unsigned long long)sp);
+    if (ss) atomicAdd(&slot[kStatSkipped], (unsigned long long)ss);
+    if (sn) atomicAdd(&slot[kStatNpred], (unsigned long long)sn);
   }
 }
 
@@ -1025,8 +1042,11 @@ hipError_t launch_trace_label(const DevStats* st, const uint8_t* chg, const Trac
 // k_flag_decide picks pull when the changed rows hold at least 1/pdiv of the
 // CSR entries (lpa_tuning.pull_divisor, default 16), push otherwise; the
 // kernels of the other way return at once.
-__global__ void k_flag_decide(DevStats* st, int64_t m, int64_t n, int force, int pdiv) {
-  if (threadIdx.x != 0 || blockIdx.x != 0 || st->stop) return;
+__global__ __launch_bounds__(1024) void k_flag_decide(DevStats* st, int64_t m, int64_t n, int force,
+                                                      int pdiv) {
+  if (st->stop) return;
+  fold_stats(st);
+  if (threadIdx.x != 0) return;
   unsigned long long fw = 0, changed = 0;
   for (int c = 0; c < kNumClasses; ++c) {
     fw += st->flagw[c];
@@ -1051,7 +1071,7 @@ __global__ void k_flag_decide(DevStats* st, int64_t m, int64_t n, int force, int
 
 hipError_t launch_flag_decide(DevStats* st, int64_t m, int64_t n, int force, int pdiv,
                               hipStream_t s) {
-  hipLaunchKernelGGL(k_flag_decide, dim3(1), dim3(64), 0, s, st, m, n, force, pdiv);
+  hipLaunchKernelGGL(k_flag_decide, dim3(1), dim3(1024), 0, s, st, m, n, force, pdiv);
   return hipGetLastError();
 }
 
@@ -1448,7 +1468,7 @@ __global__ __launch_bounds__(BT, WORDS ? 1 : 8) void k_pull_flags(const OffT* of
   if (threadIdx.x == 0) {
     unsigned long long t = 0;
     for (int q = 0; q < BT / 64; ++q) t += ws[q];
-    if (t) atomicAdd(&st->pull_scanned, t);
+    if (t) atomicAdd(&stat_slot(st)[kStatPullScanned], t);
   }
 }
 
@@ -1491,7 +1511,7 @@ __global__ __launch_bounds__(kBT) void k_pull_hubs(const OffT* off, const int32_
   if (threadIdx.x == 0) {
     unsigned long long t = 0;
     for (int q = 0; q < kBT / 64; ++q) t += ws[q];
-    if (t) atomicAdd(&st->pull_scanned, t);
+    if (t) atomicAdd(&stat_slot(st)[kStatPullScanned], t);
   }
 }
 

@@ -265,6 +265,45 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
 }
 
 
+// The copy of the run's counters that this workgroup adds to.
+__device__ __forceinline__ unsigned long long* stat_slot(DevStats* st) {
+  return reinterpret_cast<DevState*>(st)->slot[blockIdx.x % kStatSlots];
+}
+
+// All copies added to the run's counters and cleared, by a workgroup of 1024
+// threads (every thread calls it; the sums are visible to all on return).
+__device__ __forceinline__ void fold_stats(DevStats* st) {
+  static_assert(kStatSlots == 32 && kStatWords == 64, "two slots per wave of the workgroup");
+  __shared__ unsigned long long part[16][kStatWords];
+  unsigned long long(*slot)[kStatWords] = reinterpret_cast<DevState*>(st)->slot;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const unsigned long long a = slot[w][lane], b = slot[w + 16][lane];
+  if (a) slot[w][lane] = 0ull;
+  if (b) slot[w + 16][lane] = 0ull;
+  part[w][lane] = a + b;
+  __syncthreads();
+  if (w == 0) {
+    unsigned long long t = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) t += part[q][lane];
+    if (t) {
+      if (lane < 3 * kNumClasses) {
+        const int c = lane / 3, k = lane - 3 * c;
+        if (k == kStatEdges) st->edges[c] += t;
+        else if (k == kStatChanged) st->changed[c] += t;
+        else st->flagw[c] += t;
+      } else if (lane == kStatProcessed) st->processed += t;
+      else if (lane == kStatSkipped) st->skipped += t;
+      else if (lane == kStatNpred) st->npred += t;
+      else if (lane == kStatFneg) st->fneg += t;
+      else if (lane == kStatHubPairs) st->hub_pairs += t;
+      else if (lane == kStatPullScanned) st->pull_scanned += t;
+    }
+  }
+  __syncthreads();
+}
+
+
 // Adds a workgroup's counters to the iteration's: sums over each wave, then
 // over the waves in LDS, then one device atomic per counter and workgroup
 // (atomics on one address from every wave of a full grid serialise at the
@@ -293,9 +332,10 @@ __device__ __forceinline__ void flush_stats(unsigned long long edges, uint32_t c
       tc += fs_c[q];
       tf += fs_f[q];
     }
-    if (te) atomicAdd(&st->edges[cls], te);
-    if (tc) atomicAdd(&st->changed[cls], (unsigned long long)tc);
-    if (tf) atomicAdd(&st->flagw[cls], tf);
+    unsigned long long* slot = stat_slot(st) + 3 * cls;
+    if (te) atomicAdd(&slot[kStatEdges], te);
+    if (tc) atomicAdd(&slot[kStatChanged], (unsigned long long)tc);
+    if (tf) atomicAdd(&slot[kStatFlagw], tf);
   }
 }
 

@@ -18,6 +18,13 @@ constexpr int kClassHub = 9;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;  // empty hashtable key
 constexpr int kXcds = 8;                  // accelerator complex dies of an MI355X
 
+// A counter on a cache line of its own: atomics on one line, whichever of its
+// words they go to, follow one another (about 8-12 ns each).
+struct alignas(128) LineCount {
+  unsigned int n;
+  __host__ __device__ operator unsigned int() const { return n; }
+};
+
 // Per-iteration device counters.  Reset at the start of every iteration by
 // the hub-plan kernel, read back by the host after the iteration.
 struct DevStats {
@@ -35,7 +42,7 @@ struct DevStats {
                                                 // revert decision
   unsigned long long reverted;                  // Cross-Check: changes reverted
                                                 // in this iteration
-  unsigned int active[kNumClasses];             // vertices appended per class
+  LineCount active[kNumClasses];                // vertices appended per class
   unsigned long long hub_pairs;                 // (label, sum) pairs the hub slices
                                                 // wrote this iteration
   unsigned int hub_items;                       // hub slices queued this iteration
@@ -78,6 +85,23 @@ struct DevStats {
   double mod_acc[4];                            // lpa_modularity_noalloc: the
                                                 // accumulators, read back with
                                                 // the counters
+};
+
+// What every workgroup of a kernel adds at its end goes to one of kStatSlots
+// copies of the counters, each on lines of its own, by workgroup number:
+// k_flag_decide (in a work-queue run k_iter_end) adds the copies up and clears
+// them.  With one copy, 2048 workgroups that end together wait 46 us for their
+// three atomics each; with 32, 3 us.
+constexpr int kStatSlots = 32;
+constexpr int kStatWords = 64;
+// words of a slot: the three counters of class c at 3 c, then
+constexpr int kStatEdges = 0, kStatChanged = 1, kStatFlagw = 2;
+constexpr int kStatProcessed = 32, kStatSkipped = 33, kStatNpred = 34, kStatFneg = 35,
+              kStatHubPairs = 36, kStatPullScanned = 37;
+static_assert(3 * kNumClasses <= kStatProcessed, "the classes' counters overlap the others");
+struct DevState {
+  DevStats st;
+  alignas(512) unsigned long long slot[kStatSlots][kStatWords];
 };
 
 // Learned-skipping parameters of a run (zero: plain run).
@@ -280,7 +304,9 @@ hipError_t launch_init(int64_t n, const int32_t* init, const int32_t* inv, int32
 hipError_t launch_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
                             int graphs, const LearnParams& lp, hipStream_t s);
 hipError_t launch_arm_flags(uint8_t* F, int64_t n, const DevStats* st, hipStream_t s);
-hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, hipStream_t s);
+// fold: add up the counters' copies first (iterations without launch_flag_decide)
+hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, bool fold,
+                           hipStream_t s);
 hipError_t launch_batch_step(const BatchArgs& b, const uint8_t* chg, uint8_t* F, DevStats* st,
                              hipStream_t s);
 hipError_t launch_batch_reset(const BatchArgs& b, hipStream_t s);

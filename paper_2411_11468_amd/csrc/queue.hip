@@ -458,7 +458,7 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
   if (tid == 0) {
     unsigned long long t = 0;
     for (int x = 0; x < kQWaves; ++x) t += wp[x];
-    if (t) atomicAdd(&st->processed, t);
+    if (t) atomicAdd(&stat_slot(st)[kStatProcessed], t);
   }
 }
 
@@ -477,7 +477,7 @@ __global__ void k_queue_iter_begin(QueueArgs q) {
     st->pl = (st->rho > 0 && st->iter % st->rho == 0) ? 1 : 0;
   }
   if (tid < kNumClasses) {
-    st->active[tid] = 0;
+    st->active[tid].n = 0;
     st->edges[tid] = 0;
     st->changed[tid] = 0;
     st->flagw[tid] = 0;

@@ -126,7 +126,7 @@ __device__ __forceinline__ void flush_fneg(uint32_t fneg, DevStats* st) {
   if (threadIdx.x == 0) {
     uint32_t t = 0;
     for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += fn_w[q];
-    if (t) atomicAdd(&st->fneg, (unsigned long long)t);
+    if (t) atomicAdd(&stat_slot(st)[kStatFneg], (unsigned long long)t);
   }
 }
 
@@ -1460,8 +1460,9 @@ __global__ __launch_bounds__(BT) void k_hub_part(HubArgs a) {
   if (tid == 0) {
     unsigned long long t = 0;
     for (int q = 0; q < BT / 64; ++q) t += we[q];
-    if (t) atomicAdd(&a.st->edges[kClassHub], t);
-    if (my_pairs) atomicAdd(&a.st->hub_pairs, my_pairs);
+    unsigned long long* slot = stat_slot(a.st);
+    if (t) atomicAdd(&slot[3 * kClassHub + kStatEdges], t);
+    if (my_pairs) atomicAdd(&slot[kStatHubPairs], my_pairs);
   }
 }
 
@@ -1705,10 +1706,10 @@ __global__ __launch_bounds__(BT) void k_hub_fin(HubArgs a) {
       } else {
         a.Cn[v] = (int32_t)cstar;
       }
-      atomicAdd(&a.st->changed[kClassHub], 1ull);
+      atomicAdd(&stat_slot(a.st)[3 * kClassHub + kStatChanged], 1ull);
       a.chg[v] = 1;
     }
-    atomicAdd(&a.st->flagw[kClassHub], (unsigned long long)n);
+    atomicAdd(&stat_slot(a.st)[3 * kClassHub + kStatFlagw], (unsigned long long)n);
   }
 }
 
@@ -2022,7 +2023,7 @@ __global__ __launch_bounds__(BT) void k_hub_direct(HubArgs a) {
     if (tid == 0) my_edges += (unsigned long long)n;
   }
   const unsigned long long e = wave_sum_u64(my_edges);
-  if (lane == 0 && e) atomicAdd(&a.st->edges[kClassHub], e);
+  if (lane == 0 && e) atomicAdd(&stat_slot(a.st)[3 * kClassHub + kStatEdges], e);
 }
 
 // ---- launch wrappers ----------------------------------------------------------
