@@ -263,12 +263,14 @@ typedef enum lpa_flag_mode {
 } lpa_flag_mode;
 
 typedef enum lpa_launch {
-  /* one host round trip per iteration: per-iteration GPU time in the stats,
-   * per-kernel profile available */
+  /* kernels launched one by one, one iteration ahead of the one that runs
+   * (a host round trip per iteration with a profile, a trace or
+   * Cross-Check): per-iteration GPU time in the stats, per-kernel profile
+   * available */
   LPA_LAUNCH_EAGER = 0,
-  /* one iteration captured once as a HIP graph and replayed max_iterations
-   * times without host round trips; the kernels of iterations after the stop
-   * return at once; stats carry no per-iteration time; profile ignored */
+  /* one iteration captured once as a HIP graph and replayed, one replay
+   * ahead of the one that runs; the kernels of the one after the stop return
+   * at once; stats carry no per-iteration time; profile ignored */
   LPA_LAUNCH_GRAPH = 1
 } lpa_launch;
 

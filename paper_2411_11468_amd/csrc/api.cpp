@@ -5,10 +5,13 @@
 // deterministic mode) the label apply, reads back the iteration counters and
 // applies the stop rule.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/lpa.h"
@@ -61,6 +64,13 @@ const char* const kKidNames[kNumKids] = {
 
 struct RunCtx;
 
+// Iterations launched ahead of the last one known to have ended: with one
+// running and one queued the GPU does not wait for the host, and at most one
+// iteration is launched in vain after the stop (before, a captured run launched
+// all max_iterations, and an eager one waited for each).  LFR 1M, captured:
+// 1.91 -> 1.60 ms; a 10 000-vertex graph, eager: 0.53 -> 0.38 ms.
+constexpr int32_t kRunAhead = 1;
+
 struct lpa_graph_s {
   hipStream_t stream = nullptr;
   int64_t n = 0, m = 0;
@@ -103,7 +113,15 @@ struct lpa_graph_s {
   int32_t* Cn = nullptr;
   uint8_t* chg = nullptr;
   DevStats* st = nullptr;
-  DevStats* st_host = nullptr;
+  // pinned: the state as read back, and the progress word of k_iter_end
+  struct HostState {
+    DevStats st;
+    DevIterStats hist[kHistInline];
+    unsigned long long progress;
+  };
+  HostState* host = nullptr;
+  DevStats* st_host = nullptr;   // &host->st
+  uint32_t run_seq = 0;
   int32_t H = 0;
   int32_t* hub_vid = nullptr;
   int64_t* hub_tab = nullptr;
@@ -337,8 +355,44 @@ struct lpa_graph_s {
     DevIterStats* h = nullptr;
     if (lpa_status e = dalloc(&h, std::max(cap, 32))) return e;
     hist = h;  // the old buffer stays in dev_allocs until destroy
+    for (hipGraphExec_t& x : graph_exec) {  // captured with the old one
+      if (x) (void)hipGraphExecDestroy(x);
+      x = nullptr;
+    }
     hist_cap = std::max(cap, 32);
     return LPA_OK;
+  }
+
+  bool hist_inline() const {
+    return hist == reinterpret_cast<const DevState*>(st)->hist;
+  }
+
+  // Waits until `count` iterations of the run have ended, or the run has.
+  lpa_status wait_iterations(int32_t count, bool* stopped) {
+    *stopped = false;
+    if (count <= 0) return LPA_OK;
+    const auto t0 = std::chrono::steady_clock::now();
+    bool finished = false;  // the stream had nothing left at the last look
+    for (int spin = 1;; ++spin) {
+      const unsigned long long w = __atomic_load_n(&host->progress, __ATOMIC_RELAXED);
+      if ((uint32_t)(w >> 32) == run_seq) {
+        *stopped = ((uint32_t)w >> 31) != 0;
+        if (*stopped || (int32_t)((uint32_t)w & 0x7FFFFFFFu) >= count) return LPA_OK;
+      }
+      if (finished) return fail(LPA_ERR_HIP, "an iteration ended without its progress word");
+      if (spin % 256 != 0) continue;
+      // an error of the stream would leave the word as it is
+      const hipError_t q = hipStreamQuery(stream);
+      if (q == hipSuccess) {
+        finished = true;
+      } else {
+        (void)hipGetLastError();
+        if (q != hipErrorNotReady) return fail(LPA_ERR_HIP, hipGetErrorString(q));
+      }
+      // long iterations: the next one is queued already, so the host can doze
+      if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1))
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+    }
   }
 
   lpa_status iteration_graph(const lpa_options& o, const RunCtx& rc, hipGraphExec_t* out);
@@ -375,7 +429,7 @@ struct lpa_graph_s {
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     for (void* p : dev_allocs) (void)hipFree(p);
-    if (st_host) (void)hipHostFree(st_host);
+    if (host) (void)hipHostFree(host);
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
   }
@@ -569,11 +623,16 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
     DevState* state = nullptr;
     if (lpa_status e = G->dalloc(&state, 1)) return e;
     G->st = &state->st;
+    G->hist = state->hist;
+    G->hist_cap = kHistInline;
   }
   {
     void* h = nullptr;
-    LPA_HIP(hipHostMalloc(&h, sizeof(DevStats), hipHostMallocDefault));
-    G->st_host = static_cast<DevStats*>(h);
+    // coherent: progress is polled while kernels run
+    LPA_HIP(hipHostMalloc(&h, sizeof(lpa_graph_s::HostState), hipHostMallocCoherent));
+    G->host = static_cast<lpa_graph_s::HostState*>(h);
+    G->host->progress = 0;
+    G->st_host = &G->host->st;
   }
   LPA_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(G->st), 0u,
                           sizeof(DevState) / sizeof(uint32_t), s));
@@ -931,7 +990,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     if (lpa_status e = mark(kKidQueueStep)) return e;
     LPA_HIP(launch_queue_step(q, s));
     if (lpa_status e = mark(-1)) return e;
-    LPA_HIP(launch_iter_end(g->st, g->hist, n, true, s));
+    LPA_HIP(launch_iter_end(g->st, g->hist, n, true, &g->host->progress, s));
     return LPA_OK;
   }
   const int tv = g->tun.table_values;  // 0, or the ablation kernels' value bits
@@ -1044,7 +1103,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     LPA_HIP(launch_trace_label(g->st, g->chg, rc.tr, s));
   }
   if (lpa_status e = mark(-1)) return e;
-  LPA_HIP(launch_iter_end(g->st, g->hist, n, false, s));
+  LPA_HIP(launch_iter_end(g->st, g->hist, n, false, &g->host->progress, s));
   return LPA_OK;
 }
 
@@ -1189,7 +1248,7 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
   g->acct_feat_cmin = rc.feat_cmin;
   g->acct_feat_cmax = rc.feat_cmax;
   LPA_HIP(launch_run_begin(g->st, o.tolerance, o.max_iterations, o.pl_period, g->G > 0,
-                           g->G, lp, s));
+                           g->G, lp, ++g->run_seq, s));
   if (g->G > 0) LPA_HIP(launch_batch_reset(g->batch_args(), s));
   const int32_t* init = nullptr;
   if (o.initial_labels) {
@@ -1220,10 +1279,13 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
       !use_queue && !init && g->strict_rows && g->tun.table_values == 0;
   int32_t done = 0;
   const bool graph_mode = o.launch == LPA_LAUNCH_GRAPH && !o.profile && !trace;
+  // eager iterations that need nothing of the host in between are launched
+  // ahead of the iteration that runs, as the replays are
+  const bool ahead = !graph_mode && !o.profile && !trace && o.cc_period == 0;
   if (graph_mode) {
-    // capture one iteration on the private stream, replay it max_iterations
-    // times on the handle's stream; the kernels of iterations after the stop
-    // return at once
+    // capture one iteration on the private stream and replay it on the
+    // handle's stream; the kernels of an iteration after the stop return at
+    // once
     hipGraphExec_t exec = nullptr;
     if (lpa_status e = g->iteration_graph(o, rc, &exec)) return e;
     // iterations enqueued one by one: the table-free first sweep, and the
@@ -1236,24 +1298,27 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
                                            first_direct && l == 0))
         return e;
     }
-    for (int32_t l = l0; l < o.max_iterations; ++l) LPA_HIP(hipGraphLaunch(exec, s));
-    LPA_HIP(hipMemcpyAsync(g->st_host, g->st, sizeof(DevStats), hipMemcpyDeviceToHost, s));
-    LPA_HIP(hipStreamSynchronize(s));
-    done = g->st_host->iter;
-    const int32_t k = std::min(done, stats_cap);
-    if (k > 0) {
-      std::vector<DevIterStats> h(k);
-      LPA_HIP(hipMemcpyAsync(h.data(), g->hist, sizeof(DevIterStats) * k,
-                             hipMemcpyDeviceToHost, s));
-      LPA_HIP(hipStreamSynchronize(s));
-      for (int32_t l = 0; l < k; ++l) {
-        std::memset(&stats[l], 0, sizeof(stats[l]));
-        stats[l].iteration = h[l].iteration;
-        stats[l].pick_less = h[l].pick_less;
-        stats[l].changed = h[l].changed;
-        stats[l].processed = h[l].processed;
-        stats[l].edges_scanned = h[l].edges;
-        stats[l].skipped = (int32_t)h[l].skipped;
+    for (int32_t l = l0; l < o.max_iterations; ++l) {
+      bool stopped = false;
+      if (lpa_status e = g->wait_iterations(l - kRunAhead, &stopped)) return e;
+      if (stopped) break;
+      LPA_HIP(hipGraphLaunch(exec, s));
+    }
+  } else if (ahead) {
+    if (stats_cap > 0) {
+      if (lpa_status e = g->ensure_events(1)) return e;
+      LPA_HIP(hipEventRecord(g->ev_pool[0], s));
+    }
+    auto nomark = [](int) -> lpa_status { return LPA_OK; };
+    for (int32_t l = 0; l < o.max_iterations; ++l) {
+      bool stopped = false;
+      if (lpa_status e = g->wait_iterations(l - kRunAhead, &stopped)) return e;
+      if (stopped) break;
+      if (lpa_status e = enqueue_iteration(g, o, ctx_of(l), s, nomark, first_direct && l == 0))
+        return e;
+      if (l < stats_cap) {
+        if (lpa_status e = g->ensure_events(l + 2)) return e;
+        LPA_HIP(hipEventRecord(g->ev_pool[l + 1], s));
       }
     }
   } else {
@@ -1307,15 +1372,19 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
       if (h.stop) break;
     }
   }
+  const bool read_back = graph_mode || ahead;
+  if (read_back)
+    LPA_HIP(hipMemcpyAsync(&g->host->st, g->st,
+                           g->hist_inline() ? offsetof(lpa_graph_s::HostState, progress)
+                                            : sizeof(DevStats),
+                           hipMemcpyDeviceToHost, s));
   if (use_queue) {
+    if (read_back) LPA_HIP(hipStreamSynchronize(s));
     LPA_HIP(launch_queue_finish(g->queue_args(o.mode == LPA_MODE_ASYNC), s));
     if (g->st_host->error & 32u)
       return fail(LPA_ERR_INVALID,
                   "a row is longer than the work queue takes (the CSR changed after create)");
   }
-  if (iters_done) *iters_done = done;
-  g->flags_pending = g->st_host->flags_deferred != 0;
-  g->learned_iters = o.learned ? done : 0;
   const bool dev_out = is_device_ptr(labels);
   if (g->perm) {
     // labels in the caller's order (Cn is free once the run has ended)
@@ -1328,6 +1397,33 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
     LPA_HIP(hipMemcpyAsync(labels, g->C, sizeof(int32_t) * (size_t)n, kind, s));
   }
   LPA_HIP(hipStreamSynchronize(s));
+  if (read_back) {
+    done = g->st_host->iter;
+    const int32_t k = std::min(done, stats_cap);
+    std::vector<DevIterStats> more;
+    const DevIterStats* h = g->host->hist;
+    if (k > 0 && !g->hist_inline()) {
+      more.resize(k);
+      LPA_HIP(hipMemcpyAsync(more.data(), g->hist, sizeof(DevIterStats) * k,
+                             hipMemcpyDeviceToHost, s));
+      LPA_HIP(hipStreamSynchronize(s));
+      h = more.data();
+    }
+    for (int32_t l = 0; l < k; ++l) {
+      std::memset(&stats[l], 0, sizeof(stats[l]));
+      stats[l].iteration = h[l].iteration;
+      stats[l].pick_less = h[l].pick_less;
+      stats[l].changed = h[l].changed;
+      stats[l].processed = h[l].processed;
+      stats[l].edges_scanned = h[l].edges;
+      stats[l].skipped = (int32_t)h[l].skipped;
+      if (ahead)
+        LPA_HIP(hipEventElapsedTime(&stats[l].ms, g->ev_pool[l], g->ev_pool[l + 1]));
+    }
+  }
+  if (iters_done) *iters_done = done;
+  g->flags_pending = g->st_host->flags_deferred != 0;
+  g->learned_iters = o.learned ? done : 0;
   return LPA_OK;
 }
 

@@ -63,7 +63,7 @@ hipError_t launch_init(int64_t n, const int32_t* init, const int32_t* inv, int32
 // an iteration that is not Pick-Less with changed < tolerance * N), or, in a
 // batched run, stops when every graph has stopped.
 __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
-                            int graphs, LearnParams lp) {
+                            int graphs, LearnParams lp, unsigned int seq) {
   uint32_t* w = reinterpret_cast<uint32_t*>(st);
   for (uint32_t i = threadIdx.x; i < sizeof(DevState) / sizeof(uint32_t); i += blockDim.x)
     w[i] = 0u;  // the counters and their copies
@@ -88,13 +88,15 @@ __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batc
     st->trace_seed = lp.trace_seed;
     st->trace_cap = lp.trace_cap;
     st->cand = 1;
+    st->seq = seq;
   }
 }
 
 hipError_t launch_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
-                            int graphs, const LearnParams& lp, hipStream_t s) {
+                            int graphs, const LearnParams& lp, unsigned int seq,
+                            hipStream_t s) {
   hipLaunchKernelGGL(k_run_begin, dim3(1), dim3(1024), 0, s, st, tol, cap, rho, batched, graphs,
-                     lp);
+                     lp, seq);
   return hipGetLastError();
 }
 
@@ -113,7 +115,8 @@ hipError_t launch_arm_flags(uint8_t* F, int64_t n, const DevStats* st, hipStream
 // FOLD: no k_flag_decide has added up the counters' copies (a work-queue run);
 // otherwise only the pull kernels have added to them since.
 template <bool FOLD>
-__global__ __launch_bounds__(1024) void k_iter_end(DevStats* st, DevIterStats* hist, int64_t n) {
+__global__ __launch_bounds__(1024) void k_iter_end(DevStats* st, DevIterStats* hist, int64_t n,
+                                                   unsigned long long* progress) {
   if (st->stop) return;
   if constexpr (FOLD) {
     fold_stats(st);
@@ -157,13 +160,20 @@ __global__ __launch_bounds__(1024) void k_iter_end(DevStats* st, DevIterStats* h
   // near the stop (changed < 2 tol N) the next iteration is a plain sweep
   st->cand = (double)changed < 2.0 * st->tol * (double)n ? 1 : 0;
   st->iter = l + 1;
-  st->stop = (stop || l + 1 >= st->cap) ? 1 : 0;
+  const int ended = (stop || l + 1 >= st->cap) ? 1 : 0;
+  st->stop = ended;
+  // for the host, which launches on while iterations run: the word alone is
+  // read there, so that no other write has to be visible with it
+  __hip_atomic_store(progress,
+                     (unsigned long long)st->seq << 32 | (unsigned int)ended << 31 |
+                         (unsigned int)(l + 1),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, bool fold,
-                           hipStream_t s) {
-  if (fold) hipLaunchKernelGGL(k_iter_end<true>, dim3(1), dim3(1024), 0, s, st, hist, n);
-  else hipLaunchKernelGGL(k_iter_end<false>, dim3(1), dim3(64), 0, s, st, hist, n);
+                           unsigned long long* progress, hipStream_t s) {
+  if (fold) hipLaunchKernelGGL(k_iter_end<true>, dim3(1), dim3(1024), 0, s, st, hist, n, progress);
+  else hipLaunchKernelGGL(k_iter_end<false>, dim3(1), dim3(64), 0, s, st, hist, n, progress);
   return hipGetLastError();
 }
 

@@ -56,6 +56,7 @@ struct DevStats {
   int iter;                                     // index of the iteration being run
   int ident;                                    // the run started from labels = vertex ids
   int stop;                                     // 1: run ended, kernels return at once
+  unsigned int seq;                             // number of the run, given by the host
   int pl;                                       // Pick-Less in this iteration
   int batched;                                  // per-graph stop rule
   unsigned int graphs_left;                     // batched: graphs still running
@@ -87,6 +88,21 @@ struct DevStats {
                                                 // the counters
 };
 
+// Statistics of one iteration as recorded on the device (same layout as the
+// leading fields of lpa_iter_stats).
+struct DevIterStats {
+  int32_t iteration;
+  int32_t pick_less;
+  long long changed;
+  long long processed;
+  long long edges;
+  long long skipped;
+  long long npred;
+  long long fneg;
+  int32_t skipping;
+  int32_t fallback;
+};
+
 // What every workgroup of a kernel adds at its end goes to one of kStatSlots
 // copies of the counters, each on lines of its own, by workgroup number:
 // k_flag_decide (in a work-queue run k_iter_end) adds the copies up and clears
@@ -99,8 +115,13 @@ constexpr int kStatEdges = 0, kStatChanged = 1, kStatFlagw = 2;
 constexpr int kStatProcessed = 32, kStatSkipped = 33, kStatNpred = 34, kStatFneg = 35,
               kStatHubPairs = 36, kStatPullScanned = 37;
 static_assert(3 * kNumClasses <= kStatProcessed, "the classes' counters overlap the others");
+// Iterations whose statistics a handle has room for from the start; a run of
+// more allocates its own.
+constexpr int kHistInline = 64;
+// st and hist are read back in one copy.
 struct DevState {
   DevStats st;
+  DevIterStats hist[kHistInline];
   alignas(512) unsigned long long slot[kStatSlots][kStatWords];
 };
 
@@ -230,21 +251,6 @@ struct HubArgs {
   uint32_t wbase[kXcds + 1];
 };
 
-// Statistics of one iteration as recorded on the device (same layout as the
-// leading fields of lpa_iter_stats).
-struct DevIterStats {
-  int32_t iteration;
-  int32_t pick_less;
-  long long changed;
-  long long processed;
-  long long edges;
-  long long skipped;
-  long long npred;
-  long long fneg;
-  int32_t skipping;
-  int32_t fallback;
-};
-
 // Per-graph state of a batched run.
 struct BatchArgs {
   int32_t G;
@@ -302,11 +308,13 @@ struct QueueArgs {
 hipError_t launch_init(int64_t n, const int32_t* init, const int32_t* inv, int32_t* C,
                        uint8_t* F, DevStats* st, hipStream_t s);
 hipError_t launch_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
-                            int graphs, const LearnParams& lp, hipStream_t s);
+                            int graphs, const LearnParams& lp, unsigned int seq, hipStream_t s);
 hipError_t launch_arm_flags(uint8_t* F, int64_t n, const DevStats* st, hipStream_t s);
 // fold: add up the counters' copies first (iterations without launch_flag_decide)
+// progress: host memory that takes (run number << 32) | (stop << 31) |
+// iterations ended
 hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, bool fold,
-                           hipStream_t s);
+                           unsigned long long* progress, hipStream_t s);
 hipError_t launch_batch_step(const BatchArgs& b, const uint8_t* chg, uint8_t* F, DevStats* st,
                              hipStream_t s);
 hipError_t launch_batch_reset(const BatchArgs& b, hipStream_t s);
