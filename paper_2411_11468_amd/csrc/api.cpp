@@ -147,7 +147,6 @@ struct lpa_graph_s {
   int64_t max_items = 0, max_bitems = 0;
   int hub_reduce_grid = 8;
   double* mod_sig = nullptr;
-  double* mod_acc = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   std::vector<void*> dev_allocs;
   size_t dev_bytes = 0;          // bytes held in dev_allocs
@@ -1822,16 +1821,28 @@ static ModCsr modularity_csr(lpa_graph g, const int32_t* lab) {
   return ModCsr{g->off, g->tgt, g->w, g->Cn};
 }
 
+// Modularity of checked or unchecked labels (the kernels return at once when
+// the label check before them set the error), read back with the counters.
+static lpa_status modularity_of(lpa_graph g, const ModCsr& mc, double* sig, double* q) {
+  hipStream_t s = g->stream;
+  LPA_HIP(launch_modularity(g->off64, mc.off, mc.tgt, mc.w, g->n, g->m, mc.lab, sig,
+                            g->st->mod_acc, g->st, s));
+  LPA_HIP(hipMemcpyAsync(g->st_host, g->st, sizeof(DevStats), hipMemcpyDeviceToHost, s));
+  LPA_HIP(hipStreamSynchronize(s));
+  if (g->st_host->error & 4u) return fail(LPA_ERR_INVALID, "labels must lie in [0, N)");
+  const double* acc = g->st_host->mod_acc;
+  *q = acc[1] > 0.0 ? acc[0] / acc[1] - acc[2] / (acc[1] * acc[1]) : 0.0;
+  return LPA_OK;
+}
+
 lpa_status lpa_modularity(lpa_graph g, const int32_t* labels, double* q) {
   if (!g || !q) return fail(LPA_ERR_INVALID, "NULL argument");
   *q = 0.0;
   if (g->n == 0) return LPA_OK;
   if (!labels) return fail(LPA_ERR_INVALID, "labels is NULL");
   hipStream_t s = g->stream;
-  if (!g->mod_sig) {
+  if (!g->mod_sig)
     if (lpa_status e = g->dalloc(&g->mod_sig, g->n)) return e;
-    if (lpa_status e = g->dalloc(&g->mod_acc, 4)) return e;
-  }
   const int32_t* lab = labels;
   if (!is_device_ptr(labels)) {
     if (lpa_status e = stage_labels(g, labels, g->lab_in)) return e;
@@ -1840,25 +1851,14 @@ lpa_status lpa_modularity(lpa_graph g, const int32_t* labels, double* q) {
   LPA_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(g->st), 0u,
                           sizeof(DevStats) / sizeof(uint32_t), s));
   LPA_HIP(launch_check_labels(g->n, lab, g->st, s));
-  LPA_HIP(hipMemcpyAsync(g->st_host, g->st, sizeof(DevStats), hipMemcpyDeviceToHost, s));
-  LPA_HIP(hipStreamSynchronize(s));
-  if (g->st_host->error & 4u) return fail(LPA_ERR_INVALID, "labels must lie in [0, N)");
   const ModCsr mc = modularity_csr(g, lab);
   if (!mc.lab) return fail(LPA_ERR_HIP, "moving the labels to the internal order failed");
-  LPA_HIP(launch_modularity(g->off64, mc.off, mc.tgt, mc.w, g->n, g->m, mc.lab, g->mod_sig,
-                            g->mod_acc, s));
-  double acc[4];
-  LPA_HIP(hipMemcpyAsync(acc, g->mod_acc, sizeof(acc), hipMemcpyDeviceToHost, s));
-  LPA_HIP(hipStreamSynchronize(s));
-  const double two_m = acc[1];
-  *q = two_m > 0.0 ? acc[0] / two_m - acc[2] / (two_m * two_m) : 0.0;
-  return LPA_OK;
+  return modularity_of(g, mc, g->mod_sig, q);
 }
 
-// The same result as lpa_modularity with no device allocation: Sigma_c and
-// the accumulators in the GPU's file-scope scratch (graph.hip), host labels
-// staged through the handle's own buffer, the accumulators read back with
-// the handle's pinned counters.
+// The same result as lpa_modularity with no device allocation: Sigma_c in
+// the GPU's file-scope scratch (graph.hip), host labels
+// staged through the handle's own buffer.
 lpa_status lpa_modularity_noalloc(lpa_graph g, const int32_t* labels, double* q) {
   if (!g || !q) return fail(LPA_ERR_INVALID, "NULL argument");
   *q = 0.0;
@@ -1870,8 +1870,7 @@ lpa_status lpa_modularity_noalloc(lpa_graph g, const int32_t* labels, double* q)
   if (!labels) return fail(LPA_ERR_INVALID, "labels is NULL");
   hipStream_t s = g->stream;
   double* sig = nullptr;
-  double* acc = nullptr;
-  LPA_HIP(modularity_scratch(&sig, &acc));
+  LPA_HIP(modularity_scratch(&sig));
   const int32_t* lab = labels;
   if (!is_device_ptr(labels)) {
     if (lpa_status e = stage_labels(g, labels, g->lab_in)) return e;
@@ -1882,16 +1881,7 @@ lpa_status lpa_modularity_noalloc(lpa_graph g, const int32_t* labels, double* q)
   LPA_HIP(launch_check_labels(g->n, lab, g->st, s));
   const ModCsr mc = modularity_csr(g, lab);
   if (!mc.lab) return fail(LPA_ERR_HIP, "moving the labels to the internal order failed");
-  LPA_HIP(launch_modularity(g->off64, mc.off, mc.tgt, mc.w, g->n, g->m, mc.lab, sig, acc, s));
-  LPA_HIP(hipMemcpyAsync(g->st->mod_acc, acc, sizeof(double) * 4, hipMemcpyDeviceToDevice, s));
-  LPA_HIP(hipMemcpyAsync(g->st_host, g->st, sizeof(DevStats), hipMemcpyDeviceToHost, s));
-  LPA_HIP(hipStreamSynchronize(s));
-  if (g->st_host->error & 4u) return fail(LPA_ERR_INVALID, "labels must lie in [0, N)");
-  const double two_m = g->st_host->mod_acc[1];
-  *q = two_m > 0.0 ? g->st_host->mod_acc[0] / two_m -
-                         g->st_host->mod_acc[2] / (two_m * two_m)
-                   : 0.0;
-  return LPA_OK;
+  return modularity_of(g, mc, sig, q);
 }
 
 }  // extern "C"

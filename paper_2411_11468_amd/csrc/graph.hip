@@ -3,6 +3,7 @@
 // vertex in its own community and unprocessed), the frontier of flagged
 // vertices ("for all unprocessed i ... mark i processed"), the hub slice plan,
 // the publishing of labels and changes, and fp64 modularity (Eq. 1).
+#include <algorithm>
 #include <mutex>
 
 #include "lpa_device.h"
@@ -1569,17 +1570,29 @@ hipError_t launch_pull_hubs(bool off64, const void* off, const int32_t* tgt,
 }
 
 // ---- modularity, Eq. 1 ------------------------------------------------------
-// Community form: Q = sigma / 2m - sum_c (Sigma_c / 2m)^2.  Edge-parallel: each
-// wave owns a contiguous range of CSR entries and takes 64 consecutive ones
-// per step (coalesced target and weight loads).  The row of each entry comes
-// from the 64 row ends that follow the wave's current row, searched across
-// lanes; an entry adds its weight to 2m, to sigma when both end labels agree,
-// and to Sigma of its row's label.  Sigma is summed over each run of lanes
-// whose rows share a label, then gathered per wave in a small LDS table of
-// labels (a direct-mapped cache flushed with one fp64 atomic per label at the
-// end of the wave's range), so that a label shared by many rows -- a large
-// community -- costs few atomics on its one address.
+// Community form: Q = sigma / 2m - sum_c (Sigma_c / 2m)^2, with Sigma_c the sum
+// of the weighted degrees K_v of its vertices.  Edge-parallel: each wave owns a
+// contiguous range of CSR entries and takes 256 per step, four consecutive
+// ones a lane.  A step inside one row needs only that row's label.  Otherwise
+// the rows that start in the step write their labels to LDS at the position
+// of their first entry, and each entry takes the label at the last position
+// at or before its own (a max scan).  An entry adds its weight to sigma when
+// both end labels agree; a row adds K_v to its label once: the row length
+// for unit weights, else a segmented sum over the lanes.  The K_v are
+// gathered per workgroup in an LDS table of labels (direct-mapped; a row
+// whose slot is taken adds to memory), so that a label shared by many rows
+// costs one atomic a workgroup on its one address.  It is bound by the lines
+// that the targets' labels fetch.  The waves' ranges are short, so that the
+// waves at work together read neighbouring rows, whose targets overlap: with
+// 8192 ranges instead of up to 65536 4.04 instead of 3.08 ms on R-MAT scale
+// 24 (64 entries a step, a search and a segmented sum per entry: 3.78).  On
+// 400 000 entries 100 -> 19 us.
 namespace {
+
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  for (int ofs = 32; ofs > 0; ofs >>= 1) x += __shfl_xor(x, ofs);
+  return x;
+}
 
 __device__ __forceinline__ double block_sum_f64(double x, double* sh) {
   for (int ofs = 32; ofs > 0; ofs >>= 1) x += __shfl_xor(x, ofs);
@@ -1593,132 +1606,242 @@ __device__ __forceinline__ double block_sum_f64(double x, double* sh) {
   return t;
 }
 
-__device__ __forceinline__ int64_t shfl_i64(int64_t x, int src) {
-  const int lo = __shfl((int)(uint32_t)x, src);
-  const int hi = __shfl((int)(uint32_t)((uint64_t)x >> 32), src);
-  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+// x's maximum over the lanes up to and including this one.
+__device__ __forceinline__ int wave_scan_max(int x) {
+#pragma unroll
+  for (int ofs = 1; ofs < 64; ofs <<= 1) {
+    const int y = __shfl_up(x, ofs);
+    if ((int)(threadIdx.x & 63) >= ofs) x = x > y ? x : y;
+  }
+  return x;
 }
 
 }  // namespace
 
-constexpr int kModCache = 64;  // label slots per wave
+constexpr int kModCache = 1024;  // label slots per workgroup
+constexpr int kModStep = 256;    // entries per wave and step
+constexpr int kModWaves = 65536;  // ranges at most
 
-template <typename OffT>
+template <typename OffT, bool UNIT>
 __global__ __launch_bounds__(kBT) void k_mod_edges(const OffT* off, const int32_t* tgt,
-                                                   const float* w, int64_t n, int64_t m,
-                                                   const int32_t* C, double* sig,
-                                                   double* acc) {
+                                                   const float* w, int64_t n, int64_t m, int64_t S,
+                                                   const int32_t* C, double* sig, DevStats* st) {
   __shared__ double sh[kBT / 64];
-  __shared__ int32_t ckey_all[kBT / 64][kModCache];
-  __shared__ double cval_all[kBT / 64][kModCache];
+  __shared__ int32_t ckey[kModCache];
+  __shared__ double cval[kModCache];
+  __shared__ __align__(16) int32_t start_all[kBT / 64][kModStep];
+  if (st->error & 4u) return;  // a label out of range (k_check_labels)
+  for (int x = threadIdx.x; x < kModCache; x += kBT) {
+    ckey[x] = -1;
+    cval[x] = 0.0;
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63;
-  int32_t* ckey = ckey_all[threadIdx.x >> 6];
-  double* cval = cval_all[threadIdx.x >> 6];
-  ckey[lane] = -1;
-  cval[lane] = 0.0;
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  int32_t* start = start_all[threadIdx.x >> 6];
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  const int64_t S = (((m + nwaves - 1) / nwaves) + 63) & ~(int64_t)63;
   const int64_t e_begin = wave * S;
   const int64_t e_end = (e_begin + S < m) ? e_begin + S : m;
   double sigma = 0.0, two_m = 0.0;
-  if (e_begin < e_end) {  // uniform over the wave
-    // row of e_begin: the largest i with off[i] <= e_begin
-    int64_t lo = 0, hi = n - 1;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi + 1) >> 1;
-      if ((int64_t)off[mid] <= e_begin) lo = mid; else hi = mid - 1;
+  uint32_t same = 0;  // unit weights: sigma in whole numbers
+  auto add_degree = [&](int32_t c, double K) {
+    const int slot = (int)(((uint32_t)c * 0x9E3779B1u) >> 22);
+    int k = __hip_atomic_load(&ckey[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (k == -1) {
+      int expected = -1;
+      __hip_atomic_compare_exchange_strong(&ckey[slot], &expected, c, __ATOMIC_RELAXED,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      k = expected == -1 ? c : expected;
     }
-    int64_t r0 = lo;
-    for (int64_t base = e_begin; base < e_end; base += 64) {
-      const int64_t e = base + lane;
-      const bool valid = e < e_end;
-      // row of e: r0 plus the number of row ends <= e, window by window
-      int64_t myrow = valid ? -1 : r0;
-      for (int64_t rb = r0;; rb += 64) {
-        const int64_t idx = rb + 1 + lane;
-        const int64_t end_k = idx <= n ? (int64_t)off[idx] : INT64_MAX;
-        int pos = 0;
+    if (k == c)
+      __hip_atomic_fetch_add(&cval[slot], K, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+      unsafeAtomicAdd(&sig[c], K);  // slot held by another label
+  };
+  if (e_begin < e_end) {  // uniform over the wave
+    // row of e_begin: the largest i with off[i] <= e_begin, 64 probes a round
+    int64_t r0 = 0;
+    for (int64_t len = n; len > 1;) {
+      const int64_t step = (len + 63) / 64;
+      const int64_t at = lane * step;
+      const bool le = at < len && (int64_t)off[r0 + at] <= e_begin;
+      const int64_t below = (int64_t)__popcll(__ballot(le)) - 1;  // >= 0: off[r0] <= e_begin
+      r0 += below * step;
+      len = len - below * step < step ? len - below * step : step;
+    }
+    int32_t cl = C[r0];
+    if constexpr (UNIT) {
+      if (lane == 0 && (int64_t)off[r0] == e_begin)
+        add_degree(cl, (double)((int64_t)off[r0 + 1] - e_begin));
+    }
+    double carry = 0.0, hold = 0.0;  // weights: the current row's sum so far
+    auto load_targets = [&](int64_t base) {
+      const int64_t e = base + 4 * lane;
+      int4 t = make_int4(0, 0, 0, 0);
+      if (e + 4 <= e_end) {
+        __builtin_memcpy(&t, tgt + e, sizeof(t));
+      } else {
+        if (e < e_end) t.x = tgt[e];
+        if (e + 1 < e_end) t.y = tgt[e + 1];
+        if (e + 2 < e_end) t.z = tgt[e + 2];
+      }
+      return t;
+    };
+    int4 nxt = load_targets(e_begin);
+    for (int64_t base = e_begin; base < e_end; base += kModStep) {
+      const int4 t = nxt;
+      const int64_t e = base + 4 * lane;
+      const int valid = e >= e_end ? 0 : (e_end - e < 4 ? (int)(e_end - e) : 4);
+      const int64_t lim = base + kModStep < e_end ? base + kModStep : e_end;
+      int32_t lj[4];
+      lj[0] = C[t.x];
+      lj[1] = C[t.y];
+      lj[2] = C[t.z];
+      lj[3] = C[t.w];
+      float we[4];
+      if constexpr (!UNIT) {
 #pragma unroll
-        for (int step = 32; step >= 1; step >>= 1) {
-          const int64_t v = shfl_i64(end_k, pos + step - 1);
-          if (v <= e) pos += step;
+        for (int i = 0; i < 4; ++i) we[i] = i < valid ? w[e + i] : 0.0f;
+      }
+      if (base + kModStep < e_end) nxt = load_targets(base + kModStep);
+      int32_t la[4];
+      if ((int64_t)off[r0 + 1] >= lim) {
+        la[0] = la[1] = la[2] = la[3] = cl;
+        if constexpr (!UNIT) hold += ((double)we[0] + we[1]) + ((double)we[2] + we[3]);
+      } else {
+        *reinterpret_cast<int4*>(start + 4 * lane) = make_int4(-1, -1, -1, -1);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        int64_t rn = r0;
+        for (int64_t rb = r0 + 1;; rb += 64) {
+          const int64_t i = rb + lane;
+          const int64_t v = i < n ? (int64_t)off[i] : INT64_MAX;
+          const bool in = v < lim;
+          bool starts = false;
+          if (in) {
+            const int64_t v1 = (int64_t)off[i + 1];
+            if (v1 > v) {
+              starts = true;
+              const int32_t c = C[i];
+              start[v - base] = c;
+              if constexpr (UNIT) add_degree(c, (double)(v1 - v));
+            }
+          }
+          const unsigned long long b = __ballot(starts);
+          if (b) rn = rb + 63 - __clzll((long long)b);
+          if (!__all(in)) break;
         }
-        const int cnt = pos + (shfl_i64(end_k, pos) <= e ? 1 : 0);
-        if (myrow < 0 && cnt < 64) myrow = rb + cnt;
-        if (!__any(myrow < 0)) break;
-      }
-      int32_t ci = -1;
-      double we = 0.0;
-      if (valid) {
-        ci = C[myrow];
-        we = w ? (double)w[e] : 1.0;
-        two_m += we;
-        if (C[tgt[e]] == ci) sigma += we;
-      }
-      // segmented sum of we over runs of equal labels, one atomic per run
-      const int32_t prev = __shfl_up(ci, 1);
-      const int32_t next = __shfl_down(ci, 1);
-      int f = (lane == 0 || prev != ci) ? 1 : 0;
-      double sm = we;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        const int4 l4 = *reinterpret_cast<const int4*>(start + 4 * lane);
+        const int32_t l[4] = {l4.x, l4.y, l4.z, l4.w};
+        int p = -1;  // the lane's last row start
 #pragma unroll
-      for (int ofs = 1; ofs < 64; ofs <<= 1) {
-        const double ys = __shfl_up(sm, ofs);
-        const int yf = __shfl_up(f, ofs);
-        if (lane >= ofs && !f) {
-          sm += ys;
-          f |= yf;
+        for (int i = 0; i < 4; ++i)
+          if (l[i] >= 0) p = 4 * lane + i;
+        int before = __shfl_up(wave_scan_max(p), 1);
+        if (lane == 0) before = -1;
+        const int32_t prev = before >= 0 ? start[before] : cl;
+        la[0] = l[0] >= 0 ? l[0] : prev;
+#pragma unroll
+        for (int i = 1; i < 4; ++i) la[i] = l[i] >= 0 ? l[i] : la[i - 1];
+        if constexpr (!UNIT) {
+          carry += wave_sum_f64(hold);
+          hold = 0.0;
+          // the sum of the row open at the lane's end, over the lanes
+          double open = 0.0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) open = (l[i] >= 0 ? 0.0 : open) + we[i];
+          if (lane == 0 && p < 0) open += carry;
+          int f = p >= 0 ? 1 : 0;
+#pragma unroll
+          for (int ofs = 1; ofs < 64; ofs <<= 1) {
+            const double ys = __shfl_up(open, ofs);
+            const int yf = __shfl_up(f, ofs);
+            if (lane >= ofs && !f) {
+              open += ys;
+              f |= yf;
+            }
+          }
+          double run = __shfl_up(open, 1);
+          if (lane == 0) run = carry;
+          // the rows that end in the lane
+          int32_t c = prev;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (l[i] >= 0) {
+              if (run != 0.0) add_degree(c, run);
+              run = 0.0;
+              c = l[i];
+            }
+            run += we[i];
+          }
+          carry = __shfl(open, 63);
+        }
+        cl = __builtin_amdgcn_readlane(la[3], 63);
+        r0 = rn;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool eq = i < valid && lj[i] == la[i];
+        if constexpr (UNIT) {
+          same += eq ? 1u : 0u;
+        } else {
+          sigma += eq ? (double)we[i] : 0.0;
+          two_m += (double)we[i];
         }
       }
-      const bool tail = lane == 63 || next != ci;
-      if (tail && ci >= 0 && sm != 0.0) {
-        const int slot = (int)(((uint32_t)ci * 0x9E3779B1u) >> 26);  // 64 slots
-        int k = __hip_atomic_load(&ckey[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        if (k == -1) {
-          int expected = -1;
-          __hip_atomic_compare_exchange_strong(&ckey[slot], &expected, ci, __ATOMIC_RELAXED,
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-          k = expected == -1 ? ci : expected;
-        }
-        if (k == ci)
-          __hip_atomic_fetch_add(&cval[slot], sm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        else
-          atomicAdd(&sig[ci], sm);  // slot held by another label
-      }
-      const int last = (int)((e_end - 1 - base) < 63 ? (e_end - 1 - base) : 63);
-      r0 = shfl_i64(myrow, last);
+    }
+    if constexpr (!UNIT) {
+      carry += wave_sum_f64(hold);
+      if (lane == 0 && carry != 0.0) add_degree(cl, carry);
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  if (ckey[lane] >= 0 && cval[lane] != 0.0) atomicAdd(&sig[ckey[lane]], cval[lane]);
+  if constexpr (UNIT) sigma = (double)same;
   const double s1 = block_sum_f64(sigma, sh);
-  const double s2 = block_sum_f64(two_m, sh);
+  const double s2 = UNIT ? 0.0 : block_sum_f64(two_m, sh);
+  __syncthreads();
+  for (int x = threadIdx.x; x < kModCache; x += kBT)
+    if (ckey[x] >= 0 && cval[x] != 0.0) unsafeAtomicAdd(&sig[ckey[x]], cval[x]);
   if (threadIdx.x == 0) {
-    atomicAdd(&acc[0], s1);
-    atomicAdd(&acc[1], s2);
+    double* slot = reinterpret_cast<double*>(stat_slot(st)) + kStatMod;
+    unsafeAtomicAdd(&slot[0], s1);
+    if (UNIT && blockIdx.x == 0) unsafeAtomicAdd(&slot[1], (double)m);
+    if (!UNIT) unsafeAtomicAdd(&slot[1], s2);
   }
 }
 
-__global__ __launch_bounds__(kBT) void k_mod_sq(const double* sig, int64_t n, double* acc) {
+__global__ __launch_bounds__(kBT) void k_mod_sq(const double* sig, int64_t n, DevStats* st) {
   __shared__ double sh[kBT / 64];
   double s = 0.0;
   for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
        c += (int64_t)gridDim.x * blockDim.x)
     s += sig[c] * sig[c];
   const double t = block_sum_f64(s, sh);
-  if (threadIdx.x == 0) atomicAdd(&acc[2], t);
+  if (threadIdx.x == 0)
+    unsafeAtomicAdd(reinterpret_cast<double*>(stat_slot(st)) + kStatMod + 2, t);
+}
+
+// The copies of the three sums added to acc and cleared; one wave.
+__global__ void k_mod_fold(DevStats* st, double* acc) {
+  const int lane = threadIdx.x & 63;
+  for (int k = 0; k < 3; ++k) {
+    double x = 0.0;
+    if (lane < kStatSlots) {
+      double* p = reinterpret_cast<double*>(reinterpret_cast<DevState*>(st)->slot[lane]) + kStatMod + k;
+      x = *p;
+      *p = 0.0;
+    }
+    const double t = wave_sum_f64(x);
+    if (lane == 0) acc[k] = t;
+  }
 }
 
 // ---- modularity scratch for callers that cannot allocate ----------------------
-// Sigma_c (one double per vertex) and the four accumulators of
-// lpa_modularity_noalloc live in this file-scope array: one copy per GPU,
-// 32 MiB, held until the process ends.  Host code never takes the array's
+// Sigma_c (one double per vertex) of lpa_modularity_noalloc lives in this
+// file-scope array: one copy per GPU, 32 MiB, held until the process ends.  Host code never takes the array's
 // name as an address (it is a host-side stand-in); the device address comes
 // from hipGetSymbolAddress, once per device, with that device current.
-static __device__ __align__(256) double scratch[kModScratchVertices + 4];
+static __device__ __align__(256) double scratch[kModScratchVertices];
 
-hipError_t modularity_scratch(double** sig, double** acc) {
+hipError_t modularity_scratch(double** sig) {
   constexpr int kMaxDevices = 64;
   static std::mutex mu;
   static double* addr[kMaxDevices] = {};
@@ -1734,29 +1857,30 @@ hipError_t modularity_scratch(double** sig, double** acc) {
     addr[dev] = static_cast<double*>(p);
   }
   *sig = addr[dev];
-  *acc = addr[dev] + kModScratchVertices;
   return hipSuccess;
 }
 
 hipError_t launch_modularity(bool off64, const void* off, const int32_t* tgt, const float* w,
                              int64_t n, int64_t m, const int32_t* C, double* sig,
-                             double* acc, hipStream_t s) {
+                             double* acc, DevStats* st, hipStream_t s) {
   hipError_t e = launch_fill_f64(sig, 0.0, n, s);
   if (e != hipSuccess) return e;
-  e = launch_fill_f64(acc, 0.0, 4, s);
-  if (e != hipSuccess) return e;
   if (m > 0) {
-    const int g = grid_for((m + 63) / 64, kBT, 16384);
-    if (off64)
-      hipLaunchKernelGGL(k_mod_edges<int64_t>, dim3(g), dim3(kBT), 0, s, (const int64_t*)off,
-                         tgt, w, n, m, C, sig, acc);
-    else
-      hipLaunchKernelGGL(k_mod_edges<int32_t>, dim3(g), dim3(kBT), 0, s, (const int32_t*)off,
-                         tgt, w, n, m, C, sig, acc);
+    const int64_t S = std::max<int64_t>((m + kModWaves - 1) / kModWaves + kModStep - 1, kModStep) /
+                      kModStep * kModStep;
+    const int g = (int)(((m + S - 1) / S + kBT / 64 - 1) / (kBT / 64));
+    auto go = [&](auto kernel, auto* o) {
+      hipLaunchKernelGGL(kernel, dim3(g), dim3(kBT), 0, s, o, tgt, w, n, m, S, C, sig, st);
+    };
+    if (off64 && w) go(k_mod_edges<int64_t, false>, (const int64_t*)off);
+    else if (off64) go(k_mod_edges<int64_t, true>, (const int64_t*)off);
+    else if (w) go(k_mod_edges<int32_t, false>, (const int32_t*)off);
+    else go(k_mod_edges<int32_t, true>, (const int32_t*)off);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_mod_sq, dim3(grid_for(n, kBT, 8192)), dim3(kBT), 0, s, sig, n, acc);
+  hipLaunchKernelGGL(k_mod_sq, dim3(grid_for(n, kBT, 2048)), dim3(kBT), 0, s, sig, n, st);
+  hipLaunchKernelGGL(k_mod_fold, dim3(1), dim3(64), 0, s, st, acc);
   return hipGetLastError();
 }
 

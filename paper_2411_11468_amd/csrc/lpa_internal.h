@@ -83,9 +83,8 @@ struct DevStats {
   unsigned long long fneg;                      // of those, processed and changed
   unsigned long long trace_n;                   // samples drawn so far
   unsigned long long trace_first;               // trace_n when the iteration began
-  double mod_acc[4];                            // lpa_modularity_noalloc: the
-                                                // accumulators, read back with
-                                                // the counters
+  double mod_acc[4];                            // modularity's sums, read back
+                                                // with the counters
 };
 
 // Statistics of one iteration as recorded on the device (same layout as the
@@ -113,7 +112,8 @@ constexpr int kStatWords = 64;
 // words of a slot: the three counters of class c at 3 c, then
 constexpr int kStatEdges = 0, kStatChanged = 1, kStatFlagw = 2;
 constexpr int kStatProcessed = 32, kStatSkipped = 33, kStatNpred = 34, kStatFneg = 35,
-              kStatHubPairs = 36, kStatPullScanned = 37;
+              kStatHubPairs = 36, kStatPullScanned = 37,
+              kStatMod = 40;  // modularity's three sums, fp64
 static_assert(3 * kNumClasses <= kStatProcessed, "the classes' counters overlap the others");
 // Iterations whose statistics a handle has room for from the start; a run of
 // more allocates its own.
@@ -416,14 +416,13 @@ int tv_max_resident(int cls, int bits);
 // Bucket count of a hub of degree d: 2^lgb buckets of about chunk entries.
 int hub_bucket_log2(int64_t d, int chunk);
 constexpr int kHubMaxBucketLog2 = 12;   // 4096 buckets (LDS histogram of k_hub_part)
-// lpa_modularity_noalloc: the device addresses of the current GPU's
-// file-scope scratch (kModScratchVertices doubles for Sigma_c, then 4
-// accumulators), looked up once per device.
+// lpa_modularity_noalloc: the device address of the current GPU's file-scope
+// scratch (kModScratchVertices doubles for Sigma_c), looked up once per device.
 constexpr int64_t kModScratchVertices = (int64_t)1 << 22;
-hipError_t modularity_scratch(double** sig, double** acc);
+hipError_t modularity_scratch(double** sig);
 hipError_t launch_modularity(bool off64, const void* off, const int32_t* tgt,
                              const float* w, int64_t n, int64_t m,
-                             const int32_t* C, double* sig, double* acc,
+                             const int32_t* C, double* sig, double* acc, DevStats* st,
                              hipStream_t s);
 
 // Work-queue form of a batched run (queue.hip): queue every chunk of every
