@@ -976,7 +976,7 @@ struct RunCtx {
 template <typename Mark>
 static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const RunCtx& rc,
                                     hipStream_t s, Mark&& mark, bool direct = false,
-                                    bool cc = false) {
+                                    bool cc = false, bool lean = false) {
   const int64_t n = g->n;
   const int async_mode = o.mode == LPA_MODE_ASYNC;
   if (g->wq && o.prune) {
@@ -989,7 +989,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     if (lpa_status e = mark(kKidQueueStep)) return e;
     LPA_HIP(launch_queue_step(q, s));
     if (lpa_status e = mark(-1)) return e;
-    LPA_HIP(launch_iter_end(g->st, g->hist, n, true, &g->host->progress, s));
+    LPA_HIP(launch_iter_end(g->st, g->hist, n, true, &g->host->progress, nullptr, false, s));
     return LPA_OK;
   }
   const int tv = g->tun.table_values;  // 0, or the ablation kernels' value bits
@@ -997,8 +997,15 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   // without pruning every vertex is processed in every iteration
   if (!o.prune) LPA_HIP(launch_arm_flags(g->F, n, g->st, s));
   const HubArgs ha = g->hub_args(async_mode);
-  if (lpa_status e = mark(kKidPlan)) return e;
-  LPA_HIP(launch_hub_plan(g->off64, ha, g->C, g->F, s));
+  // lean (no host reads between iterations, no profile): without hubs the
+  // iteration before has begun this one, and the flags take one launch
+  const bool lean_plan = lean && g->H == 0;
+  const bool lean_flags = lean_plan && !tv && !cc && flags_in_one_launch(g->n_active);
+  const FlagRule rule{g->m, n, o.flag_mode, g->tun.pull_divisor};
+  if (!lean_plan) {
+    if (lpa_status e = mark(kKidPlan)) return e;
+    LPA_HIP(launch_hub_plan(g->off64, ha, g->C, g->F, s));
+  }
   if (lpa_status e = mark(kKidFrontier)) return e;
   // after the first iteration only the vertices of positive degree can be
   // flagged (without pruning every vertex is, every iteration)
@@ -1055,7 +1062,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   }
   if (cc) {
     if (!async_mode)
-      LPA_HIP(launch_publish(g->st, g->chg, g->n_active, g->Cn, g->C, g->chg_bits, true, false, s));
+      LPA_HIP(launch_publish(g->st, g->chg, g->n_active, g->Cn, g->C, g->chg_bits, true, 0, s));
     // Cross-Check: rounds until no revert decision changes (the decisions
     // depend only on smaller ids, so at most one round per chain step)
     if (lpa_status e = mark(-1)) return e;
@@ -1072,26 +1079,33 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   }
   // flag the neighbours of the changed vertices: the decide kernel picks
   // push or pull from this iteration's counters, the other kernels return
-  if (lpa_status e = mark(kKidDecide)) return e;
-  LPA_HIP(launch_flag_decide(g->st, g->m, g->n, o.flag_mode, g->tun.pull_divisor, s));
+  if (!lean_flags) {
+    if (lpa_status e = mark(kKidDecide)) return e;
+    LPA_HIP(launch_flag_decide(g->st, rule, s));
+  }
   // labels (Cross-Check has published its own) and change bits
   if (lpa_status e = mark(kKidApply)) return e;
   LPA_HIP(launch_publish(g->st, g->chg, g->n_active, g->Cn, g->C, g->chg_bits,
-                         !async_mode && !cc, true, s));
-  if (lpa_status e = mark(kKidPush)) return e;
-  LPA_HIP(launch_push_lists(g->off64, g->off, g->tgt, g->lists, g->chg, g->F, g->st,
-                            g->push_grid, s));
-  if (g->H > 0) {
-    if (lpa_status e = mark(kKidPushHubs)) return e;
-    LPA_HIP(launch_push_hubs(g->off64, ha, g->hub_fin_grid, s));
-  }
-  if (lpa_status e = mark(kKidPull)) return e;
-  LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
-                            g->st, s));
-  if (g->H > 0) {
-    if (lpa_status e = mark(kKidPullHubs)) return e;
-    LPA_HIP(launch_pull_hubs(g->off64, g->off, g->tgt, g->hub_vid, g->H, g->chg_bits, g->F,
-                             g->st, s));
+                         !async_mode && !cc, lean_flags ? 2 : 1, s));
+  if (lean_flags) {
+    LPA_HIP(launch_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F, g->st,
+                         g->lists, g->chg, rule, s));
+  } else {
+    if (lpa_status e = mark(kKidPush)) return e;
+    LPA_HIP(launch_push_lists(g->off64, g->off, g->tgt, g->lists, g->chg, g->F, g->st,
+                              g->push_grid, s));
+    if (g->H > 0) {
+      if (lpa_status e = mark(kKidPushHubs)) return e;
+      LPA_HIP(launch_push_hubs(g->off64, ha, g->hub_fin_grid, s));
+    }
+    if (lpa_status e = mark(kKidPull)) return e;
+    LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
+                              g->st, s));
+    if (g->H > 0) {
+      if (lpa_status e = mark(kKidPullHubs)) return e;
+      LPA_HIP(launch_pull_hubs(g->off64, g->off, g->tgt, g->hub_vid, g->H, g->chg_bits, g->F,
+                               g->st, s));
+    }
   }
   if (g->G > 0) {
     if (lpa_status e = mark(kKidBatch)) return e;
@@ -1102,7 +1116,8 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
     LPA_HIP(launch_trace_label(g->st, g->chg, rc.tr, s));
   }
   if (lpa_status e = mark(-1)) return e;
-  LPA_HIP(launch_iter_end(g->st, g->hist, n, false, &g->host->progress, s));
+  LPA_HIP(launch_iter_end(g->st, g->hist, n, lean_flags, &g->host->progress,
+                          lean_flags ? &rule : nullptr, lean_plan, s));
   return LPA_OK;
 }
 
@@ -1124,7 +1139,7 @@ lpa_status lpa_graph_s::iteration_graph(const lpa_options& o, const RunCtx& rc,
   if (!cap_stream) LPA_HIP(hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking));
   LPA_HIP(hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal));
   auto nomark = [](int) -> lpa_status { return LPA_OK; };
-  const lpa_status st = enqueue_iteration(this, o, rc, cap_stream, nomark);
+  const lpa_status st = enqueue_iteration(this, o, rc, cap_stream, nomark, false, false, true);
   hipGraph_t graph = nullptr;
   const hipError_t end = hipStreamEndCapture(cap_stream, &graph);
   if (st != LPA_OK) {
@@ -1294,7 +1309,7 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
     for (int32_t l = 0; l < l0; ++l) {
       auto nomark = [](int) -> lpa_status { return LPA_OK; };
       if (lpa_status e = enqueue_iteration(g, o, ctx_of(l), s, nomark,
-                                           first_direct && l == 0))
+                                           first_direct && l == 0, false, true))
         return e;
     }
     for (int32_t l = l0; l < o.max_iterations; ++l) {
@@ -1313,7 +1328,8 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
       bool stopped = false;
       if (lpa_status e = g->wait_iterations(l - kRunAhead, &stopped)) return e;
       if (stopped) break;
-      if (lpa_status e = enqueue_iteration(g, o, ctx_of(l), s, nomark, first_direct && l == 0))
+      if (lpa_status e = enqueue_iteration(g, o, ctx_of(l), s, nomark, first_direct && l == 0, false,
+                                           true))
         return e;
       if (l < stats_cap) {
         if (lpa_status e = g->ensure_events(l + 2)) return e;
@@ -1745,7 +1761,7 @@ lpa_status lpa_get_flags(lpa_graph g, uint8_t* flags) {
     // from the change bytes it left (the frontier of a next run clears them)
     hipStream_t s = g->stream;
     LPA_HIP(launch_flags_resume(g->st, s));
-    LPA_HIP(launch_publish(g->st, g->chg, g->n_active, nullptr, nullptr, g->chg_bits, false, true,
+    LPA_HIP(launch_publish(g->st, g->chg, g->n_active, nullptr, nullptr, g->chg_bits, false, 1,
                            s));
     LPA_HIP(launch_pull_flags(g->off64, g->off, g->tgt, g->n_active, g->cls, g->chg_bits, g->F,
                               g->st, s));

@@ -63,6 +63,34 @@ hipError_t launch_init(int64_t n, const int32_t* init, const int32_t* inv, int32
 // the iteration's statistics and applies the stop rule of Algorithm 1 (after
 // an iteration that is not Pick-Less with changed < tolerance * N), or, in a
 // batched run, stops when every graph has stopped.
+// The counters and switches of iteration st->iter, by the first kNumClasses
+// threads of one workgroup.
+__device__ __forceinline__ void begin_iteration(DevStats* st) {
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    st->processed = 0;
+    st->pull_scanned = 0; st->pull_mode = 0;
+    st->hub_pairs = 0;
+    st->reverted = 0;
+    st->graphs_left = 0;
+    // Pick-Less in iterations l with l mod rho == 0, counting from 0
+    st->pl = (st->rho > 0 && st->iter % st->rho == 0) ? 1 : 0;
+    // learned skipping: predictions from iteration 1 on until a fallback;
+    // skip unless this is a guard iteration or the last one changed few
+    const int l = st->iter;
+    st->predict = (st->learn && !st->fallback && l >= st->pred_start) ? 1 : 0;
+    st->skipping = (st->predict && (st->guard == 0 || l % st->guard != 0) && !st->cand) ? 1 : 0;
+    st->skipped = 0; st->npred = 0; st->fneg = 0;
+    st->trace_first = st->trace_n;
+  }
+  if (tid < kNumClasses) {
+    st->active[tid].n = 0;
+    st->edges[tid] = 0;
+    st->changed[tid] = 0;
+    st->flagw[tid] = 0;
+  }
+}
+
 __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
                             int graphs, LearnParams lp, unsigned int seq) {
   uint32_t* w = reinterpret_cast<uint32_t*>(st);
@@ -91,6 +119,7 @@ __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batc
     st->cand = 1;
     st->seq = seq;
   }
+  begin_iteration(st);  // thread 0 wrote what it reads
 }
 
 hipError_t launch_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
@@ -113,11 +142,28 @@ hipError_t launch_arm_flags(uint8_t* F, int64_t n, const DevStats* st, hipStream
   return hipGetLastError();
 }
 
-// FOLD: no k_flag_decide has added up the counters' copies (a work-queue run);
-// otherwise only the pull kernels have added to them since.
+// How this iteration's flags are set: 0 pushed, 1 pulled, 2 left to
+// lpa_get_flags (the run stops after this iteration: k_iter_end's test, same
+// operands).  fw: entries in the rows of the changed vertices.
+__device__ __forceinline__ unsigned int flag_decision(const DevStats* st, const FlagRule& r,
+                                                      unsigned long long fw,
+                                                      unsigned long long changed,
+                                                      unsigned long long skipped) {
+  if (!st->batched &&
+      ((!st->pl && (double)(changed + skipped) < st->tol * (double)r.n) || st->iter + 1 >= st->cap))
+    return 2u;
+  if (r.force) return r.force == 2 ? 1u : 0u;
+  return (unsigned long long)r.pdiv * fw >= (unsigned long long)r.m ? 1u : 0u;
+}
+
+// FOLD: no k_flag_decide has added up the counters' copies (a work-queue run,
+// k_flags); otherwise only the pull kernels have added to them since.  rule.m
+// >= 0: record k_flags' decision too.  next: no k_hub_plan begins the next
+// iteration.
 template <bool FOLD>
 __global__ __launch_bounds__(1024) void k_iter_end(DevStats* st, DevIterStats* hist, int64_t n,
-                                                   unsigned long long* progress) {
+                                                   unsigned long long* progress, FlagRule rule,
+                                                   int next) {
   if (st->stop) return;
   if constexpr (FOLD) {
     fold_stats(st);
@@ -129,52 +175,69 @@ __global__ __launch_bounds__(1024) void k_iter_end(DevStats* st, DevIterStats* h
     for (int ofs = kStatSlots / 2; ofs > 0; ofs >>= 1) t += __shfl_xor(t, ofs, kStatSlots);
     if (threadIdx.x == 0) st->pull_scanned = t;
   }
-  if (threadIdx.x != 0) return;
-  unsigned long long changed = 0, edges = 0;
-  for (int c = 0; c < kNumClasses; ++c) {
-    changed += st->changed[c];
-    edges += st->edges[c];
+  __shared__ int ended_sh;
+  if (threadIdx.x == 0) {
+    unsigned long long changed = 0, edges = 0;
+    for (int c = 0; c < kNumClasses; ++c) {
+      changed += st->changed[c];
+      edges += st->edges[c];
+    }
+    if (rule.m >= 0) {
+      unsigned long long fw = 0;
+      for (int c = 0; c < kNumClasses; ++c) fw += st->flagw[c];
+      st->pull_mode = flag_decision(st, rule, fw, changed, st->skipped);
+      st->flags_deferred = st->pull_mode == 2u ? 1u : 0u;
+    }
+    changed -= st->reverted;  // Cross-Check reverts do not count as changes
+    const int l = st->iter;
+    // learned skipping: a plain iteration with predictions checks the vertices
+    // predicted unchanged; too many of them changing turns skipping off
+    if (st->predict && !st->skipping && st->npred > 0 &&
+        (double)st->fneg > st->fn_bound * (double)st->npred)
+      st->fallback = 1;
+    DevIterStats& h = hist[l];
+    h.iteration = l;
+    h.pick_less = st->pl;
+    h.changed = (long long)changed;
+    h.processed = (long long)st->processed;
+    h.edges = (long long)edges;
+    h.skipped = (long long)st->skipped;
+    h.npred = (long long)st->npred;
+    h.fneg = st->skipping ? 0ll : (long long)st->fneg;
+    h.skipping = st->skipping;
+    h.fallback = st->fallback;
+    int stop = 0;
+    if (st->batched) stop = st->graphs_left == 0u;
+    // Algorithm 1's test on changed + skipped: the skipped vertices bound what
+    // a plain sweep of this iteration could have changed in addition
+    else stop = !st->pl && (double)(changed + st->skipped) < st->tol * (double)n;
+    // near the stop (changed < 2 tol N) the next iteration is a plain sweep
+    st->cand = (double)changed < 2.0 * st->tol * (double)n ? 1 : 0;
+    st->iter = l + 1;
+    const int ended = (stop || l + 1 >= st->cap) ? 1 : 0;
+    st->stop = ended;
+    // for the host, which launches on while iterations run: the word alone is
+    // read there, so that no other write has to be visible with it
+    __hip_atomic_store(progress,
+                       (unsigned long long)st->seq << 32 | (unsigned int)ended << 31 |
+                           (unsigned int)(l + 1),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    ended_sh = ended;
   }
-  changed -= st->reverted;  // Cross-Check reverts do not count as changes
-  const int l = st->iter;
-  // learned skipping: a plain iteration with predictions checks the vertices
-  // predicted unchanged; too many of them changing turns skipping off
-  if (st->predict && !st->skipping && st->npred > 0 &&
-      (double)st->fneg > st->fn_bound * (double)st->npred)
-    st->fallback = 1;
-  DevIterStats& h = hist[l];
-  h.iteration = l;
-  h.pick_less = st->pl;
-  h.changed = (long long)changed;
-  h.processed = (long long)st->processed;
-  h.edges = (long long)edges;
-  h.skipped = (long long)st->skipped;
-  h.npred = (long long)st->npred;
-  h.fneg = st->skipping ? 0ll : (long long)st->fneg;
-  h.skipping = st->skipping;
-  h.fallback = st->fallback;
-  int stop = 0;
-  if (st->batched) stop = st->graphs_left == 0u;
-  // Algorithm 1's test on changed + skipped: the skipped vertices bound what
-  // a plain sweep of this iteration could have changed in addition
-  else stop = !st->pl && (double)(changed + st->skipped) < st->tol * (double)n;
-  // near the stop (changed < 2 tol N) the next iteration is a plain sweep
-  st->cand = (double)changed < 2.0 * st->tol * (double)n ? 1 : 0;
-  st->iter = l + 1;
-  const int ended = (stop || l + 1 >= st->cap) ? 1 : 0;
-  st->stop = ended;
-  // for the host, which launches on while iterations run: the word alone is
-  // read there, so that no other write has to be visible with it
-  __hip_atomic_store(progress,
-                     (unsigned long long)st->seq << 32 | (unsigned int)ended << 31 |
-                         (unsigned int)(l + 1),
-                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __syncthreads();
+  if (next && !ended_sh) begin_iteration(st);
 }
 
 hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, bool fold,
-                           unsigned long long* progress, hipStream_t s) {
-  if (fold) hipLaunchKernelGGL(k_iter_end<true>, dim3(1), dim3(1024), 0, s, st, hist, n, progress);
-  else hipLaunchKernelGGL(k_iter_end<false>, dim3(1), dim3(64), 0, s, st, hist, n, progress);
+                           unsigned long long* progress, const FlagRule* rule, bool next,
+                           hipStream_t s) {
+  const FlagRule r = rule ? *rule : FlagRule{-1, 0, 0, 0};
+  if (fold)
+    hipLaunchKernelGGL(k_iter_end<true>, dim3(1), dim3(1024), 0, s, st, hist, n, progress, r,
+                       next ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_iter_end<false>, dim3(1), dim3(64), 0, s, st, hist, n, progress, r,
+                       next ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -513,28 +576,9 @@ __global__ __launch_bounds__(1024) void k_hub_plan(HubArgs a, int32_t* C, uint8_
   const int tid = threadIdx.x;
   DevStats* st = a.st;
   if (st->stop) return;
+  begin_iteration(st);
   if (tid == 0) {
-    st->processed = 0;
-    st->pull_scanned = 0; st->pull_mode = 0;
-    st->hub_pairs = 0;
-    st->reverted = 0;
-    st->graphs_left = 0;
-    // Pick-Less in iterations l with l mod rho == 0, counting from 0
-    st->pl = (st->rho > 0 && st->iter % st->rho == 0) ? 1 : 0;
-    // learned skipping: predictions from iteration 1 on until a fallback;
-    // skip unless this is a guard iteration or the last one changed few
-    const int l = st->iter;
-    st->predict = (st->learn && !st->fallback && l >= st->pred_start) ? 1 : 0;
-    st->skipping = (st->predict && (st->guard == 0 || l % st->guard != 0) && !st->cand) ? 1 : 0;
-    st->skipped = 0; st->npred = 0; st->fneg = 0;
-    st->trace_first = st->trace_n;
     run_s = 0; run_b = 0; nproc = 0;
-  }
-  if (tid < kNumClasses) {
-    st->active[tid].n = 0;
-    st->edges[tid] = 0;
-    st->changed[tid] = 0;
-    st->flagw[tid] = 0;
   }
   if (a.witems && tid < kXcds) a.wctr[tid * kQueueCtrStride] = 0u;
   __syncthreads();
@@ -1053,8 +1097,7 @@ hipError_t launch_trace_label(const DevStats* st, const uint8_t* chg, const Trac
 // k_flag_decide picks pull when the changed rows hold at least 1/pdiv of the
 // CSR entries (lpa_tuning.pull_divisor, default 16), push otherwise; the
 // kernels of the other way return at once.
-__global__ __launch_bounds__(1024) void k_flag_decide(DevStats* st, int64_t m, int64_t n, int force,
-                                                      int pdiv) {
+__global__ __launch_bounds__(1024) void k_flag_decide(DevStats* st, FlagRule rule) {
   if (st->stop) return;
   fold_stats(st);
   if (threadIdx.x != 0) return;
@@ -1063,26 +1106,13 @@ __global__ __launch_bounds__(1024) void k_flag_decide(DevStats* st, int64_t m, i
     fw += st->flagw[c];
     changed += st->changed[c];
   }
-  changed -= st->reverted;
-  // the run stops after this iteration (k_iter_end's test, same operands):
+  st->pull_mode = flag_decision(st, rule, fw, changed - st->reverted, st->skipped);
   // its flags matter only to a later lpa_get_flags, which sets them then
-  if (!st->batched) {
-    const bool last = (!st->pl && (double)(changed + st->skipped) < st->tol * (double)n) ||
-                      st->iter + 1 >= st->cap;
-    if (last) {
-      st->pull_mode = 2u;
-      st->flags_deferred = 1u;
-      return;
-    }
-  }
-  st->pull_mode = force == 2   ? 1u
-                  : force == 1 ? 0u
-                               : ((unsigned long long)pdiv * fw >= (unsigned long long)m ? 1u : 0u);
+  if (st->pull_mode == 2u) st->flags_deferred = 1u;
 }
 
-hipError_t launch_flag_decide(DevStats* st, int64_t m, int64_t n, int force, int pdiv,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(k_flag_decide, dim3(1), dim3(1024), 0, s, st, m, n, force, pdiv);
+hipError_t launch_flag_decide(DevStats* st, const FlagRule& rule, hipStream_t s) {
+  hipLaunchKernelGGL(k_flag_decide, dim3(1), dim3(1024), 0, s, st, rule);
   return hipGetLastError();
 }
 
@@ -1182,10 +1212,9 @@ hipError_t launch_flags_done(DevStats* st, hipStream_t s) {
 // push: classes 1..4 with 8 lanes per vertex, classes 5..8 with a workgroup
 // per vertex (hub rows: k_push_hubs, one workgroup per slice)
 template <typename OffT>
-__global__ __launch_bounds__(kBT) void k_push_lists(const OffT* off, const int32_t* tgt,
-                                                    ListPtrs lists, const uint8_t* chg,
-                                                    uint8_t* F, DevStats* st) {
-  if (st->stop || st->pull_mode) return;
+__device__ __forceinline__ void push_lists(const OffT* off, const int32_t* tgt,
+                                           const ListPtrs& lists, const uint8_t* chg, uint8_t* F,
+                                           const DevStats* st) {
   const int lane = threadIdx.x & 63;
   const int k = lane & 7;
   const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
@@ -1212,6 +1241,14 @@ __global__ __launch_bounds__(kBT) void k_push_lists(const OffT* off, const int32
       for (int64_t e = threadIdx.x; e < d; e += blockDim.x) F[tgt[o + e]] = 1;
     }
   }
+}
+
+template <typename OffT>
+__global__ __launch_bounds__(kBT) void k_push_lists(const OffT* off, const int32_t* tgt,
+                                                    ListPtrs lists, const uint8_t* chg,
+                                                    uint8_t* F, DevStats* st) {
+  if (st->stop || st->pull_mode) return;
+  push_lists(off, tgt, lists, chg, F, st);
 }
 
 hipError_t launch_push_lists(bool off64, const void* off, const int32_t* tgt,
@@ -1265,7 +1302,7 @@ __device__ __forceinline__ bool group_any16(bool x, int g) {
 // After the sweep, over the change bytes: in deterministic mode (APPLY) the
 // changed vertices' labels go from Cn to C -- the sweeps wrote Cn for them
 // only --, and when the flags are pulled the bytes are packed into bits (bit v
-// % 32 of word v / 32; pack): the pull kernels' reads land at data-dependent
+// % 32 of word v / 32; pack, 2 ahead of k_flags' decision): the pull kernels' reads land at data-dependent
 // vertices, and the bitmap (n / 8 bytes) keeps far more of them in one cache
 // line than the bytes do.  One vertex per lane, so that the copies of a wave
 // fall on consecutive addresses.  It is bound by the bytes read and the
@@ -1277,7 +1314,7 @@ __global__ __launch_bounds__(kBT) void k_publish(const DevStats* st, const uint8
                                                  const int32_t* Cn, int32_t* C, uint32_t* bits,
                                                  int pack) {
   if (st->stop) return;
-  const bool packed = pack && st->pull_mode == 1u;
+  const bool packed = pack == 2 || (pack && st->pull_mode == 1u);
   if (!APPLY && !packed) return;
   constexpr int U = 8;  // 64-vertex groups per wave step, all in flight
   const int lane = threadIdx.x & 63;
@@ -1315,14 +1352,14 @@ __global__ __launch_bounds__(kBT) void k_publish(const DevStats* st, const uint8
 }
 
 hipError_t launch_publish(const DevStats* st, const uint8_t* chg, int64_t n, const int32_t* Cn,
-                          int32_t* C, uint32_t* bits, bool apply, bool pack, hipStream_t s) {
+                          int32_t* C, uint32_t* bits, bool apply, int pack, hipStream_t s) {
   const int g = grid_for(n, kBT * 8, 2048);
   if (apply)
     hipLaunchKernelGGL(k_publish<true>, dim3(g), dim3(kBT), 0, s, st, chg, n, Cn, C, bits,
-                       pack ? 1 : 0);
+                       pack);
   else
     hipLaunchKernelGGL(k_publish<false>, dim3(g), dim3(kBT), 0, s, st, chg, n, Cn, C, bits,
-                       pack ? 1 : 0);
+                       pack);
   return hipGetLastError();
 }
 
@@ -1354,13 +1391,52 @@ __device__ __forceinline__ int4 load_four(const int32_t* tgt, int64_t p, int64_t
 // other, so by the waves in flight: eight per SIMD, the whole grid resident at
 // once (8192 x 8192 lattice: 0.41 ms per launch; with the last four entries
 // read one by one 0.43, with two vertices per lane and six waves 0.48).
-template <typename OffT, int BT, int WORDS>
+//
+// DECIDE (k_flags): graphs of up to 1.2 M vertices without hubs take the
+// decision, the pushing and the pulling in one launch, each workgroup adding
+// up the counters' copies for itself (k_iter_end folds them): a launch that
+// returns at once still takes 4.6 us of an iteration of a captured run.  With
+// the next iteration begun by k_iter_end, three launches fewer an iteration: a
+// 10 000-vertex run 0.38 -> 0.33 ms, LFR 1M 1.60 -> 1.57 ms.
+struct PushArgs {
+  ListPtrs lists;
+  const uint8_t* chg;
+  FlagRule rule;
+};
+template <typename OffT, int BT, int WORDS, bool DECIDE>
 __global__ __launch_bounds__(BT, WORDS ? 1 : 8) void k_pull_flags(const OffT* off, const int32_t* tgt,
                                                    int64_t n, const uint8_t* cls,
                                                    const uint32_t* bits, uint8_t* F,
-                                                   DevStats* st) {
-  if (st->stop || st->pull_mode != 1u) return;
-  __shared__ uint32_t copy[WORDS ? WORDS : 1];
+                                                   DevStats* st, PushArgs pa) {
+  if (st->stop || (!DECIDE && st->pull_mode != 1u)) return;
+  __shared__ __align__(16) uint32_t copy[WORDS ? WORDS : 1];
+  if constexpr (DECIDE) {
+    __shared__ unsigned int mode_sh;
+    unsigned long long(*part)[kStatWords] =
+        reinterpret_cast<unsigned long long(*)[kStatWords]>(copy);
+    static_assert(WORDS * 4 >= BT / 64 * kStatWords * 8, "the copies' sums fit the bits' LDS");
+    const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const unsigned long long(*slot)[kStatWords] = reinterpret_cast<const DevState*>(st)->slot;
+    unsigned long long x = 0;
+    for (int q = wv; q < kStatSlots; q += BT / 64) x += slot[q][l];
+    part[wv][l] = x;
+    __syncthreads();
+    if (wv == 0) {
+      for (int q = 1; q < BT / 64; ++q) x += part[q][l];
+      const bool cls_word = l < 3 * kNumClasses;
+      const unsigned long long fw = wave_sum_u64(cls_word && l % 3 == kStatFlagw ? x : 0ull);
+      const unsigned long long ch = wave_sum_u64(cls_word && l % 3 == kStatChanged ? x : 0ull);
+      const unsigned long long sk = wave_sum_u64(l == kStatSkipped ? x : 0ull);
+      if (l == 0) mode_sh = flag_decision(st, pa.rule, fw, ch, sk);
+    }
+    __syncthreads();
+    const unsigned int mode = mode_sh;
+    if (mode == 2u) return;
+    if (mode == 0u) {
+      push_lists(off, tgt, pa.lists, pa.chg, F, st);
+      return;
+    }
+  }
   const int64_t words = (n + 31) / 32;
   if constexpr (WORDS > 0) {
     for (int w = threadIdx.x; w < (int)words; w += BT) copy[w] = bits[w];
@@ -1531,27 +1607,45 @@ __global__ __launch_bounds__(kBT) void k_pull_hubs(const OffT* off, const int32_
 // of 16 waves to a CU; larger graphs read them from memory.
 constexpr int kPullSmallWords = 8192, kPullBigWords = 38912;
 
-template <typename OffT>
+template <typename OffT, bool DECIDE>
 static void pull_flags(const void* off, const int32_t* tgt, int64_t n, const uint8_t* cls,
-                       const uint32_t* bits, uint8_t* F, DevStats* st, hipStream_t s) {
+                       const uint32_t* bits, uint8_t* F, DevStats* st, const PushArgs& pa,
+                       hipStream_t s) {
   const OffT* o = (const OffT*)off;
   const int64_t words = (n + 31) / 32;
   if (words <= kPullSmallWords)
-    hipLaunchKernelGGL((k_pull_flags<OffT, 256, kPullSmallWords>), dim3(grid_for(n, 256, 1024)),
-                       dim3(256), 0, s, o, tgt, n, cls, bits, F, st);
+    hipLaunchKernelGGL((k_pull_flags<OffT, 256, kPullSmallWords, DECIDE>),
+                       dim3(grid_for(n, 256, 1024)), dim3(256), 0, s, o, tgt, n, cls, bits, F, st,
+                       pa);
   else if (words <= kPullBigWords)
-    hipLaunchKernelGGL((k_pull_flags<OffT, 1024, kPullBigWords>), dim3(grid_for(n, 1024, 256)),
-                       dim3(1024), 0, s, o, tgt, n, cls, bits, F, st);
-  else
-    hipLaunchKernelGGL((k_pull_flags<OffT, 256, 0>), dim3(grid_for(n, 256, 2048)), dim3(256), 0, s,
-                       o, tgt, n, cls, bits, F, st);
+    hipLaunchKernelGGL((k_pull_flags<OffT, 1024, kPullBigWords, DECIDE>),
+                       dim3(grid_for(n, 1024, 256)), dim3(1024), 0, s, o, tgt, n, cls, bits, F, st,
+                       pa);
+  else if constexpr (!DECIDE)
+    hipLaunchKernelGGL((k_pull_flags<OffT, 256, 0, false>), dim3(grid_for(n, 256, 2048)),
+                       dim3(256), 0, s, o, tgt, n, cls, bits, F, st, pa);
 }
 
 hipError_t launch_pull_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
                              const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F,
                              DevStats* st, hipStream_t s) {
-  if (off64) pull_flags<int64_t>(off, tgt, n, cls, chg_bits, F, st, s);
-  else pull_flags<int32_t>(off, tgt, n, cls, chg_bits, F, st, s);
+  if (off64) pull_flags<int64_t, false>(off, tgt, n, cls, chg_bits, F, st, PushArgs{}, s);
+  else pull_flags<int32_t, false>(off, tgt, n, cls, chg_bits, F, st, PushArgs{}, s);
+  return hipGetLastError();
+}
+
+bool flags_in_one_launch(int64_t n) { return (n + 31) / 32 <= kPullBigWords; }
+
+hipError_t launch_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
+                        const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F, DevStats* st,
+                        int32_t* const* lists, const uint8_t* chg, const FlagRule& rule,
+                        hipStream_t s) {
+  PushArgs pa;
+  for (int q = 0; q < kNumClasses; ++q) pa.lists.p[q] = lists[q];
+  pa.chg = chg;
+  pa.rule = rule;
+  if (off64) pull_flags<int64_t, true>(off, tgt, n, cls, chg_bits, F, st, pa, s);
+  else pull_flags<int32_t, true>(off, tgt, n, cls, chg_bits, F, st, pa, s);
   return hipGetLastError();
 }
 

@@ -125,6 +125,14 @@ struct DevState {
   alignas(512) unsigned long long slot[kStatSlots][kStatWords];
 };
 
+// Operands of the choice between pushed and pulled flags (k_flag_decide).
+struct FlagRule {
+  int64_t m;   // CSR entries
+  int64_t n;
+  int force;   // lpa_flag_mode
+  int pdiv;    // lpa_tuning.pull_divisor
+};
+
 // Learned-skipping parameters of a run (zero: plain run).
 struct LearnParams {
   int learn;
@@ -312,9 +320,11 @@ hipError_t launch_run_begin(DevStats* st, double tol, int cap, int rho, int batc
 hipError_t launch_arm_flags(uint8_t* F, int64_t n, const DevStats* st, hipStream_t s);
 // fold: add up the counters' copies first (iterations without launch_flag_decide)
 // progress: host memory that takes (run number << 32) | (stop << 31) |
-// iterations ended
+// iterations ended; rule: launch_flags' (NULL: launch_flag_decide ran); next:
+// begin the next iteration too, in place of launch_hub_plan
 hipError_t launch_iter_end(DevStats* st, DevIterStats* hist, int64_t n, bool fold,
-                           unsigned long long* progress, hipStream_t s);
+                           unsigned long long* progress, const FlagRule* rule, bool next,
+                           hipStream_t s);
 hipError_t launch_batch_step(const BatchArgs& b, const uint8_t* chg, uint8_t* F, DevStats* st,
                              hipStream_t s);
 hipError_t launch_batch_reset(const BatchArgs& b, hipStream_t s);
@@ -355,8 +365,15 @@ hipError_t launch_frontier_learned(int64_t n, int64_t n_later, uint8_t* F, const
                                    const TraceArgs& tr, int grid, hipStream_t s);
 hipError_t launch_trace_label(const DevStats* st, const uint8_t* chg, const TraceArgs& tr,
                               hipStream_t s);
-hipError_t launch_flag_decide(DevStats* st, int64_t m, int64_t n, int force, int pdiv,
-                              hipStream_t s);
+hipError_t launch_flag_decide(DevStats* st, const FlagRule& rule, hipStream_t s);
+// Decision, pushing and pulling in one launch, after launch_publish with pack
+// 2, for handles without hubs of at most flags_in_one_launch vertices;
+// launch_iter_end gets the same rule and folds.
+bool flags_in_one_launch(int64_t n);
+hipError_t launch_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
+                        const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F, DevStats* st,
+                        int32_t* const* lists, const uint8_t* chg, const FlagRule& rule,
+                        hipStream_t s);
 // Cross-Check (Sec. 4.1): save the labels before an iteration; one round of
 // the id-order revert decisions (st->cc_moved set when one changes; the host
 // repeats rounds until none does); apply the reverts.  perm/inv map caller
@@ -375,9 +392,9 @@ hipError_t launch_flags_resume(DevStats* st, hipStream_t s);
 hipError_t launch_flags_done(DevStats* st, hipStream_t s);
 // After the sweep: the changed vertices' labels copied from Cn to C (apply),
 // and chg packed into chg_bits ((n + 31) / 32 words) if this iteration's
-// flags are pulled (pack).
+// flags are pulled (pack 1) or in any case (2).
 hipError_t launch_publish(const DevStats* st, const uint8_t* chg, int64_t n, const int32_t* Cn,
-                          int32_t* C, uint32_t* chg_bits, bool apply, bool pack, hipStream_t s);
+                          int32_t* C, uint32_t* chg_bits, bool apply, int pack, hipStream_t s);
 // Pulls the flags, from the bits that launch_publish packed.
 hipError_t launch_pull_flags(bool off64, const void* off, const int32_t* tgt, int64_t n,
                              const uint8_t* cls, const uint32_t* chg_bits, uint8_t* F,
