@@ -164,8 +164,8 @@ typedef struct lpa_graph_s* lpa_graph;
  * queue_chunk: vertices per queue item, a power of two in 64 .. 1024
  *   (0 = default 512).
  * queue_group: rows of up to this many entries (16 .. 64, 0 = default 64)
- *   are processed by 16 lanes each with a 127-slot LDS table; longer rows
- *   by a wavefront each with a 1023-slot table.
+ *   are processed by 16 lanes each, equal labels matched over a hashed LDS
+ *   slot; longer rows by the whole workgroup with a 1023-slot table.
  * sort_rows: with the internal order (relabel), sort each row of the
  *   internal CSR by target id at create, so that the label reads of a row
  *   walk upwards through the label array and the entries in its dense

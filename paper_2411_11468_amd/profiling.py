@@ -37,8 +37,8 @@ CSRC = os.path.join(HERE, "csrc")
 _NAME_RULES = [
     (r"k_sweep_small<[^,]+, 4[,>]", "sweep_small4"),
     (r"k_sweep_small<[^,]+, 16[,>]", "sweep_small16"),
-    (r"k_sweep_small16x2<", "sweep_small16"),
-    (r"k_sweep_group<[^,]+, 127,", "sweep_wave127"),
+    (r"k_sweep_(small16x2|row16)<", "sweep_small16"),
+    (r"k_sweep_(group|row64)<", "sweep_wave127"),
     (r"k_sweep_wave_pipe<[^,]+, 1023,", "sweep_wave1023"),
     (r"k_sweep_block(_pipe)?<[^,]+, 2047,", "sweep_block2047"),
     (r"k_sweep_block(_pipe)?<[^,]+, 4095,", "sweep_block4095"),
@@ -74,7 +74,9 @@ _NAME_RULES = [
     (r"k_mlp_infer", "mlp_infer"),
     (r"k_mlp_grad", "mlp_grad"),
     (r"k_adam", "adam"),
-    (r"k_apply", "apply"),
+    (r"k_apply|k_publish<", "apply"),
+    # small graphs decide, push and pull in one launch
+    (r"k_pull_flags<[^>]+, true>", "flags"),
     (r"k_pull_flags<", "pull_flags"),
     (r"k_pull_hubs<", "pull_hubs"),
     (r"k_push_lists<", "push_flags"),
