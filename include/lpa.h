@@ -140,7 +140,8 @@ typedef struct lpa_graph_s* lpa_graph;
  *   (step doubled on each collision), 3 = double hashing (step key mod p2);
  *   every mode continues linearly after max_retries probes.  The same
  *   results; for measuring the probe sequences against each other.  Rows of
- *   up to 64 entries are summed without a probed table (table_values 0).
+ *   up to 256 entries (64 in a work-queue or learned run) are summed without
+ *   a probed table (table_values 0).
  * table_values: the precision of the hashtable values (Sec. 4.4 compares
  *   32- and 64-bit).  0 (default) = 32-bit, in every class kernel above.
  *   32 or 64 = 32- or 64-bit values in one simpler kernel set used for
@@ -179,8 +180,8 @@ typedef struct lpa_graph_s* lpa_graph;
  *   its load: 1 = nextPow2(D) - 1 (the smallest 2^m > D, minus one: the
  *   paper's, up to full load), 2 (default) = the smallest 2^m >= 2D, minus
  *   one (load <= 1/2), 4 = the smallest 2^m >= 4D, minus one (load <= 1/4),
- *   capped by the class's LDS table.  Same results.  Rows of more than 64
- *   entries.
+ *   capped by the class's LDS table.  Same results.  Rows that take a table
+ *   (see probe).
  * pull_divisor: the neighbour flags of an iteration are pulled (every vertex
  *   checks its row) when the changed rows hold at least 1/pull_divisor of
  *   the CSR entries, else pushed (each changed row flags its neighbours);

@@ -509,6 +509,58 @@ __device__ __forceinline__ void match_sums(const uint32_t (&lab)[U], const float
   }
 }
 
+// match_sums for a row of up to 64 U entries held by the wave, in a table of
+// at least 512 slots that is empty before and after: returns the lane's
+// largest packed (sum, label).
+template <int U>
+__device__ __forceinline__ unsigned long long match_wave(const uint32_t (&lab)[U],
+                                                         const float (&wt)[U], uint32_t* keys,
+                                                         float* vals) {
+  uint32_t x[U], left = 0;
+  unsigned long long best = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    x[u] = lab[u] * 0x9E3779B1u;
+    if (lab[u] != kEmpty) left |= 1u << u;
+  }
+  for (uint32_t sh = 23;; sh = sh >= 9 ? sh - 9 : 23) {
+    uint32_t h[U], hit = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      h[u] = (x[u] >> sh) & 511u;
+      if (left & (1u << u))
+        __hip_atomic_store(&keys[h[u]], lab[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    uint32_t got[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      got[u] = __hip_atomic_load(&keys[h[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if ((left & (1u << u)) && got[u] == lab[u]) {
+        hit |= 1u << u;
+        __hip_atomic_fetch_add(&vals[h[u]], wt[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    float sum[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      sum[u] = __hip_atomic_load(&vals[h[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (hit & (1u << u)) {
+        best = umax64(best, pack_key(sum[u], lab[u]));
+        __hip_atomic_store(&vals[h[u]], 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&keys[h[u]], kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    left &= ~hit;
+    if (!__any(left != 0u)) return best;
+  }
+}
+
 // Max within each 16-lane row of 32-bit keys, result in every lane of the row.
 __device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
 __device__ __forceinline__ uint32_t row16_max_u32(uint32_t x) {

@@ -504,9 +504,16 @@ struct RecPartial {
 // weights) before it scans and clears the current vertex's table, so that
 // those loads are in flight while the scan runs.  Labels are not
 // prefetched: they are read when the row is accumulated, as before.
+// A row whose entries all fit the wave's registers (256) is summed by
+// match_wave, four LDS steps a round for all of them, where the table takes
+// three in a row for each entry a lane holds and a pass over the claimed
+// slots: R-MAT 22 1.42 -> 1.33 ms a run, R-MAT 26 6.90 -> 6.79 (bound by the
+// label lines), LFR 1M 0.288 -> 0.278.  Longer rows and the learned variant,
+// whose record needs the table read back, keep the table.
 // FEAT: the learned variant, which also rewrites the state record.
 template <typename OffT, int SLOTS, int WAVES, int U, bool FEAT>
 __global__ __launch_bounds__(WAVES * 64) void k_sweep_wave_pipe(SweepArgs a) {
+  static_assert(SLOTS >= 512, "match_wave's slots");
   __shared__ uint32_t keys_all[WAVES][SLOTS];
   __shared__ float vals_all[WAVES][SLOTS];
   // per wave: the slots its current row claimed, read back instead of all
@@ -583,59 +590,67 @@ __global__ __launch_bounds__(WAVES * 64) void k_sweep_wave_pipe(SweepArgs a) {
       lab[u] = (j[u] != v) ? (id0 ? (uint32_t)j[u] : (uint32_t)a.C[j[u]]) : kEmpty;
     #pragma unroll
     for (int u = 0; u < U; ++u) merge_lead(lab[u], wt[u], a.w == nullptr);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      int32_t cl = -1;
-      if (lab[u] != kEmpty) {
-        cl = lds_accumulate_claim(keys, vals, p1, lab[u], wt[u], a.probe);
-        if constexpr (FEAT) rp.K += wt[u];
-      }
-      claim(cl);
-    }
-    for (int64_t base = 64 * U; base < d; base += 64 * U) {
-      int32_t jj[U];
-      float ww[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t e = base + u * 64 + lane;
-        const bool has = e < d;
-        jj[u] = has ? __builtin_nontemporal_load(&a.tgt[o + e]) : v;
-        ww[u] = has ? edge_weight(a.w, o + e) : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        lab[u] = (jj[u] != v) ? (id0 ? (uint32_t)jj[u] : (uint32_t)a.C[jj[u]]) : kEmpty;
-      #pragma unroll
-      for (int u = 0; u < U; ++u) merge_lead(lab[u], ww[u], a.w == nullptr);
+    // next vertex's head and the offsets of the one after, in flight during
+    // the matching or the scan below
+    int32_t nj[U];
+    float nw[U];
+    int64_t o2 = 0, e2 = 0;
+    auto next = [&]() {
+      if (nitem < count) head(v1, o1, e1 - o1, nj, nw);
+      if (n2item < count) row_bounds<OffT>(a.off, v2, &o2, &e2);
+    };
+    unsigned long long best = 0;
+    if (!FEAT && d <= 64 * U) {
+      next();
+      best = match_wave<U>(lab, wt, keys, vals);
+    } else {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int32_t cl = -1;
         if (lab[u] != kEmpty) {
-          cl = lds_accumulate_claim(keys, vals, p1, lab[u], ww[u], a.probe);
-          if constexpr (FEAT) rp.K += ww[u];
+          cl = lds_accumulate_claim(keys, vals, p1, lab[u], wt[u], a.probe);
+          if constexpr (FEAT) rp.K += wt[u];
         }
         claim(cl);
       }
+      for (int64_t base = 64 * U; base < d; base += 64 * U) {
+        int32_t jj[U];
+        float ww[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t e = base + u * 64 + lane;
+          const bool has = e < d;
+          jj[u] = has ? __builtin_nontemporal_load(&a.tgt[o + e]) : v;
+          ww[u] = has ? edge_weight(a.w, o + e) : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          lab[u] = (jj[u] != v) ? (id0 ? (uint32_t)jj[u] : (uint32_t)a.C[jj[u]]) : kEmpty;
+        #pragma unroll
+        for (int u = 0; u < U; ++u) merge_lead(lab[u], ww[u], a.w == nullptr);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          int32_t cl = -1;
+          if (lab[u] != kEmpty) {
+            cl = lds_accumulate_claim(keys, vals, p1, lab[u], ww[u], a.probe);
+            if constexpr (FEAT) rp.K += ww[u];
+          }
+          claim(cl);
+        }
+      }
+      next();
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      for (uint32_t i = lane; i < nl; i += 64) {
+        const uint32_t s = lst[i];
+        const uint32_t kk = keys[s];
+        const unsigned long long pk = pack_key(vals[s], kk);
+        if constexpr (FEAT) rp.slot(pk, kk, vals[s], cur);
+        best = umax64(best, pk);
+        keys[s] = kEmpty;
+        vals[s] = 0.0f;
+      }
+      nl = 0;
     }
-    // next vertex's head and the offsets of the one after, in flight during
-    // the scan below
-    int32_t nj[U];
-    float nw[U];
-    if (nitem < count) head(v1, o1, e1 - o1, nj, nw);
-    int64_t o2 = 0, e2 = 0;
-    if (n2item < count) row_bounds<OffT>(a.off, v2, &o2, &e2);
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    unsigned long long best = 0;
-    for (uint32_t i = lane; i < nl; i += 64) {
-      const uint32_t s = lst[i];
-      const uint32_t kk = keys[s];
-      const unsigned long long pk = pack_key(vals[s], kk);
-      if constexpr (FEAT) rp.slot(pk, kk, vals[s], cur);
-      best = umax64(best, pk);
-      keys[s] = kEmpty;
-      vals[s] = 0.0f;
-    }
-    nl = 0;
     best = wave_max_u64(best);
     uint32_t cstar = 0;
     const bool moved = decide(best, cur, pl, &cstar);
