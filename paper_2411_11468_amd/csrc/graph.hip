@@ -1384,6 +1384,15 @@ __device__ __forceinline__ int4 load_four(const int32_t* tgt, int64_t p, int64_t
   return j;
 }
 
+constexpr int kPullSmallWords = 8192, kPullBigWords = 38912;
+// Vertices per wave and step.  A small graph has waves to spare: 16, so that
+// the rows left unresolved take one round of the wave (10 000 vertices, longest
+// pull of a run: 13.5 -> 7.8 us; 20 011: 20.5 -> 17.3).
+template <int WORDS>
+__host__ __device__ constexpr int pull_rows(int64_t n) {
+  return WORDS == kPullSmallWords && n <= 65536 ? 16 : 64;
+}
+
 // WORDS > 0: the bits are copied to LDS first (n <= 32 WORDS), where a lookup
 // costs a few cycles a wave instead of the address unit's 64 (LFR, 1 M
 // vertices, 20 M entries: 87 -> 61 us in the longest pull of a run).  From
@@ -1460,11 +1469,12 @@ __global__ __launch_bounds__(BT, WORDS ? 1 : 8) void k_pull_flags(const OffT* of
   // internal order's rows sorted by target, the last entries are the
   // lowest-degree neighbours, which are the ones that still change late in a
   // run (from the start: 0.58 -> 0.89 ms per launch on R-MAT 26)
-  for (int64_t base = wave * 64; base < n; base += nwaves * 64) {
+  const int per = pull_rows<WORDS>(n);
+  for (int64_t base = wave * per; base < n; base += nwaves * per) {
     const int64_t v = base + lane;
     OffT o = 0;
     int32_t d = 0;  // a hub's row is scanned by k_pull_hubs
-    if (v < n && cls[v] != kClassHub) {
+    if (lane < per && v < n && cls[v] != kClassHub) {
       o = off[v];
       d = (int32_t)(off[v + 1] - o);
     }
@@ -1605,8 +1615,6 @@ __global__ __launch_bounds__(kBT) void k_pull_hubs(const OffT* off, const int32_
 // Where the bits go: graphs of up to 2^18 vertices keep them in 32 KB of LDS,
 // four workgroups and more to a CU; of up to 1.2 M in 152 KB, one workgroup
 // of 16 waves to a CU; larger graphs read them from memory.
-constexpr int kPullSmallWords = 8192, kPullBigWords = 38912;
-
 template <typename OffT, bool DECIDE>
 static void pull_flags(const void* off, const int32_t* tgt, int64_t n, const uint8_t* cls,
                        const uint32_t* bits, uint8_t* F, DevStats* st, const PushArgs& pa,
@@ -1615,8 +1623,8 @@ static void pull_flags(const void* off, const int32_t* tgt, int64_t n, const uin
   const int64_t words = (n + 31) / 32;
   if (words <= kPullSmallWords)
     hipLaunchKernelGGL((k_pull_flags<OffT, 256, kPullSmallWords, DECIDE>),
-                       dim3(grid_for(n, 256, 1024)), dim3(256), 0, s, o, tgt, n, cls, bits, F, st,
-                       pa);
+                       dim3(grid_for(n, 4 * pull_rows<kPullSmallWords>(n), 1024)), dim3(256), 0, s, o,
+                       tgt, n, cls, bits, F, st, pa);
   else if (words <= kPullBigWords)
     hipLaunchKernelGGL((k_pull_flags<OffT, 1024, kPullBigWords, DECIDE>),
                        dim3(grid_for(n, 1024, 256)), dim3(1024), 0, s, o, tgt, n, cls, bits, F, st,
