@@ -43,8 +43,10 @@ struct AdamStep {
   float lr, beta1, omb1, beta2, omb2, eps, c1, c2;
 };
 
-// Gradients of a minibatch by workgroup: at most kMlpMaxParts of
-// kMlpPartStride floats.
+// Gradients of a minibatch by workgroup of kGradSamples samples (and of
+// further groups of as many from kMlpMaxParts workgroups on): at most
+// kMlpMaxParts of kMlpPartStride floats.
+constexpr int kGradSamples = 64;
 constexpr int kMlpPartStride = 5120;
 constexpr int kMlpMaxParts = 512;
 static_assert(kMlpParams <= kMlpPartStride, "part stride");
@@ -157,18 +159,19 @@ __device__ inline float mlp_logit16(const MlpLane& r, const float f[4]) {
 }
 
 // Gradient of the mean loss of B >= 1 samples (idx: samples idx[0 .. B-1] of X
-// and y; NULL: the first B) in mlp_grad_parts(B) parts, and the samples'
-// losses (B floats; *loss cleared unless add); then the parts summed into g
-// and the losses added to *loss; the same with one Adam step.
+// and y; NULL: the first B) in mlp_grad_parts(B) parts, and the losses of each
+// kGradSamples samples (mlp_grad_losses(B) floats); then the parts summed into
+// g and the losses into *loss; the same with one Adam step (add: on top of
+// *loss).
 int mlp_grad_parts(int64_t B);
+int64_t mlp_grad_losses(int64_t B);
 hipError_t launch_mlp_grad(const float* p, const float* X, const float* y, const int32_t* idx,
-                           int64_t B, float pos_weight, float* part, float* ploss, double* loss,
-                           bool add, hipStream_t s);
+                           int64_t B, float pos_weight, float* part, float* ploss, hipStream_t s);
 hipError_t launch_mlp_reduce(const float* part, const float* ploss, int64_t B, float* g,
                              double* loss, hipStream_t s);
 hipError_t launch_mlp_reduce_step(const float* part, const float* ploss, int64_t B, float* g,
-                                  double* loss, float* p, float* m, float* v, int t, float lr,
-                                  hipStream_t s);
+                                  double* loss, bool add, float* p, float* m, float* v, int t,
+                                  float lr, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int t, float lr,
                        hipStream_t s);
 hipError_t launch_fill_zero(float* x, int n, hipStream_t s);

@@ -7,7 +7,7 @@
 //
 //   k_mlp_grad    forward + backward of a minibatch in fp32 on bf16-rounded
 //                 weights and inputs, on v_mfma_f32_16x16x4_f32; each
-//                 workgroup writes the gradient of its samples
+//                 workgroup writes the gradient of its 64 samples
 //   k_mlp_reduce  sums the workgroups' gradients (and losses) in fp64 and,
 //                 in training, takes the Adam step on the sum
 //   k_adam        one Adam step (Kingma & Ba 2015) with bias correction
@@ -30,67 +30,65 @@ constexpr int oW1 = 0, ob1 = oW1 + kIn * kH, oW2 = ob1 + kH, ob2 = oW2 + kH * kH
               oW3 = ob2 + kH, ob3 = oW3 + kH;
 static_assert(ob3 + 1 == kMlpParams, "parameter count");
 
-constexpr int kGradSamples = 32;  // samples per workgroup and round
-constexpr int kGradTiles = kGradSamples / 16;
-constexpr int kGradThreads = 256;
+constexpr int kGradTiles = 2;     // of 16 samples per wave
+constexpr int kGradThreads = 512;
 constexpr int kGradStride = 80;   // floats between two samples' units in LDS
 constexpr int kH2Stride = 68;     // the same for reads of one sample per lane
+static_assert(kGradSamples == 2 * 16 * kGradTiles, "a wave half per half of the samples");
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-// Sum over the 16 lanes of a DPP row, in every lane of it.
-__device__ __forceinline__ float dpp_row_sum(float x) {
-  x += __shfl_xor(x, 1);
-  x += __shfl_xor(x, 2);
-  x += __shfl_xor(x, 4);
-  x += __shfl_xor(x, 8);
-  return x;
-}
 
 }  // namespace
 
 // ---- training -------------------------------------------------------------------
 // Forward and backward pass of the samples s0, s0 + 1, ... (idx: through this
-// list), kGradSamples per workgroup and round; the workgroup's gradient goes
-// to part + blockIdx.x * kMlpPartStride, each sample's loss to loss[], and
-// *total is cleared for the reduction unless add.
+// list), kGradSamples = 64 per workgroup and round; the workgroup's gradient
+// goes to part + blockIdx.x * kMlpPartStride, the loss of each 64 samples to
+// loss[].
 //
-// The four waves share the samples and split the hidden units: wave w has
-// units 16 w .. 16 w + 15 of every layer.  All products run as 16 x 16 tiles
-// of v_mfma_f32_16x16x4_f32 (fp32 operands and sums, as before on the vector
-// units) with the units as rows and the samples as columns, so that lane
-// (j, k) = (lane % 16, lane / 16) holds units 16 w + 4 k + r, r = 0 .. 3, of
-// sample j.  The forward sums run over the inputs in their order, one fused
-// multiply-add after the other, so that a sample's logit and loss do not
-// depend on how the samples are split; the backward product over the units
-// takes them in the order 16 m + 4 k + r that one 16-byte read per four
-// products gives.  The weight gradients sum over samples: there the samples
-// are the inner dimension, and both operands are read from LDS with a stride
-// of 80 floats, which spreads the four sample rows of a read over different
-// banks.  A wave's weights (the W2 columns and rows of its units) and
-// gradient tiles stay in registers over the rounds.
+// Training amplifies a gradient's last bit (the weights are rounded to bf16 at
+// every step: one ulp of a master weight near a rounding boundary moves the
+// next gradient by 2^-9 of that weight), so the order of every sum is part of
+// what the kernel computes: per output one chain of fused multiply-adds, over
+// the inputs in the forward products, over the units in da1, and in every
+// weight and bias gradient over the 64 samples in their order.
+// v_mfma_f32_16x16x4_f32 is such a chain over its four k (fp32 operands and
+// sums), so all products run as its 16 x 16 tiles, and a sum of plain values
+// has ones as its other operand.
 //
-// It is bound by latency at a minibatch's size (4,096 samples are one round
-// of 128 workgroups: 110 products of 32 cycles per wave between five
-// barriers).  Measured there: 37 us with scalar LDS loops and 5,057 atomic
-// adds per workgroup, 16 us with this kernel and 4 us for k_mlp_reduce; 10^6
-// samples 1.3 -> 0.4 ms.
+// The eight waves are four unit groups (units 16 u .. 16 u + 15 of every layer)
+// times two halves of the samples.  In the products over inputs and units the
+// units are rows and the samples columns, so that lane (j, k) = (lane % 16,
+// lane / 16) holds units 16 u + 4 k + r, r = 0 .. 3, of sample j of a tile.
+// In the gradients the samples are the inner dimension: the halves then split
+// the rows of W2's, and at the end one half takes W1 and b1 (the row of ones
+// that W1's 12 inputs leave free), the other W3 and b2.  Samples lie 80 floats
+// apart in LDS, which spreads the four sample rows of a read over different
+// banks.  A wave's weights and gradient tiles stay in registers over the rounds.
+//
+// It is bound by latency at a minibatch's size: 4,096 samples are one round of
+// 64 workgroups, 128 to 144 products of 32 cycles per wave between six
+// barriers.  Four waves and 32 samples a workgroup, summed in another order,
+// had as many products per wave on twice the CUs.
 __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(
     const float* __restrict__ p, const float* __restrict__ X, const float* __restrict__ y,
     const int32_t* __restrict__ idx, int64_t B, float inv_total, float pos_weight,
-    float* __restrict__ part, float* __restrict__ loss, double* total, int add) {
+    float* __restrict__ part, float* __restrict__ loss) {
   __shared__ __align__(16) float h1s[kGradSamples * kGradStride];   // later da1
   __shared__ __align__(16) float da2s[kGradSamples * kGradStride];
   __shared__ __align__(16) float h2s[kGradSamples * kH2Stride];
   __shared__ __align__(16) float w3s[kH];
   __shared__ float xs[kGradSamples][kIn + 1];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, u = (tid >> 6) & 3, half = tid >> 8;
   const int j = lane & 15, k = lane >> 4;
+  const int c0 = 16 * u + j;                       // the lane's column in a gradient tile
+  const int sm0 = 16 * kGradTiles * half + j;      // the lane's sample in the first tile
   // a round's features and targets, loaded a round ahead: the thread's share of
-  // xs, and in lanes 0 .. 31 of every wave the sample's target
+  // xs, and in every wave the target of sample lane
   constexpr int kX = (kGradSamples * kIn + kGradThreads - 1) / kGradThreads;
   float xv[kX], tn = 0.0f;
   auto fetch = [&](int64_t s0) {
@@ -103,40 +101,34 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(
       row[q] = s < B ? s : last;
       if (idx) row[q] = idx[row[q]];
     }
-    ty = s0 + (lane & 31) < B ? s0 + (lane & 31) : last;
+    ty = s0 + lane < B ? s0 + lane : last;
     if (idx) ty = idx[ty];
 #pragma unroll
     for (int q = 0; q < kX; ++q) xv[q] = X[row[q] * kIn + (tid + q * kGradThreads) % kIn];
     tn = y[ty];
   };
   fetch((int64_t)blockIdx.x * kGradSamples);
-  // the wave's weights: w1a[q] = W1[4 q + k][16 w + j]; w2f[q] = W2[4 q + k][16 w
-  // + j]; w2b[m][r] = W2[16 w + j][16 m + 4 k + r]
-  float w1a[3], w2f[16], w2b[4][4];
+  // the wave's weights: w1a[q] = W1[4 q + k][c0]; w2f[q] = W2[4 q + k][c0];
+  // w2b[q] = W2[c0][4 q + k]
+  float w1a[3], w2f[16], w2b[16];
   v4f b1v, b2v, w3v;
 #pragma unroll
-  for (int q = 0; q < 3; ++q) w1a[q] = bf16_round(p[oW1 + (4 * q + k) * kH + 16 * w + j]);
+  for (int q = 0; q < 3; ++q) w1a[q] = bf16_round(p[oW1 + (4 * q + k) * kH + c0]);
 #pragma unroll
-  for (int q = 0; q < 16; ++q) w2f[q] = bf16_round(p[oW2 + (4 * q + k) * kH + 16 * w + j]);
+  for (int q = 0; q < 16; ++q) w2f[q] = bf16_round(p[oW2 + (4 * q + k) * kH + c0]);
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      w2b[m][r] = bf16_round(p[oW2 + (16 * w + j) * kH + 16 * m + 4 * k + r]);
-    }
+  for (int q = 0; q < 16; ++q) w2b[q] = bf16_round(p[oW2 + c0 * kH + 4 * q + k]);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    b1v[r] = p[ob1 + 16 * w + 4 * k + r];
-    b2v[r] = p[ob2 + 16 * w + 4 * k + r];
-    w3v[r] = bf16_round(p[oW3 + 16 * w + 4 * k + r]);
+    b1v[r] = p[ob1 + 16 * u + 4 * k + r];
+    b2v[r] = p[ob2 + 16 * u + 4 * k + r];
+    w3v[r] = bf16_round(p[oW3 + 16 * u + 4 * k + r]);
   }
   if (tid < kH) w3s[tid] = bf16_round(p[oW3 + tid]);
-  if (blockIdx.x == 0 && tid == 0 && !add) *total = 0.0;
   const float b3 = p[ob3];
   const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  v4f g2[4] = {zero, zero, zero, zero}, g1 = zero;  // rows 16 m + 4 k + r, column 16 w + j
-  v4f gb1 = zero, gb2 = zero, g3 = zero;            // units 16 w + 4 k + r, of column j
-  float gb3 = 0.0f;
+  v4f g2[2] = {zero, zero};        // W2: rows 32 half + 16 m + 4 k + r, column c0
+  v4f ga = zero, gb = zero;        // half 0: W1 and b1, b3; half 1: W3, b2
   for (int64_t s0 = (int64_t)blockIdx.x * kGradSamples; s0 < B;
        s0 += (int64_t)gridDim.x * kGradSamples) {
     const int ns = (int)((B - s0) < kGradSamples ? (B - s0) : kGradSamples);
@@ -145,7 +137,7 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(
       const int i = tid + q * kGradThreads;
       if (i < kGradSamples * kIn) xs[i / kIn][i % kIn] = i / kIn < ns ? bf16_round(xv[q]) : 0.0f;
     }
-    const float t = tn;  // target of sample lane (lanes 0 .. 31)
+    const float t = tn;  // target of sample lane
     const int64_t next = s0 + (int64_t)gridDim.x * kGradSamples;
     if (next < B) fetch(next);
     __syncthreads();
@@ -153,125 +145,130 @@ __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(
     v4f h1[kGradTiles];
 #pragma unroll
     for (int a = 0; a < kGradTiles; ++a) {
+      const int sm = sm0 + 16 * a;
       v4f acc = b1v;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) acc = mfma4(w1a[q], xs[16 * a + j][4 * q + k], acc);
+      for (int q = 0; q < 3; ++q) acc = mfma4(w1a[q], xs[sm][4 * q + k], acc);
 #pragma unroll
       for (int r = 0; r < 4; ++r) h1[a][r] = fmaxf(acc[r], 0.0f);
-      *reinterpret_cast<v4f*>(&h1s[(16 * a + j) * kGradStride + 16 * w + 4 * k]) = h1[a];
+      *reinterpret_cast<v4f*>(&h1s[sm * kGradStride + 16 * u + 4 * k]) = h1[a];
     }
     __syncthreads();
     // layer 2
     v4f h2[kGradTiles];
 #pragma unroll
     for (int a = 0; a < kGradTiles; ++a) {
+      const int sm = sm0 + 16 * a;
       v4f acc = b2v;
 #pragma unroll
-      for (int q = 0; q < 16; ++q)
-        acc = mfma4(w2f[q], h1s[(16 * a + j) * kGradStride + 4 * q + k], acc);
+      for (int q = 0; q < 16; ++q) acc = mfma4(w2f[q], h1s[sm * kGradStride + 4 * q + k], acc);
 #pragma unroll
       for (int r = 0; r < 4; ++r) h2[a][r] = fmaxf(acc[r], 0.0f);
-      *reinterpret_cast<v4f*>(&h2s[(16 * a + j) * kH2Stride + 16 * w + 4 * k]) = h2[a];
+      *reinterpret_cast<v4f*>(&h2s[sm * kH2Stride + 16 * u + 4 * k]) = h2[a];
     }
     __syncthreads();
-    // logit and d loss / d logit of sample lane, in lanes 0 .. 31 of every wave
-    float dz = 0.0f;
-    if (lane < ns && lane < kGradSamples) {
+    // logit and d loss / d logit of sample lane, in every wave
+    float dz = 0.0f, my_loss = 0.0f;
+    if (lane < ns) {
       float z = b3;
 #pragma unroll
-      for (int u = 0; u < kH; u += 4) {
-        const v4f h = *reinterpret_cast<const v4f*>(&h2s[lane * kH2Stride + u]);
-        const v4f c = *reinterpret_cast<const v4f*>(&w3s[u]);
+      for (int i = 0; i < kH; i += 4) {
+        const v4f h = *reinterpret_cast<const v4f*>(&h2s[lane * kH2Stride + i]);
+        const v4f c = *reinterpret_cast<const v4f*>(&w3s[i]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) z += h[r] * c[r];
       }
       const float sg = 1.0f / (1.0f + __expf(-z));
       // d/dz of -[pw t log s + (1 - t) log(1 - s)]
       dz = (pos_weight * t * (sg - 1.0f) + (1.0f - t) * sg) * inv_total;
-      if (w == 0) {
+      if (tid < 64) {
         // log sigmoid(z) and log(1 - sigmoid(z)), stable
         const float ls = -(fmaxf(-z, 0.0f) + log1pf(__expf(-fabsf(z))));
         const float l1s = -(fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z))));
-        loss[s0 + lane] = -(pos_weight * t * ls + (1.0f - t) * l1s);
+        my_loss = -(pos_weight * t * ls + (1.0f - t) * l1s);
       }
     }
-    gb3 += dz;
+    if (tid < 64) {
+      for (int ofs = 32; ofs > 0; ofs >>= 1) my_loss += __shfl_xor(my_loss, ofs);
+      if (lane == 0) loss[s0 / kGradSamples] = my_loss;
+    }
     // da2 = dz W3 [h2 > 0]
 #pragma unroll
     for (int a = 0; a < kGradTiles; ++a) {
-      const float d = __shfl(dz, 16 * a + j);
+      const int sm = sm0 + 16 * a;
+      const float d = __shfl(dz, sm);
       v4f da2;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        g3[r] += h2[a][r] * d;
-        da2[r] = h2[a][r] > 0.0f ? d * w3v[r] : 0.0f;
-        gb2[r] += da2[r];
-      }
-      *reinterpret_cast<v4f*>(&da2s[(16 * a + j) * kGradStride + 16 * w + 4 * k]) = da2;
+      for (int r = 0; r < 4; ++r) da2[r] = h2[a][r] > 0.0f ? d * w3v[r] : 0.0f;
+      *reinterpret_cast<v4f*>(&da2s[sm * kGradStride + 16 * u + 4 * k]) = da2;
     }
     __syncthreads();
-    // W2 gradient, the wave's columns: sum over samples of h1[s][.] da2[s][.]
+    // W2 gradient, the wave's columns and half of the rows: sum over samples of
+    // h1[s][.] da2[s][.]
 #pragma unroll
     for (int q = 0; q < kGradSamples / 4; ++q) {
-      const float b = da2s[(4 * q + k) * kGradStride + 16 * w + j];
+      const float b = da2s[(4 * q + k) * kGradStride + c0];
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-        g2[m] = mfma4(h1s[(4 * q + k) * kGradStride + 16 * m + j], b, g2[m]);
+      for (int m = 0; m < 2; ++m)
+        g2[m] = mfma4(h1s[(4 * q + k) * kGradStride + 32 * half + 16 * m + j], b, g2[m]);
     }
-    // da1 = da2 W2^T [h1 > 0], the wave's units
+    // da1 = da2 W2^T [h1 > 0], the wave's units and samples
     v4f da1[kGradTiles];
 #pragma unroll
     for (int a = 0; a < kGradTiles; ++a) {
       v4f acc = zero;
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const v4f b = *reinterpret_cast<const v4f*>(
-            &da2s[(16 * a + j) * kGradStride + 16 * m + 4 * k]);
+      for (int q = 0; q < 16; ++q)
+        acc = mfma4(w2b[q], da2s[(sm0 + 16 * a) * kGradStride + 4 * q + k], acc);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc = mfma4(w2b[m][r], b[r], acc);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        da1[a][r] = h1[a][r] > 0.0f ? acc[r] : 0.0f;
-        gb1[r] += da1[a][r];
-      }
+      for (int r = 0; r < 4; ++r) da1[a][r] = h1[a][r] > 0.0f ? acc[r] : 0.0f;
     }
     __syncthreads();  // every wave has read h1s
 #pragma unroll
     for (int a = 0; a < kGradTiles; ++a)
-      *reinterpret_cast<v4f*>(&h1s[(16 * a + j) * kGradStride + 16 * w + 4 * k]) = da1[a];
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    // W1 gradient, the wave's columns (written by the wave itself)
+      *reinterpret_cast<v4f*>(&h1s[(sm0 + 16 * a) * kGradStride + 16 * u + 4 * k]) = da1[a];
+    __syncthreads();
+    if (half == 0) {
+      // rows 0 .. 11: W1 gradient, the wave's columns; row 12: b1's; and b3's
 #pragma unroll
-    for (int q = 0; q < kGradSamples / 4; ++q)
-      g1 = mfma4(j < kIn ? xs[4 * q + k][j] : 0.0f,
-                 h1s[(4 * q + k) * kGradStride + 16 * w + j], g1);
-    __syncthreads();  // xs, h1s and h2s are rewritten by the next round
+      for (int q = 0; q < kGradSamples / 4; ++q) {
+        const float a = j < kIn ? xs[4 * q + k][j] : (j == kIn ? 1.0f : 0.0f);
+        ga = mfma4(a, h1s[(4 * q + k) * kGradStride + c0], ga);
+        if (u == 0) gb = mfma4(1.0f, __shfl(dz, 4 * q + k), gb);
+      }
+    } else {
+      // W3 and b2 gradients of the wave's units, the same in every column
+#pragma unroll
+      for (int q = 0; q < kGradSamples / 4; ++q) {
+        ga = mfma4(h2s[(4 * q + k) * kH2Stride + c0], __shfl(dz, 4 * q + k), ga);
+        gb = mfma4(da2s[(4 * q + k) * kGradStride + c0], 1.0f, gb);
+      }
+    }
+    __syncthreads();  // the LDS arrays are rewritten by the next round
   }
   float* out = part + (size_t)blockIdx.x * kMlpPartStride;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    if (4 * k + r < kIn) out[oW1 + (4 * k + r) * kH + 16 * w + j] = g1[r];
+    const int row = 4 * k + r;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) out[oW2 + (16 * m + 4 * k + r) * kH + 16 * w + j] = g2[m][r];
-    const float x1 = dpp_row_sum(gb1[r]), x2 = dpp_row_sum(gb2[r]), x3 = dpp_row_sum(g3[r]);
-    if (j == 0) {
-      const int u = 16 * w + 4 * k + r;
-      out[ob1 + u] = x1;
-      out[ob2 + u] = x2;
-      out[oW3 + u] = x3;
+    for (int m = 0; m < 2; ++m) out[oW2 + (32 * half + 16 * m + row) * kH + c0] = g2[m][r];
+    if (half == 0) {
+      if (row < kIn) out[oW1 + row * kH + c0] = ga[r];
+      if (row == kIn) out[ob1 + c0] = ga[r];
+    } else if (j == 0) {
+      out[oW3 + 16 * u + row] = ga[r];
+      out[ob2 + 16 * u + row] = gb[r];
     }
   }
-  if (w == 0) {
-    for (int ofs = 32; ofs > 0; ofs >>= 1) gb3 += __shfl_xor(gb3, ofs);
-    if (lane == 0) out[ob3] = gb3;
-  }
+  if (tid == 0) out[ob3] = gb[0];
 }
 
+// The products that are rounded and those that are fused are written out: the
+// compiler's choice differs from kernel to kernel.
 __device__ __forceinline__ void adam_update(float* p, float* m, float* v, int i, float gi,
                                             const AdamStep& a) {
-  const float mi = a.beta1 * m[i] + a.omb1 * gi;
-  const float vi = a.beta2 * v[i] + a.omb2 * gi * gi;
+  const float mi = fmaf(a.omb1, gi, a.beta1 * m[i]);
+  const float vi = fmaf(gi, a.omb2 * gi, a.beta2 * v[i]);
   m[i] = mi;
   v[i] = vi;
   p[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
@@ -279,13 +276,13 @@ __device__ __forceinline__ void adam_update(float* p, float* m, float* v, int i,
 
 // The gradient from the parts of np workgroups, summed in fp64: 64 parameters
 // per workgroup, the parts split over its four waves.  STEP: also the Adam
-// step.  The losses of the B samples are added to *loss, in fp32 over each 64
-// consecutive samples and in fp64 over those.
+// step.  The first workgroup sums the nl losses in fp64: to *loss, or (add) on
+// top of it.  Every sum is in a fixed order.
 template <bool STEP>
 __global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ part,
                                                     const float* __restrict__ ploss, int np,
-                                                    int64_t B, float* g, double* loss, float* p,
-                                                    float* m, float* v, AdamStep a) {
+                                                    int64_t nl, float* g, double* loss, int add,
+                                                    float* p, float* m, float* v, AdamStep a) {
   __shared__ double sums[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
@@ -308,13 +305,15 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ pa
     g[i] = gi;
     if constexpr (STEP) adam_update(p, m, v, i, gi, a);
   }
+  if (blockIdx.x != 0) return;
   double t = 0.0;
-  for (int64_t s0 = ((int64_t)blockIdx.x * 4 + w) * 64; s0 < B; s0 += (int64_t)gridDim.x * 256) {
-    float x = s0 + lane < B ? ploss[s0 + lane] : 0.0f;
-    for (int ofs = 32; ofs > 0; ofs >>= 1) x += __shfl_xor(x, ofs);
-    t += (double)x;
-  }
-  if (lane == 0 && t != 0.0) atomicAdd(loss, t);
+  for (int64_t q = threadIdx.x; q < nl; q += 256) t += (double)ploss[q];
+  for (int ofs = 32; ofs > 0; ofs >>= 1) t += __shfl_xor(t, ofs);
+  __syncthreads();
+  if (lane == 0) sums[w][0] = t;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *loss = (add ? *loss : 0.0) + (sums[0][0] + sums[1][0] + sums[2][0] + sums[3][0]);
 }
 
 __global__ void k_adam(float* p, const float* g, float* m, float* v, int n, AdamStep a) {
@@ -398,8 +397,10 @@ hipError_t launch_fill_zero(float* x, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+int64_t mlp_grad_losses(int64_t B) { return (B + kGradSamples - 1) / kGradSamples; }
+
 int mlp_grad_parts(int64_t B) {
-  const int64_t g = (B + kGradSamples - 1) / kGradSamples;
+  const int64_t g = mlp_grad_losses(B);
   return (int)(g < kMlpMaxParts ? g : kMlpMaxParts);
 }
 
@@ -420,26 +421,27 @@ static AdamStep adam_step(int t, float lr) {
 }
 
 hipError_t launch_mlp_grad(const float* p, const float* X, const float* y, const int32_t* idx,
-                           int64_t B, float pos_weight, float* part, float* ploss, double* loss,
-                           bool add, hipStream_t s) {
+                           int64_t B, float pos_weight, float* part, float* ploss, hipStream_t s) {
   if (B <= 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)mlp_grad_parts(B)), dim3(kGradThreads), 0, s, p,
-                     X, y, idx, B, 1.0f / (float)B, pos_weight, part, ploss, loss, add ? 1 : 0);
+                     X, y, idx, B, 1.0f / (float)B, pos_weight, part, ploss);
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_reduce(const float* part, const float* ploss, int64_t B, float* g,
                              double* loss, hipStream_t s) {
   hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((kMlpParams + 63) / 64), dim3(256), 0, s, part,
-                     ploss, mlp_grad_parts(B), B, g, loss, nullptr, nullptr, nullptr, AdamStep{});
+                     ploss, mlp_grad_parts(B), mlp_grad_losses(B), g, loss, 0, nullptr, nullptr,
+                     nullptr, AdamStep{});
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_reduce_step(const float* part, const float* ploss, int64_t B, float* g,
-                                  double* loss, float* p, float* m, float* v, int t, float lr,
-                                  hipStream_t s) {
+                                  double* loss, bool add, float* p, float* m, float* v, int t,
+                                  float lr, hipStream_t s) {
   hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((kMlpParams + 63) / 64), dim3(256), 0, s, part,
-                     ploss, mlp_grad_parts(B), B, g, loss, p, m, v, adam_step(t, lr));
+                     ploss, mlp_grad_parts(B), mlp_grad_losses(B), g, loss, add ? 1 : 0, p, m, v,
+                     adam_step(t, lr));
   return hipGetLastError();
 }
 

@@ -26,7 +26,7 @@ struct lpa_predictor_s {
   float* v = nullptr;      // Adam second moment
   double* loss = nullptr;  // summed loss of the last gradient
   float* part = nullptr;   // gradients by workgroup
-  float* ploss = nullptr;  // the samples' losses (loss_cap of them)
+  float* ploss = nullptr;  // losses of each 64 samples (loss_cap of them)
   int64_t loss_cap = 0;
   uint8_t host[kGradBytes];  // a gradient and its loss read back
   MlpTiles* tiles = nullptr;
@@ -44,8 +44,9 @@ struct lpa_predictor_s {
 namespace {
 
 // Room for the losses of n samples at a time.
-constexpr int64_t kLossCap = 8192;
-lpa_status loss_space(lpa_predictor p, int64_t n) {
+constexpr int64_t kLossCap = 1024;
+lpa_status loss_space(lpa_predictor p, int64_t samples) {
+  const int64_t n = mlp_grad_losses(samples);
   if (n <= p->loss_cap) return LPA_OK;
   float* q = nullptr;
   if (hipMalloc(&q, sizeof(float) * (size_t)n) != hipSuccess) {
@@ -269,8 +270,8 @@ lpa_status lpa_predictor_gradient(lpa_predictor p, const float* X, const float* 
   if (lpa_status e = to_device(y, (size_t)n, &dy, &st.bufs, p->stream)) return e;
   if (lpa_status e = loss_space(p, n)) return e;
   if (n > 0) {
-    LPA_HIP(launch_mlp_grad(p->p, dX, dy, nullptr, n, pos_weight, p->part, p->ploss, p->loss,
-                            false, p->stream));
+    LPA_HIP(launch_mlp_grad(p->p, dX, dy, nullptr, n, pos_weight, p->part, p->ploss,
+                            p->stream));
     LPA_HIP(launch_mlp_reduce(p->part, p->ploss, n, p->g, p->loss, p->stream));
   } else {
     LPA_HIP(launch_fill_zero(p->g, kMlpParams, p->stream));
@@ -331,10 +332,10 @@ lpa_status lpa_predictor_train(lpa_predictor p, const float* X, const float* y, 
     for (int64_t b0 = 0; b0 < n; b0 += opt->batch) {
       const int64_t nb = std::min<int64_t>(opt->batch, n - b0);
       LPA_HIP(launch_mlp_grad(p->p, dX, dy, didx + b0, nb, opt->pos_weight, p->part, p->ploss,
-                              p->loss, b0 > 0, p->stream));
+                              p->stream));
       p->steps += 1;
-      LPA_HIP(launch_mlp_reduce_step(p->part, p->ploss, nb, p->g, p->loss, p->p, p->m, p->v,
-                                     p->steps, opt->lr, p->stream));
+      LPA_HIP(launch_mlp_reduce_step(p->part, p->ploss, nb, p->g, p->loss, b0 > 0, p->p, p->m,
+                                     p->v, p->steps, opt->lr, p->stream));
     }
     if (ep + 1 < opt->epochs) std::shuffle(perm.begin(), perm.end(), rng);
   }
