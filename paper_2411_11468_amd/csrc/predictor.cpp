@@ -25,37 +25,40 @@ struct lpa_predictor_s {
   float* m = nullptr;      // Adam first moment
   float* v = nullptr;      // Adam second moment
   double* loss = nullptr;  // summed loss of the last gradient
-  float* part = nullptr;   // gradients by workgroup
-  float* ploss = nullptr;  // losses of each 64 samples (loss_cap of them)
-  int64_t loss_cap = 0;
   uint8_t host[kGradBytes];  // a gradient and its loss read back
   MlpTiles* tiles = nullptr;
   bool tiles_ok = false;
   int32_t steps = 0;       // Adam steps taken
   uint8_t* slab = nullptr;  // one allocation for all of the above
-  float* more_loss = nullptr;  // ploss once it outgrows its part of the slab
+  // for the gradients of up to work_n samples: the parts by workgroup, and the
+  // losses of each kGradSamples samples
+  float* part = nullptr;
+  float* ploss = nullptr;
+  int64_t work_n = 0;
 
   ~lpa_predictor_s() {
     if (slab) (void)hipFree(slab);
-    if (more_loss) (void)hipFree(more_loss);
+    if (part) (void)hipFree(part);
   }
 };
 
 namespace {
 
-// Room for the losses of n samples at a time.
-constexpr int64_t kLossCap = 1024;
-lpa_status loss_space(lpa_predictor p, int64_t samples) {
-  const int64_t n = mlp_grad_losses(samples);
-  if (n <= p->loss_cap) return LPA_OK;
-  float* q = nullptr;
-  if (hipMalloc(&q, sizeof(float) * (size_t)n) != hipSuccess) {
+// Room for the gradient of n samples at a time, allocated by the first call
+// that needs it (up to 10 MB of parts, 1.3 MB at 4,096 samples: a predictor
+// that never trains has none).
+lpa_status grad_space(lpa_predictor p, int64_t n) {
+  if (n <= p->work_n) return LPA_OK;
+  const size_t parts = (size_t)mlp_grad_parts(n) * kMlpPartStride;
+  void* q = nullptr;
+  if (hipMalloc(&q, sizeof(float) * (parts + (size_t)mlp_grad_losses(n))) != hipSuccess) {
     (void)hipGetLastError();
-    return fail(LPA_ERR_OOM, "hipMalloc failed for the samples' losses");
+    return fail(LPA_ERR_OOM, "hipMalloc failed for the gradient's parts");
   }
-  if (p->more_loss) (void)hipFree(p->more_loss);  // idle: every call waits for its work
-  p->more_loss = p->ploss = q;
-  p->loss_cap = n;
+  if (p->part) (void)hipFree(p->part);  // idle: every call waits for its work
+  p->part = static_cast<float*>(q);
+  p->ploss = p->part + parts;
+  p->work_n = n;
   return LPA_OK;
 }
 
@@ -112,8 +115,7 @@ lpa_status lpa_predictor_create(uint64_t seed, void* stream, lpa_predictor* out)
   lpa_predictor p = new (std::nothrow) lpa_predictor_s();
   if (!p) return fail(LPA_ERR_OOM, "host allocation failed");
   p->stream = (hipStream_t)stream;
-  // parameters, gradient and loss, moments, operand tiles, losses and the
-  // gradient's parts (10 MB) in one allocation
+  // parameters, gradient and loss, moments and operand tiles in one allocation
   size_t bytes = 0;
   auto take = [&](size_t size) {
     const size_t at = bytes;
@@ -122,9 +124,7 @@ lpa_status lpa_predictor_create(uint64_t seed, void* stream, lpa_predictor* out)
   };
   const size_t params = sizeof(float) * kMlpParams;
   const size_t at_p = take(params), at_g = take(kGradBytes), at_m = take(params),
-               at_v = take(params), at_t = take(sizeof(MlpTiles)),
-               at_l = take(sizeof(float) * kLossCap),
-               at_part = take(sizeof(float) * (size_t)kMlpMaxParts * kMlpPartStride);
+               at_v = take(params), at_t = take(sizeof(MlpTiles));
   if (hipMalloc(&p->slab, bytes) != hipSuccess) {
     (void)hipGetLastError();
     delete p;
@@ -136,9 +136,6 @@ lpa_status lpa_predictor_create(uint64_t seed, void* stream, lpa_predictor* out)
   p->m = reinterpret_cast<float*>(p->slab + at_m);
   p->v = reinterpret_cast<float*>(p->slab + at_v);
   p->tiles = reinterpret_cast<MlpTiles*>(p->slab + at_t);
-  p->ploss = reinterpret_cast<float*>(p->slab + at_l);
-  p->loss_cap = kLossCap;
-  p->part = reinterpret_cast<float*>(p->slab + at_part);
   // He-uniform weights (limit sqrt(6 / fan_in)), zero biases
   std::vector<float> h(kMlpParams, 0.0f);
   std::mt19937_64 rng(seed);
@@ -268,7 +265,7 @@ lpa_status lpa_predictor_gradient(lpa_predictor p, const float* X, const float* 
   float *dX = nullptr, *dy = nullptr;
   if (lpa_status e = to_device(X, (size_t)n * kMlpIn, &dX, &st.bufs, p->stream)) return e;
   if (lpa_status e = to_device(y, (size_t)n, &dy, &st.bufs, p->stream)) return e;
-  if (lpa_status e = loss_space(p, n)) return e;
+  if (lpa_status e = grad_space(p, n)) return e;
   if (n > 0) {
     LPA_HIP(launch_mlp_grad(p->p, dX, dy, nullptr, n, pos_weight, p->part, p->ploss,
                             p->stream));
@@ -306,7 +303,7 @@ lpa_status lpa_predictor_train(lpa_predictor p, const float* X, const float* y, 
   float *dX = nullptr, *dy = nullptr;
   if (lpa_status e = to_device(X, (size_t)n * kMlpIn, &dX, &st.bufs, p->stream)) return e;
   if (lpa_status e = to_device(y, (size_t)n, &dy, &st.bufs, p->stream)) return e;
-  if (lpa_status e = loss_space(p, std::min<int64_t>(n, opt->batch))) return e;
+  if (lpa_status e = grad_space(p, std::min<int64_t>(n, opt->batch))) return e;
   // one permutation of the samples per epoch (host RNG); the minibatches take
   // the samples through it, and the host draws the next epoch's while the GPU
   // runs this one
