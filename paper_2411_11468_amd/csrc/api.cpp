@@ -331,7 +331,12 @@ struct lpa_graph_s {
   // captured iterations, one executable graph per launch configuration
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph_exec[24] = {};
-  const MlpTiles* graph_tiles[24] = {};
+  // what a captured learned iteration holds besides
+  struct GraphLearn {
+    const MlpTiles* tiles = nullptr;
+    int cmin = 0, cmax = 0;
+  };
+  GraphLearn graph_learn[24];
   // learned skipping: attached predictor and options, per-vertex records
   lpa_predictor pred = nullptr;
   lpa_learned_options lopt{};
@@ -1123,15 +1128,20 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
 
 lpa_status lpa_graph_s::iteration_graph(const lpa_options& o, const RunCtx& rc,
                                         hipGraphExec_t* out) {
-  // a captured learned iteration holds the predictor's tile address: rebuild
-  // it when another predictor is attached
+  // a captured learned iteration holds the predictor's tile address and the
+  // classes whose sweeps keep records: rebuild it when another predictor or
+  // other options are attached
   const int key = (o.mode == LPA_MODE_ASYNC ? 6 : 0) + (o.prune ? 3 : 0) + o.flag_mode +
                   (rc.feat ? 12 : 0);
-  if (graph_exec[key] && graph_tiles[key] != rc.tiles) {
+  GraphLearn& held = graph_learn[key];
+  if (graph_exec[key] && rc.feat &&
+      (held.tiles != rc.tiles || held.cmin != rc.feat_cmin || held.cmax != rc.feat_cmax)) {
     (void)hipGraphExecDestroy(graph_exec[key]);
     graph_exec[key] = nullptr;
   }
-  graph_tiles[key] = rc.tiles;
+  held.tiles = rc.tiles;
+  held.cmin = rc.feat_cmin;
+  held.cmax = rc.feat_cmax;
   if (graph_exec[key]) {
     *out = graph_exec[key];
     return LPA_OK;
