@@ -359,6 +359,7 @@ struct lpa_graph_s {
     DevIterStats* h = nullptr;
     if (lpa_status e = dalloc(&h, std::max(cap, 32))) return e;
     hist = h;  // the old buffer stays in dev_allocs until destroy
+    learned_iters = 0;  // its records were there
     for (hipGraphExec_t& x : graph_exec) {  // captured with the old one
       if (x) (void)hipGraphExecDestroy(x);
       x = nullptr;

@@ -93,9 +93,14 @@ __device__ __forceinline__ void begin_iteration(DevStats* st) {
 
 __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
                             int graphs, LearnParams lp, unsigned int seq) {
+  // the counters and their copies; the history stays that of the last run
+  // (lpa_learned_history) until an iteration of this one ends
   uint32_t* w = reinterpret_cast<uint32_t*>(st);
-  for (uint32_t i = threadIdx.x; i < sizeof(DevState) / sizeof(uint32_t); i += blockDim.x)
-    w[i] = 0u;  // the counters and their copies
+  for (uint32_t i = threadIdx.x; i < sizeof(DevStats) / sizeof(uint32_t); i += blockDim.x)
+    w[i] = 0u;
+  uint32_t* c = reinterpret_cast<uint32_t*>(reinterpret_cast<DevState*>(st)->slot);
+  for (uint32_t i = threadIdx.x; i < sizeof(DevState::slot) / sizeof(uint32_t); i += blockDim.x)
+    c[i] = 0u;
   __syncthreads();
   if (threadIdx.x == 0) {
     st->tol = tol;

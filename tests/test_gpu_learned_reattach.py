@@ -1,5 +1,5 @@
-"""Captured learned runs after the same predictor is attached with other
-options: the iteration captured before must not be replayed."""
+"""State that outlives a learned run: a captured iteration after the same
+predictor is attached with other options, the history after a refused run."""
 import numpy as np
 import pytest
 
@@ -33,5 +33,23 @@ def test_classes_predicted_follow_the_attached_options(order, launch):
                         predict_small=bool(small), predict_large=bool(large))
         res = G.run("det", learned=True, launch=launch)
         _assert_same(_oracle(g, SMALL_TUNING, small, large), G, res)
+    G.close()
+    pr.close()
+
+
+def test_history_survives_a_refused_run():
+    g = graphgen.planted_partition_10k(1)
+    G = _gpu_graph(g)
+    pr = lpa.Predictor(params=P_HISTORY)
+    G.set_predictor(pr, threshold=0.5, fn_bound=1.0)
+    G.run("det", learned=True)
+    kept = G.learned_history()
+    assert len(kept) > 2 and kept[1]["iteration"] == 1
+    bad = np.full(len(g.offsets) - 1, -1, dtype=np.int32)
+    with pytest.raises(lpa.LpaError):
+        G.run("det", learned=True, initial_labels=bad)
+    assert G.learned_history() == kept
+    G.run("det")                       # a plain run has none
+    assert G.learned_history() == []
     G.close()
     pr.close()
