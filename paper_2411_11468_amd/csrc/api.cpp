@@ -796,6 +796,9 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
   LPA_HIP(hipStreamSynchronize(s));
   for (int c = 0; c < kNumClasses; ++c) G->cls_count[c] = (int64_t)hcounts[c];
   G->n_active = G->perm ? n - G->cls_count[0] : n;
+  // bits that no iteration packs
+  if (G->n_active < n)
+    LPA_HIP(launch_fill_u32(G->chg_bits, 0u, (n + 31) / 32, s));
   G->H = (int32_t)(uint32_t)hcounts[kNumClasses];
   for (int c = 1; c < kNumClasses; ++c) {
     if (c == kClassHub) continue;

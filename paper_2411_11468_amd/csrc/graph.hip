@@ -1423,7 +1423,7 @@ __global__ __launch_bounds__(BT, WORDS ? 1 : 8) void k_pull_flags(const OffT* of
                                                    const uint32_t* bits, uint8_t* F,
                                                    DevStats* st, PushArgs pa) {
   if (st->stop || (!DECIDE && st->pull_mode != 1u)) return;
-  __shared__ __align__(16) uint32_t copy[WORDS ? WORDS : 1];
+  __shared__ __align__(16) uint32_t copy[WORDS + 1];
   if constexpr (DECIDE) {
     __shared__ unsigned int mode_sh;
     unsigned long long(*part)[kStatWords] =
@@ -1451,13 +1451,17 @@ __global__ __launch_bounds__(BT, WORDS ? 1 : 8) void k_pull_flags(const OffT* of
       return;
     }
   }
-  const int64_t words = (n + 31) / 32;
+  // the word after the copied ones stands for the vertices from n on, which have
+  // no entries and never change (the internal order's last; one is a target
+  // only if the CSR is not symmetric)
+  [[maybe_unused]] const int last = (int)((n + 31) / 32);
   if constexpr (WORDS > 0) {
-    for (int w = threadIdx.x; w < (int)words; w += BT) copy[w] = bits[w];
+    for (int w = threadIdx.x; w < last; w += BT) copy[w] = bits[w];
+    if (threadIdx.x == 0) copy[last] = 0u;
     __syncthreads();
   }
   auto changed = [&](int32_t j) {
-    if constexpr (WORDS > 0) return chg_bit(copy, j);
+    if constexpr (WORDS > 0) return ((copy[min(j >> 5, last)] >> (j & 31)) & 1u) != 0u;
     else return chg_bit(bits, j);
   };
   const int lane = threadIdx.x & 63;
