@@ -153,6 +153,13 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
   uint32_t* Bn = par ? q.B0 : q.B1;            // (and of the next one), or
   uint8_t* Fc = par ? q.F1 : q.F0;             // bytes for the graphs whose
   uint8_t* Fn = par ? q.F0 : q.F1;             // bits LDS does not hold
+  // a neighbour's label.  Asynchronous mode reads past the CU's cache: a graph
+  // whose labels fit there would otherwise not see the other CUs' updates until
+  // the sweep ends
+  auto label = [&](uint32_t v) {
+    if constexpr (DET) return (uint32_t)Cc[v];
+    else return (uint32_t)__hip_atomic_load(&Cc[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   const OffT* off = reinterpret_cast<const OffT*>(q.off);
   const int64_t CH = (int64_t)1 << q.chunk_log2;
   uint32_t* hdr = chunk_lds;
@@ -303,13 +310,8 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
             for (int u = 0; u < U; ++u) {
               ids[r][u] = (uint32_t)j[r][u];
               wc[r][u] = UNIT ? 1.0f : wt[r][u];
-              // asynchronous mode reads past the CU's cache: a graph whose
-              // labels fit there would otherwise not see the other CUs'
-              // updates until the sweep ends
               if constexpr (FIRST) got[r][u] = ids[r][u];
-              else if constexpr (DET) got[r][u] = (uint32_t)Cc[ids[r][u]];
-              else got[r][u] = (uint32_t)__hip_atomic_load(&Cc[ids[r][u]], __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT);
+              else got[r][u] = label(ids[r][u]);
             }
           }
           targets();
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
         if (direct) {
           if (j != v) best = umax64(best, pack_key(wt, (uint32_t)j));
         } else {
-          uint32_t lab = (j != v) ? (id0 ? (uint32_t)j : (uint32_t)Cc[j]) : kEmpty;
+          uint32_t lab = (j != v) ? (id0 ? (uint32_t)j : label((uint32_t)j)) : kEmpty;
           merge_lead(lab, wt, UNIT);
           if (lab != kEmpty) lds_accumulate(tags, vals, p1, lab, wt, q.probe);
         }
