@@ -307,8 +307,9 @@ typedef struct lpa_iter_stats {
  * handle's stream); bytes: algorithmic bytes moved -- per scanned CSR entry
  * the target (4 B), the weight (4 B, none for unit weights) and the gathered
  * neighbour label (4 B); per processed vertex its active-list id (4 B), two
- * row offsets and its own label (4 B); per change the new label (4 B, 8 B for
- * a queued pair in deterministic mode) and one flag byte per neighbour;
+ * row offsets and its own label (4 B); per change the new label (4 B) and the
+ * change byte; pushed flags: one byte per neighbour; pulled flags: the change
+ * bits and the targets read up to the first changed one;
  * edges, vertices: CSR entries scanned and vertices processed.
  */
 typedef struct lpa_kernel_profile {

@@ -169,10 +169,9 @@ struct lpa_graph_s {
   // Algorithmic bytes of one launch: what the method must read and write,
   // independent of caching (per scanned CSR entry: target 4 B, weight 4 B
   // unless unit weights, gathered neighbour label 4 B; per processed vertex:
-  // its active-list id 4 B, its two row offsets, its own label 4 B, and in
-  // deterministic mode its next label 4 B; per change: the new label 4 B in
-  // asynchronous mode (a queued hub pair 8 B in deterministic mode) and one
-  // flag byte per neighbour).
+  // its active-list id 4 B, its two row offsets, its own label 4 B; per change
+  // the new label 4 B, the change byte and, pushed, one flag byte per
+  // neighbour).
   // flag_mode: 0 pushed, 1 pulled, 2 deferred to lpa_get_flags
   void account(int kid, float ms, const DevStats& h, bool async_mode, int flag_mode) {
     const bool pull = flag_mode == 1, push = flag_mode == 0;
@@ -185,7 +184,6 @@ struct lpa_graph_s {
     const bool direct = (kid > kKidDirect0 && kid <= kKidDirect0 + 8) || kid == kKidHubDirect;
     const double eb = ((id0 || direct) ? 4.0 : 8.0) + (w ? 4.0 : 0.0);
     const double ob = off64 ? 16.0 : 8.0;
-    const double chb = async_mode ? 4.0 : 8.0;
     double bytes = 0.0;
     int64_t edges = 0, verts = 0;
     if ((kid >= kKidSweep0 + 1 && kid <= kKidSweep0 + 8) || (direct && kid != kKidHubDirect)) {
@@ -198,8 +196,9 @@ struct lpa_graph_s {
       // table-free sweep of rows up to 4 entries: internal rows, each
       // target's caller id read from inv
       const double ebc = eb + ((direct && c == 1 && perm) ? 4.0 : 0.0);
-      bytes = ebc * edges + (4.0 + ob + own) * verts + (double)h.changed[c] +
-              (async_mode ? 4.0 * h.changed[c] : 4.0 * verts);
+      // a change: the label (in place, or beside the iteration's own) and the
+      // change byte
+      bytes = ebc * edges + (4.0 + ob + own) * verts + 5.0 * (double)h.changed[c];
       if (acct_feat && c >= acct_feat_cmin && c <= acct_feat_cmax)
         bytes += 16.0 * verts;  // state record read and written
     } else if (kid == kKidHubPart || kid == kKidHubDirect) {
@@ -211,7 +210,7 @@ struct lpa_graph_s {
       edges = (int64_t)h.hub_pairs;
       bytes = 8.0 * (double)h.hub_pairs;
     } else if (kid == kKidHubFin) {
-      bytes = chb * h.changed[kClassHub] + (double)h.changed[kClassHub];
+      bytes = 5.0 * (double)h.changed[kClassHub];
     } else if (kid == kKidFrontier) {
       verts = (int64_t)h.processed;
       // flag, class and change byte per vertex; flag clear + list id per
@@ -220,12 +219,12 @@ struct lpa_graph_s {
       // learned frontier: the record of every predicted or traced vertex
       if (acct_feat) bytes += 8.0 * (double)(h.processed + h.skipped);
     } else if (kid == kKidPull || kid == kKidPullHubs) {
-      // row offsets and class per vertex, target + change byte per entry
-      // read, flag byte per vertex; the two kernels share one counter, so
-      // the whole figure is booked on the first
+      // row offsets and class per vertex, the change bits, the targets read,
+      // flag byte per vertex; the two kernels share one counter, so the whole
+      // figure is booked on the first
       if (kid == kKidPull && pull) {
         edges = (int64_t)h.pull_scanned;
-        bytes = (double)n * ((off64 ? 8.0 : 4.0) + 2.0) + 5.0 * (double)h.pull_scanned;
+        bytes = (double)n * ((off64 ? 8.0 : 4.0) + 2.0) + n / 8.0 + 4.0 * (double)h.pull_scanned;
       }
     } else if (kid == kKidPush || kid == kKidPushHubs) {
       // per changed row: its offsets and, per entry, target read + flag byte
@@ -237,21 +236,21 @@ struct lpa_graph_s {
         bytes = 5.0 * (double)listed + (off64 ? 16.0 : 8.0) * (double)ch + 5.0 * (double)fw;
       }
     } else if (kid == kKidQueueSweep) {
-      // per scanned entry as the class sweeps; per processed vertex its flag,
-      // offsets and own label (and the next label in deterministic mode);
-      // per change the new label (asynchronous mode)
+      // per scanned entry as the class sweeps; a flag bit per vertex; per
+      // processed vertex its offsets and own label; per change the new label
       edges = (int64_t)h.edges[0];
       verts = (int64_t)h.processed;
-      bytes = eb * edges + (1.0 + ob + 4.0 + (async_mode ? 0.0 : 4.0)) * verts +
-              (async_mode ? 4.0 * h.changed[0] : 0.0);
+      bytes = eb * edges + n / 8.0 + (ob + 4.0) * verts + 4.0 * (double)h.changed[0];
     } else if (kid == kKidBatch) {
       bytes = 2.0 * n;  // change byte read, flag cleared at most once
     } else if (kid == kKidApply) {
-      // change byte per vertex; per changed vertex its label read and written
+      // change byte per vertex; deterministic: per changed vertex its label read
+      // and written; pulled: the change bits
       unsigned long long changed = 0;
       for (int c = 0; c < kNumClasses; ++c) changed += h.changed[c];
-      verts = (int64_t)changed;
-      bytes = (double)n + 8.0 * (double)changed;
+      verts = async_mode ? 0 : (int64_t)changed;
+      if (!async_mode || pull) bytes = (double)n + 8.0 * (double)verts;
+      if (pull) bytes += n / 8.0;
     }
     p.launches += 1;
     p.total_ms += ms;
