@@ -70,6 +70,9 @@ struct RunCtx;
 // all max_iterations, and an eager one waited for each).  LFR 1M, captured:
 // 1.91 -> 1.60 ms; a 10 000-vertex graph, eager: 0.53 -> 0.38 ms.
 constexpr int32_t kRunAhead = 1;
+// Events that time the iterations launched ahead, used in turn (one for every
+// iteration held 0.8 KB each until the handle was destroyed).
+constexpr int32_t kTimedAhead = 128;
 
 struct lpa_graph_s {
   hipStream_t stream = nullptr;
@@ -1309,6 +1312,14 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
   // eager iterations that need nothing of the host in between are launched
   // ahead of the iteration that runs, as the replays are
   const bool ahead = !graph_mode && !o.profile && !trace && o.cc_period == 0;
+  // the times of iterations timed .. upto - 1, from the events before and after
+  int32_t timed = 0;
+  auto read_times = [&](int32_t upto) -> lpa_status {
+    for (; timed < std::min(upto, stats_cap); ++timed)
+      LPA_HIP(hipEventElapsedTime(&stats[timed].ms, g->ev_pool[timed % kTimedAhead],
+                                  g->ev_pool[(timed + 1) % kTimedAhead]));
+    return LPA_OK;
+  };
   if (graph_mode) {
     // capture one iteration on the private stream and replay it on the
     // handle's stream; the kernels of an iteration after the stop return at
@@ -1341,12 +1352,15 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
       bool stopped = false;
       if (lpa_status e = g->wait_iterations(l - kRunAhead, &stopped)) return e;
       if (stopped) break;
+      // iteration l - kRunAhead - 1 has ended, so the events before it have passed
+      if (l + 1 - timed >= kTimedAhead)
+        if (lpa_status e = read_times(l - kRunAhead - 1)) return e;
       if (lpa_status e = enqueue_iteration(g, o, ctx_of(l), s, nomark, first_direct && l == 0, false,
                                            true))
         return e;
       if (l < stats_cap) {
-        if (lpa_status e = g->ensure_events(l + 2)) return e;
-        LPA_HIP(hipEventRecord(g->ev_pool[l + 1], s));
+        if (lpa_status e = g->ensure_events(std::min(l + 2, kTimedAhead))) return e;
+        LPA_HIP(hipEventRecord(g->ev_pool[(l + 1) % kTimedAhead], s));
       }
     }
   } else {
@@ -1437,7 +1451,10 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
       LPA_HIP(hipStreamSynchronize(s));
       h = more.data();
     }
+    if (ahead)
+      if (lpa_status e = read_times(k)) return e;
     for (int32_t l = 0; l < k; ++l) {
+      const float ms = ahead ? stats[l].ms : 0.0f;
       std::memset(&stats[l], 0, sizeof(stats[l]));
       stats[l].iteration = h[l].iteration;
       stats[l].pick_less = h[l].pick_less;
@@ -1445,8 +1462,7 @@ static lpa_status run_impl(lpa_graph g, const lpa_options* opt, int32_t* labels,
       stats[l].processed = h[l].processed;
       stats[l].edges_scanned = h[l].edges;
       stats[l].skipped = (int32_t)h[l].skipped;
-      if (ahead)
-        LPA_HIP(hipEventElapsedTime(&stats[l].ms, g->ev_pool[l], g->ev_pool[l + 1]));
+      stats[l].ms = ms;
     }
   }
   if (iters_done) *iters_done = done;
