@@ -125,6 +125,8 @@ struct lpa_graph_s {
   HostState* host = nullptr;
   DevStats* st_host = nullptr;   // &host->st
   uint32_t run_seq = 0;
+  // unit weights, or whole ones of at most 2^18: 64 of them sum exactly
+  bool exact_sums = true;
   int32_t H = 0;
   int32_t* hub_vid = nullptr;
   int64_t* hub_tab = nullptr;
@@ -325,6 +327,7 @@ struct lpa_graph_s {
     q.items = wq_items; q.qbase = wq_qbase; q.qctr = wq_qctr; q.gchanged = wq_gchanged;
     q.b = batch_args(); q.st = st;
     q.nchunks = wq_nchunks; q.chunk_log2 = wq_chunk_log2; q.group_max = wq_group;
+    q.exact_sums = exact_sums;
     q.async_mode = async_mode;
     q.strict_rows = strict_rows ? 1 : 0;
     q.probe = ProbeCfg{tun.max_retries, tun.probe};
@@ -660,18 +663,19 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
   // kernels then read none (the sums, hence every result, are the same)
   if (G->w && m > 0) {
     unsigned int* other = nullptr;
-    if (hipMalloc(&other, sizeof(unsigned)) != hipSuccess) {
+    if (hipMalloc(&other, 2 * sizeof(unsigned)) != hipSuccess) {
       (void)hipGetLastError();
       return fail(LPA_ERR_OOM, "hipMalloc failed for the weight check");
     }
-    unsigned int h = 1u;
+    unsigned int h[2] = {1u, 1u};
     hipError_t e = launch_unit_weights(G->w, m, other, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&h, other, sizeof(h), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(h, other, sizeof(h), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(other);
     if (e != hipSuccess)
       return fail(LPA_ERR_HIP, std::string("weight check: ") + hipGetErrorString(e));
-    if (h == 0u) {
+    G->exact_sums = h[1] == 0u;
+    if (h[0] == 0u) {
       G->w = nullptr;
       G->uw = nullptr;
     }
@@ -1053,6 +1057,7 @@ static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const Run
   a.tload = g->tun.table_load;
   a.block_threads = g->tun.block_threads;
   a.small_labels = g->n <= ((int64_t)1 << 25);
+  a.exact_sums = g->exact_sums;
   for (int c = kClassHub - 1; c >= 1; --c) {
     if (g->cls_count[c] == 0) continue;
     a.cls = c;

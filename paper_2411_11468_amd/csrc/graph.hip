@@ -370,18 +370,23 @@ hipError_t launch_validate(bool off64, const void* off, const int32_t* tgt,
   return hipGetLastError();
 }
 
-// Any weight other than 1.0f: *other receives 1 (else the weights are unit
-// weights, and the kernels need not read them).
+// Any weight other than 1.0f: other[0] receives 1 (else the weights are unit
+// weights, and the kernels need not read them).  Any that is not a whole number
+// of at most 2^18: other[1] receives 1 (else 64 of them sum exactly in any order).
 __global__ void k_unit_weights(const float* w, int64_t m, unsigned int* other) {
-  bool any = false;
+  bool any = false, rounds = false;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
-       e += (int64_t)gridDim.x * blockDim.x)
-    any |= __float_as_uint(__builtin_nontemporal_load(&w[e])) != 0x3F800000u;
-  if (__any(any) && (threadIdx.x & 63) == 0) *other = 1u;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const float x = __builtin_nontemporal_load(&w[e]);
+    any |= __float_as_uint(x) != 0x3F800000u;
+    rounds |= !(x >= 0.0f && x <= 262144.0f && x == truncf(x));
+  }
+  if (__any(any) && (threadIdx.x & 63) == 0) other[0] = 1u;
+  if (__any(rounds) && (threadIdx.x & 63) == 0) other[1] = 1u;
 }
 
 hipError_t launch_unit_weights(const float* w, int64_t m, unsigned int* other, hipStream_t s) {
-  hipError_t e = launch_fill_u32(other, 0u, 1, s);
+  hipError_t e = launch_fill_u32(other, 0u, 2, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_unit_weights, dim3(grid_for(m, kBT, 8192)), dim3(kBT), 0, s, w, m, other);
   return hipGetLastError();

@@ -368,6 +368,32 @@ __device__ __forceinline__ void merge_lead(uint32_t& lab, float& wt, bool unit) 
   }
 }
 
+// merge_lead within each 16-lane row, for weights: the lanes of a row that hold
+// the label of its first entry hand their weights to that lane.  Rows of up to
+// 64 entries whose sums may round take it before match_sums, so that each
+// label's weights are added in one order: in each 16 entries the first one's
+// label as a tree, the others in their order.  (Whole weights of up to 2^18 sum
+// exactly in any order there: lpa_graph_s::exact_sums.)  The lanes of a row are
+// active or inactive together.
+__device__ __forceinline__ void merge_lead16(uint32_t& lab, float& wt) {
+  const unsigned long long act = __ballot(lab != kEmpty);
+  const int lane = (int)(threadIdx.x & 63);
+  const int row0 = lane & ~15;
+  const uint32_t ract = (uint32_t)(act >> row0) & 0xFFFFu;
+  const int first = row0 + (ract ? __ffs((int)ract) - 1 : 0);
+  const uint32_t lead = (uint32_t)__shfl((int)lab, first);
+  const bool mine = ract != 0u && lab == lead;
+  float x = mine ? wt : 0.0f;
+  x += dppf<0x128>(x);  // row_ror:8
+  x += dppf<0x124>(x);
+  x += dppf<0x122>(x);
+  x += dppf<0x121>(x);
+  if (mine) {
+    if (lane == first) wt = x;
+    else lab = kEmpty;
+  }
+}
+
 // Lane N of each DPP row in all its 16 lanes; each lane's value taken from the
 // lane N to its right (cyclic in the row).
 template <int N>

@@ -202,6 +202,7 @@ struct SweepArgs {
   const float* uw;
   const int32_t* inv;
   int small_labels = 0;   // every label is below 2^25 (row16_label)
+  int exact_sums = 0;     // rows of up to 64 entries sum exactly in any order
 };
 
 // Hubs (rows longer than the largest LDS table).  Each slice of chunk CSR
@@ -304,6 +305,7 @@ struct QueueArgs {
   DevStats* st;
   int64_t nchunks;
   int32_t chunk_log2;
+  int32_t exact_sums;              // rows of up to 64 entries sum exactly in any order
   int32_t group_max;               // rows of up to this many entries: 16 lanes
   int async_mode;
   int strict_rows;                 // every row's targets strictly increase
@@ -467,6 +469,7 @@ int hub_block_threads();
 int hub_max_resident();
 
 // *other = 1 if any of the m weights differs from 1.0f, else 0.
+// other: two words
 hipError_t launch_unit_weights(const float* w, int64_t m, unsigned int* other, hipStream_t s);
 
 // One pass reading every entry's target and neighbour label (sink: grid*256).

@@ -116,8 +116,8 @@ static_assert(kQueueMaxDegree < 1024, "header");
 // that a step loads only targets and labels (the next step's targets while
 // the current step's labels are in flight).  The lists are by row length, so
 // that the four rows of a wave step take the same number of 16-entry
-// slices: up to 16 entries (sums by rotations), up to 32 and up to 64 (sums
-// by match_sums).  New flags are gathered as bits in LDS and added to the
+// slices: up to 16 entries (sums by rotations, where they are exact), up to 32
+// and up to 64 (sums by match_sums).  New flags are gathered as bits in LDS and added to the
 // graph's words once per chunk, where a byte store per entry took as many
 // address cycles as reading the entry's label; a graph whose bits LDS does
 // not hold keeps flag bytes (atomic bits per entry were twice as slow there).
@@ -168,6 +168,7 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
   uint16_t* lst_b = lst_a + CH;
   uint32_t* fb = chunk_lds + 3 * CH;           // the graph's new flags, bits
   const int64_t gm = q.group_max;
+  const bool exact = UNIT || q.exact_sums != 0;
   for (int s = tid; s < kQPool; s += kQBT) vals[s] = 0.0f;
   for (int s = tid; s < q.fb_words; s += kQBT) fb[s] = 0u;
   uint32_t* tag = tags + (tid >> 4) * kMatchSlots;
@@ -328,9 +329,13 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
             if constexpr (FIRST) {
 #pragma unroll
               for (int u = 0; u < U; ++u) sum[u] = wc[r][u];
-            } else if constexpr (U == 1) {
+            } else if (U == 1 && exact) {
               sum[0] = rotate_sum<UNIT>(lab[0], wc[r][0]);
             } else {
+              if (!exact) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) merge_lead16(lab[u], wc[r][u]);
+              }
               match_sums<U, UNIT, false>(lab, wc[r], tag, val, sum, nullptr);
             }
             const uint32_t c = row16_label<U, UNIT>(lab, sum, small, lbase, cc[r]);

@@ -705,6 +705,7 @@ __global__ __launch_bounds__(256) void k_sweep_row64(SweepArgs a) {
   if (a.st->stop) return;
   const int pl = a.st->pl;  // fixed for the whole sweep
   const bool small = a.small_labels != 0;
+  [[maybe_unused]] const bool exact = a.exact_sums != 0;
   const bool id0 = a.st->iter == 0 && a.st->ident;  // labels are still the ids
   const int gi = threadIdx.x / G, k = threadIdx.x & (G - 1);
   uint32_t* tag = tag_all[gi];
@@ -767,6 +768,12 @@ __global__ __launch_bounds__(256) void k_sweep_row64(SweepArgs a) {
         targets();
 #pragma unroll
         for (int u = 0; u < U; ++u) lab[u] = use[u] ? (id0 ? ids[u] : got[u]) : kEmpty;
+        if constexpr (!UNIT) {
+          if (!exact) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) merge_lead16(lab[u], wt[u]);
+          }
+        }
         match_sums<U, UNIT, false>(lab, wt, tag, val, sum, nullptr);
         const uint32_t c = row16_label<U, UNIT>(lab, sum, small, 0u, cs);
         if ((uint32_t)k == t) res = c;
@@ -785,7 +792,7 @@ __global__ __launch_bounds__(256) void k_sweep_row64(SweepArgs a) {
 
 // The learned variant: it also reduces the record quantities over the group
 // and rewrites each evaluated vertex's state record.
-template <typename OffT>
+template <typename OffT, bool EXACT>
 __global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
   constexpr int G = 16, U = 4;
   constexpr int NG = 256 / G;
@@ -825,6 +832,10 @@ __global__ __launch_bounds__(256) void k_sweep_group(SweepArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
       lab[u] = (j[u] != v) ? (id0 ? (uint32_t)j[u] : (uint32_t)a.C[j[u]]) : kEmpty;
+    if constexpr (!EXACT) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) merge_lead16(lab[u], wt[u]);
+    }
     float K = 0.0f;
 #pragma unroll
     for (int u = 0; u < U; ++u) K += lab[u] != kEmpty ? wt[u] : 0.0f;
@@ -2128,7 +2139,10 @@ static hipError_t sweep_t(int cls, const SweepArgs& a, int grid, hipStream_t s) 
       else hipLaunchKernelGGL((k_sweep_row16<OffT, true>), dim3(grid), dim3(256), 0, s, a);
       break;
     case 3:
-      if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_group<OffT>), dim3(grid), dim3(256), 0, s, a);
+      if constexpr (FEAT) {
+        if (a.exact_sums) hipLaunchKernelGGL((k_sweep_group<OffT, true>), dim3(grid), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_sweep_group<OffT, false>), dim3(grid), dim3(256), 0, s, a);
+      }
       else if (a.w) hipLaunchKernelGGL((k_sweep_row64<OffT, false>), dim3(grid), dim3(256), 0, s, a);
       else hipLaunchKernelGGL((k_sweep_row64<OffT, true>), dim3(grid), dim3(256), 0, s, a);
       break;
