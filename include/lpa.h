@@ -229,7 +229,11 @@ typedef struct lpa_tuning {
  *                   device memory
  *   profile         1: bracket every kernel launch with HIP events and add its
  *                   duration and algorithmic bytes to the per-kernel profile
- *                   read by lpa_profile (default 0)
+ *                   read by lpa_profile (default 0).  Each step then has a
+ *                   launch of its own: graphs without hub rows otherwise begin
+ *                   an iteration in the last kernel of the one before, and of up
+ *                   to 1.2 M vertices choose, push and pull the flags in one
+ *                   launch
  *   launch          lpa_launch (default LPA_LAUNCH_EAGER)
  *   flag_mode       how the neighbours of the vertices changed in an
  *                   iteration are flagged after its sweep (the flags are
@@ -413,8 +417,7 @@ lpa_status lpa_predictor_get_params(lpa_predictor p, float* params);
  * only reports the size (LPA_PREDICTOR_BLOB_BYTES).  lpa_predictor_load
  * restores them into p: it then holds exactly the saved state (the same
  * predictions; training continues from the same parameters and moments,
- * and follows the saved predictor up to the order of the gradient's float
- * atomic sums).  Layout: a 32-byte header
+ * and follows the saved predictor to the bit).  Layout: a 32-byte header
  * (magic "LPAPRED1", uint32 version 1, uint16 layer sizes 12, 64, 64, 1,
  * uint32 parameter count 5057, int32 Adam steps, uint32 0), then 3 x 5057
  * fp32 (parameters, first moments, second moments), little-endian.
@@ -567,7 +570,7 @@ lpa_status lpa_modularity(lpa_graph g, const int32_t* labels, double* q);
  * forbid hipMalloc.  Same arguments, result and errors as lpa_modularity,
  * for graphs of at most LPA_MODULARITY_NOALLOC_MAX_VERTICES vertices
  * (larger: LPA_ERR_INVALID, nothing launched).  Its scratch (per-community
- * sums and accumulators, 32 MiB) is a fixed array in the library's device
+ * sums, 32 MiB) is a fixed array in the library's device
  * code: each GPU the library runs on holds one copy until the process ends,
  * and every call on that GPU uses it, so calls that overlap on one GPU (from
  * several threads or streams) race and must not be made; each call clears

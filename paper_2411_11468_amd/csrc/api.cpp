@@ -1,9 +1,10 @@
 // api.cpp -- host runtime of the label-propagation library and its C ABI
 // (declared in include/lpa.h).  Owns device memory, builds the degree classes
 // at create time and drives the iterations of Algorithm 1 (lpa): per
-// iteration it enqueues the hub plan, the frontier, the class sweeps and (in
-// deterministic mode) the label apply, reads back the iteration counters and
-// applies the stop rule.
+// iteration it enqueues the hub plan, the frontier, the class sweeps, the
+// publishing of labels and changes and the flags, one iteration ahead of the
+// one that runs.  The stop rule is applied on the GPU (k_iter_end); the counters
+// are read back once, at the end.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -968,10 +969,6 @@ static lpa_status stage_labels(lpa_graph g, const int32_t* src, int32_t* dst) {
 
 }  // extern "C"
 
-// Enqueue one iteration of Algorithm 1 on stream s.  Every kernel reads the
-// iteration's Pick-Less flag and the stop flag from device memory, so the
-// sequence can be replayed without the host (eagerly or as a captured graph).
-// mark(kid) brackets launches for the optional per-kernel profile.
 // Learned-variant context of a run: records kept (feat), predictor tiles
 // (NULL: no predictions) and trace buffers (X NULL: no trace).
 struct RunCtx {
@@ -984,10 +981,14 @@ struct RunCtx {
   TraceArgs tr{};
 };
 
-// direct: the first sweep of a run from identity labels over rows with
-// strictly increasing targets, which takes the table-free kernels.  cc: a
+// Enqueues one iteration of Algorithm 1 on stream s.  Every kernel reads the
+// iteration's Pick-Less flag and the stop flag from device memory, so the
+// sequence can be replayed without the host (eagerly or as a captured graph).
+// mark(kid) brackets launches for the optional per-kernel profile.  direct: the first sweep of a run from identity labels over rows
+// with strictly increasing targets, which takes the table-free kernels.  cc: a
 // Cross-Check iteration (eager launches only: its revert rounds are repeated
-// from the host until they settle).
+// from the host until they settle).  lean: nothing is read or timed between
+// this iteration's kernels and the next one's; launches are merged.
 template <typename Mark>
 static lpa_status enqueue_iteration(lpa_graph g, const lpa_options& o, const RunCtx& rc,
                                     hipStream_t s, Mark&& mark, bool direct = false,

@@ -63,34 +63,6 @@ hipError_t launch_init(int64_t n, const int32_t* init, const int32_t* inv, int32
 // the iteration's statistics and applies the stop rule of Algorithm 1 (after
 // an iteration that is not Pick-Less with changed < tolerance * N), or, in a
 // batched run, stops when every graph has stopped.
-// The counters and switches of iteration st->iter, by the first kNumClasses
-// threads of one workgroup.
-__device__ __forceinline__ void begin_iteration(DevStats* st) {
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    st->processed = 0;
-    st->pull_scanned = 0; st->pull_mode = 0;
-    st->hub_pairs = 0;
-    st->reverted = 0;
-    st->graphs_left = 0;
-    // Pick-Less in iterations l with l mod rho == 0, counting from 0
-    st->pl = (st->rho > 0 && st->iter % st->rho == 0) ? 1 : 0;
-    // learned skipping: predictions from iteration 1 on until a fallback;
-    // skip unless this is a guard iteration or the last one changed few
-    const int l = st->iter;
-    st->predict = (st->learn && !st->fallback && l >= st->pred_start) ? 1 : 0;
-    st->skipping = (st->predict && (st->guard == 0 || l % st->guard != 0) && !st->cand) ? 1 : 0;
-    st->skipped = 0; st->npred = 0; st->fneg = 0;
-    st->trace_first = st->trace_n;
-  }
-  if (tid < kNumClasses) {
-    st->active[tid].n = 0;
-    st->edges[tid] = 0;
-    st->changed[tid] = 0;
-    st->flagw[tid] = 0;
-  }
-}
-
 __global__ void k_run_begin(DevStats* st, double tol, int cap, int rho, int batched,
                             int graphs, LearnParams lp, unsigned int seq) {
   // the counters and their copies; the history stays that of the last run

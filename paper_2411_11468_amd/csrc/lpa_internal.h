@@ -9,8 +9,8 @@ namespace lpa {
 
 // Vertex classes by degree (bounds come from lpa_tuning):
 //   0 degree 0 (never processed: no neighbour to adopt a label from)
-//   1 4-lane register groups          2 16-lane register groups
-//   3 wave, LDS table <= 127 slots    4 wave, LDS table <= 1023 slots
+//   1 up to 4 entries: registers      2 up to 16: registers of 16 lanes
+//   3 up to 64: 16 lanes, LDS slots   4 up to 512: wave, LDS table <= 1023 slots
 //   5..8 workgroup, LDS table <= 2047 / 4095 / 8191 / 16383 slots
 //   9 hub: several workgroups per vertex + global-memory table
 constexpr int kNumClasses = 10;
@@ -25,8 +25,11 @@ struct alignas(128) LineCount {
   __host__ __device__ operator unsigned int() const { return n; }
 };
 
-// Per-iteration device counters.  Reset at the start of every iteration by
-// the hub-plan kernel, read back by the host after the iteration.
+// Run control and the counters of the iteration being run, on the device.  The
+// counters are reset by begin_iteration: in k_run_begin, in k_hub_plan or
+// k_queue_iter_begin, or in the k_iter_end before.  The host reads them back
+// once per run, after every iteration only with a profile, a trace or
+// Cross-Check.
 struct DevStats {
   unsigned long long processed;                 // vertices taken this iteration
   unsigned long long edges[kNumClasses];        // CSR entries scanned, per class

@@ -174,7 +174,6 @@ hipError_t launch_mlp_reduce_step(const float* part, const float* ploss, int64_t
                                   float lr, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int t, float lr,
                        hipStream_t s);
-hipError_t launch_fill_zero(float* x, int n, hipStream_t s);
 hipError_t launch_mlp_pack(const float* p, MlpTiles* t, hipStream_t s);
 hipError_t launch_mlp_infer(const MlpTiles* t, const float* X, int64_t B, float* out,
                             hipStream_t s);

@@ -387,16 +387,6 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const MlpTiles* t, const floa
   }
 }
 
-__global__ void k_fill_zero(float* x, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    x[i] = 0.0f;
-}
-
-hipError_t launch_fill_zero(float* x, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_zero, dim3((n + 255) / 256), dim3(256), 0, s, x, n);
-  return hipGetLastError();
-}
-
 int64_t mlp_grad_losses(int64_t B) { return (B + kGradSamples - 1) / kGradSamples; }
 
 int mlp_grad_parts(int64_t B) {

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "host_common.h"
+#include "lpa_internal.h"
 #include "lpa_mlp.h"
 
 using namespace lpa;
@@ -271,7 +272,7 @@ lpa_status lpa_predictor_gradient(lpa_predictor p, const float* X, const float* 
                             p->stream));
     LPA_HIP(launch_mlp_reduce(p->part, p->ploss, n, p->g, p->loss, p->stream));
   } else {
-    LPA_HIP(launch_fill_zero(p->g, kMlpParams, p->stream));
+    LPA_HIP(launch_fill_f32(p->g, 0.0f, kMlpParams, p->stream));
   }
   LPA_HIP(hipMemcpyAsync(p->host, p->g, kGradBytes, hipMemcpyDeviceToHost, p->stream));
   LPA_HIP(hipStreamSynchronize(p->stream));

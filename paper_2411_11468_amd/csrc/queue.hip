@@ -474,22 +474,8 @@ __global__ __launch_bounds__(kQBT, 5) void k_queue_sweep(QueueArgs q) {
 __global__ void k_queue_iter_begin(QueueArgs q) {
   DevStats* st = q.st;
   if (st->stop) return;
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    st->processed = 0;
-    st->pull_scanned = 0;
-    st->pull_mode = 0;
-    st->graphs_left = 0;
-    // Pick-Less in iterations l with l mod rho == 0, counting from 0
-    st->pl = (st->rho > 0 && st->iter % st->rho == 0) ? 1 : 0;
-  }
-  if (tid < kNumClasses) {
-    st->active[tid].n = 0;
-    st->edges[tid] = 0;
-    st->changed[tid] = 0;
-    st->flagw[tid] = 0;
-  }
-  const int np = (st->iter + 1) & 1;
+  begin_iteration(st);
+  const int np = (st->iter + 1) & 1, tid = threadIdx.x;
   if (tid < 2 * kXcds) q.qctr[(size_t)(np * 2 * kXcds + tid) * kQueueCtrStride] = 0u;
 }
 

@@ -28,16 +28,17 @@
 // Classes:
 //   k_sweep_lane4     rows of up to 4 entries, one lane per row, sums in
 //                     registers (learned variant: k_sweep_small<4>).
-//   k_sweep_small<G>  G lanes per vertex (G = 4 or 16), one edge per lane,
-//                     per-label sums by DPP rotations inside the group; no
-//                     hashtable is needed for rows this short.
+//   k_sweep_small<G>  the learned variant of rows of up to 4 (G = 4) and 5-16
+//                     entries (G = 16): G lanes per vertex, one edge per lane,
+//                     per-label sums by DPP rotations inside the group.
 //   k_sweep_row16, k_sweep_row64  rows of 5-16 and 17-64 entries, 16 lanes
 //                     per vertex, four vertices per wave step, a batch of
 //                     rows' headers per wave; sums by DPP rotations, or by
 //                     matching labels in LDS slots (match_sums).
 //   k_sweep_group     the learned variant of k_sweep_row64.
-//   k_sweep_wave_pipe  one wave per vertex, LDS hashtable per wave, the next
-//                     row's head loaded during the table scan.
+//   k_sweep_wave_pipe  one wave per vertex, labels of rows of up to 256 entries
+//                     matched in LDS slots (match_wave), longer ones in an LDS
+//                     hashtable per wave, the next row's head loaded meanwhile.
 //   k_sweep_block(_pipe)  one workgroup per vertex, LDS hashtable per
 //                     workgroup; the _pipe forms load the next row's head
 //                     during the table scan.
@@ -56,23 +57,23 @@ namespace {
 
 // One rotation step of the per-label sums inside a 16-lane row (R) or a quad
 // (quad_perm Q): add the other lane's weight if it holds the same label.
-// FEAT: also count the lanes holding the lane's label (its multiplicity).
-template <int R, bool FEAT>
+// mult counts the lanes holding the lane's label.
+template <int R>
 __device__ __forceinline__ void rot16_accum(uint32_t lab, float wt, float& sum, float& mult) {
   const uint32_t ol = dpp32<0x120 + R, 0xF, 0xF, false>(lab);
   const float ow = __uint_as_float(dpp32<0x120 + R, 0xF, 0xF, false>(__float_as_uint(wt)));
   if (ol == lab) {
     sum += ow;
-    if constexpr (FEAT) mult += 1.0f;
+    mult += 1.0f;
   }
 }
-template <int Q, bool FEAT>
+template <int Q>
 __device__ __forceinline__ void rot4_accum(uint32_t lab, float wt, float& sum, float& mult) {
   const uint32_t ol = dpp32<Q, 0xF, 0xF, false>(lab);
   const float ow = __uint_as_float(dpp32<Q, 0xF, 0xF, false>(__float_as_uint(wt)));
   if (ol == lab) {
     sum += ow;
-    if constexpr (FEAT) mult += 1.0f;
+    mult += 1.0f;
   }
 }
 
@@ -133,9 +134,9 @@ __device__ __forceinline__ void flush_fneg(uint32_t fneg, DevStats* st) {
 }  // namespace
 
 // ---- small rows: G lanes per vertex, registers only -------------------------
-// FEAT: the learned variant, which also rewrites the state record of every
-// vertex it evaluates (lpa_record.h).
-template <typename OffT, int G, bool FEAT>
+// The learned variant of the rows of up to 16 entries: it also rewrites the state
+// record of every vertex it evaluates (lpa_record.h).
+template <typename OffT, int G>
 __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
   if (a.st->stop) return;
   const int pl = a.st->pl;  // fixed for the whole sweep
@@ -156,28 +157,28 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
     int32_t v = valid ? a.active[idx] : 0;
     int64_t o = 0, d = 0;
     if (valid) row_of<OffT>(a.off, v, &o, &d);
-    [[maybe_unused]] const unsigned long long rold = (FEAT && valid && k == 0) ? a.rec[v] : 0ull;
+    const unsigned long long rold = (valid && k == 0) ? a.rec[v] : 0ull;
     const bool has = valid && k < d;
     const int32_t j = has ? __builtin_nontemporal_load(&a.tgt[o + k]) : -1;
     const float wt = has ? edge_weight(a.w, o + k) : 0.0f;
     uint32_t lab = kEmpty;
     if (has && j != v) lab = id0 ? (uint32_t)j : (uint32_t)a.C[j];
     // Per-label sum seen from this lane: its own weight plus every other lane
-    // of the group holding the same label.  FEAT: mult = lanes holding it.
+    // of the group holding the same label; mult: lanes holding it.
     float sum = wt, mult = 1.0f;
     if constexpr (G == 16) {
-      rot16_accum<1, FEAT>(lab, wt, sum, mult);  rot16_accum<2, FEAT>(lab, wt, sum, mult);
-      rot16_accum<3, FEAT>(lab, wt, sum, mult);  rot16_accum<4, FEAT>(lab, wt, sum, mult);
-      rot16_accum<5, FEAT>(lab, wt, sum, mult);  rot16_accum<6, FEAT>(lab, wt, sum, mult);
-      rot16_accum<7, FEAT>(lab, wt, sum, mult);  rot16_accum<8, FEAT>(lab, wt, sum, mult);
-      rot16_accum<9, FEAT>(lab, wt, sum, mult);  rot16_accum<10, FEAT>(lab, wt, sum, mult);
-      rot16_accum<11, FEAT>(lab, wt, sum, mult); rot16_accum<12, FEAT>(lab, wt, sum, mult);
-      rot16_accum<13, FEAT>(lab, wt, sum, mult); rot16_accum<14, FEAT>(lab, wt, sum, mult);
-      rot16_accum<15, FEAT>(lab, wt, sum, mult);
+      rot16_accum<1>(lab, wt, sum, mult);  rot16_accum<2>(lab, wt, sum, mult);
+      rot16_accum<3>(lab, wt, sum, mult);  rot16_accum<4>(lab, wt, sum, mult);
+      rot16_accum<5>(lab, wt, sum, mult);  rot16_accum<6>(lab, wt, sum, mult);
+      rot16_accum<7>(lab, wt, sum, mult);  rot16_accum<8>(lab, wt, sum, mult);
+      rot16_accum<9>(lab, wt, sum, mult);  rot16_accum<10>(lab, wt, sum, mult);
+      rot16_accum<11>(lab, wt, sum, mult); rot16_accum<12>(lab, wt, sum, mult);
+      rot16_accum<13>(lab, wt, sum, mult); rot16_accum<14>(lab, wt, sum, mult);
+      rot16_accum<15>(lab, wt, sum, mult);
     } else {
-      rot4_accum<0x39, FEAT>(lab, wt, sum, mult);  // quad_perm [1,2,3,0]
-      rot4_accum<0x4E, FEAT>(lab, wt, sum, mult);  // quad_perm [2,3,0,1]
-      rot4_accum<0x93, FEAT>(lab, wt, sum, mult);  // quad_perm [3,0,1,2]
+      rot4_accum<0x39>(lab, wt, sum, mult);  // quad_perm [1,2,3,0]
+      rot4_accum<0x4E>(lab, wt, sum, mult);  // quad_perm [2,3,0,1]
+      rot4_accum<0x93>(lab, wt, sum, mult);  // quad_perm [3,0,1,2]
     }
     const unsigned long long packed = (lab != kEmpty) ? pack_key(sum, lab) : 0ull;
     const unsigned long long best = group_max<G>(packed);
@@ -185,23 +186,21 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
     const int32_t cur = valid ? a.C[v] : 0;
     const bool moved = valid && decide(best, cur, pl, &cstar);
     const bool leader = valid && k == 0;
-    if constexpr (FEAT) {
-      // every lane takes part in the group reductions
-      const float K = group_sum_f32<G>(lab != kEmpty ? wt : 0.0f);
-      const unsigned long long ownk =
-          (lab != kEmpty && (int32_t)lab == cur) ? (unsigned long long)__float_as_uint(sum) : 0ull;
-      const float own = __uint_as_float((uint32_t)group_max<G>(ownk));
-      const uint32_t bl = best ? unpack_label(best) : kEmpty;
-      const unsigned long long sk = (lab != kEmpty && lab != bl) ? pack_key(sum, lab) : 0ull;
-      const float second = __uint_as_float((uint32_t)(group_max<G>(sk) >> 32));
-      const float bw = __uint_as_float((uint32_t)(best >> 32));
-      // each label's lanes contribute 1/mult each: the group sum is the
-      // number of distinct labels up to rounding (at most 16 terms)
-      const uint32_t distinct =
-          (uint32_t)rintf(group_sum_f32<G>(lab != kEmpty ? 1.0f / mult : 0.0f));
-      if (leader && d >= 1)
-        my_fneg += rec_write(a.rec, v, rold, l, K, own, bw, second, distinct, (uint32_t)d, moved);
-    }
+    // every lane takes part in the group reductions
+    const float K = group_sum_f32<G>(lab != kEmpty ? wt : 0.0f);
+    const unsigned long long ownk =
+        (lab != kEmpty && (int32_t)lab == cur) ? (unsigned long long)__float_as_uint(sum) : 0ull;
+    const float own = __uint_as_float((uint32_t)group_max<G>(ownk));
+    const uint32_t bl = best ? unpack_label(best) : kEmpty;
+    const unsigned long long sk = (lab != kEmpty && lab != bl) ? pack_key(sum, lab) : 0ull;
+    const float second = __uint_as_float((uint32_t)(group_max<G>(sk) >> 32));
+    const float bw = __uint_as_float((uint32_t)(best >> 32));
+    // each label's lanes contribute 1/mult each: the group sum is the
+    // number of distinct labels up to rounding (at most 16 terms)
+    const uint32_t distinct =
+        (uint32_t)rintf(group_sum_f32<G>(lab != kEmpty ? 1.0f / mult : 0.0f));
+    if (leader && d >= 1)
+      my_fneg += rec_write(a.rec, v, rold, l, K, own, bw, second, distinct, (uint32_t)d, moved);
     if (leader) {
       if (a.async_mode) {
         if (moved) a.C[v] = (int32_t)cstar;
@@ -217,7 +216,7 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
     }
   }
   flush_stats(my_edges, my_changed, my_flagw, a.st, a.cls);
-  if constexpr (FEAT) flush_fneg(my_fneg, a.st);
+  flush_fneg(my_fneg, a.st);
 }
 
 // ---- short rows: headers a batch at a time ----------------------------------
@@ -2130,11 +2129,11 @@ static hipError_t sweep_t(int cls, const SweepArgs& a, int grid, hipStream_t s) 
   }
   switch (cls) {
     case 1:
-      if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_small<OffT, 4, true>), dim3(grid), dim3(256), 0, s, a);
+      if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_small<OffT, 4>), dim3(grid), dim3(256), 0, s, a);
       else hipLaunchKernelGGL((k_sweep_lane4<OffT>), dim3(grid), dim3(256), 0, s, a);
       break;
     case 2:
-      if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_small<OffT, 16, true>), dim3(grid), dim3(256), 0, s, a);
+      if constexpr (FEAT) hipLaunchKernelGGL((k_sweep_small<OffT, 16>), dim3(grid), dim3(256), 0, s, a);
       else if (a.w) hipLaunchKernelGGL((k_sweep_row16<OffT, false>), dim3(grid), dim3(256), 0, s, a);
       else hipLaunchKernelGGL((k_sweep_row16<OffT, true>), dim3(grid), dim3(256), 0, s, a);
       break;
