@@ -192,7 +192,8 @@ typedef struct lpa_graph_s* lpa_graph;
  *   (default) = none.  An allocation that would pass it fails with
  *   LPA_ERR_OOM like a failed hipMalloc; a failed lpa_create frees
  *   everything it allocated.  Buffers used only during lpa_create (checks,
- *   sort scratch) are freed before it returns and are not counted.
+ *   sort scratch) are freed before it returns and are not counted,
+ *   nor is the run state, 22 KiB whatever the graph.
  */
 typedef struct lpa_tuning {
   int32_t small4;

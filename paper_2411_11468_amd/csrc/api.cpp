@@ -631,8 +631,17 @@ static lpa_status create_impl(const lpa_csr* g, void* stream, const lpa_tuning* 
 
   // counters
   {
-    DevState* state = nullptr;
-    if (lpa_status e = G->dalloc(&state, 1)) return e;
+    // 22 KB whatever the graph: not held against memory_limit_kib, under which
+    // graphs of a few KB fit
+    void* q = nullptr;
+    const hipError_t e = hipMalloc(&q, sizeof(DevState));
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(LPA_ERR_OOM, std::string("hipMalloc failed for the run state: ") +
+                                   hipGetErrorString(e));
+    }
+    G->dev_allocs.push_back(q);
+    DevState* state = static_cast<DevState*>(q);
     G->st = &state->st;
     G->hist = state->hist;
     G->hist_cap = kHistInline;
