@@ -72,8 +72,11 @@ __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
 //
 // It is bound by latency at a minibatch's size: 4,096 samples are one round of
 // 64 workgroups, 128 to 144 products of 32 cycles per wave between six
-// barriers.  Four waves and 32 samples a workgroup, summed in another order,
-// had as many products per wave on twice the CUs.
+// barriers.  Measured there: 37 us with scalar LDS loops and 5,057 atomic adds
+// per workgroup, 20 us with this kernel and 4 us for k_mlp_reduce (17 us with
+// 32 samples and four waves a workgroup on twice the CUs, which sums in another
+// order); 10^6 samples 1.3 -> 0.55 ms.  The two tiles' chains taken in turn
+// product by product: 20 us as well.
 __global__ __launch_bounds__(kGradThreads) void k_mlp_grad(
     const float* __restrict__ p, const float* __restrict__ X, const float* __restrict__ y,
     const int32_t* __restrict__ idx, int64_t B, float inv_total, float pos_weight,
