@@ -346,12 +346,19 @@ hipError_t launch_validate(bool off64, const void* off, const int32_t* tgt,
 // weights, and the kernels need not read them).  Any that is not a whole number
 // of at most 2^18: other[1] receives 1 (else 64 of them sum exactly in any order).
 __global__ void k_unit_weights(const float* w, int64_t m, unsigned int* other) {
+  constexpr int U = 4;  // loads in flight
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   bool any = false, rounds = false;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const float x = __builtin_nontemporal_load(&w[e]);
-    any |= __float_as_uint(x) != 0x3F800000u;
-    rounds |= !(x >= 0.0f && x <= 262144.0f && x == truncf(x));
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += U * stride) {
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      x[u] = e + u * stride < m ? __builtin_nontemporal_load(&w[e + u * stride]) : 1.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      any |= __float_as_uint(x[u]) != 0x3F800000u;
+      rounds |= !(x[u] >= 0.0f && x[u] <= 262144.0f && x[u] == truncf(x[u]));
+    }
   }
   if (__any(any) && (threadIdx.x & 63) == 0) other[0] = 1u;
   if (__any(rounds) && (threadIdx.x & 63) == 0) other[1] = 1u;
